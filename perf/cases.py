@@ -89,11 +89,13 @@ def draw(rng):
     flops, elems = (1.2e13, 2.5e8) if ns == "bf16" else (1e12, 5e7)
     words, n_groups = [], rng.randint(1, 3)
     for _ in range(n_groups):
-        s = _side(rng, 16, 4096)
-        l = min(16384, max(s, _side(rng, s, 8 * s)))
-        rows, cols = (s, l) if rng.random() < 0.5 else (l, s)
         layout = "mats" if kind == "orth" else rng.choice(("mats", "mats", "stack", "packed", "heads"))
         per = {"packed": 2, "heads": 3}.get(layout, 1)
+        s = _side(rng, 16, 4096)
+        l = min(16384, max(s, _side(rng, s, 8 * s)))
+        while _dense(s, l, 5) * per * n_groups > flops or s * l * per * n_groups > elems:
+            s, l = s // 2, l // 2
+        rows, cols = (s, l) if rng.random() < 0.5 else (l, s)
         most = min(64 // per, 20 if kind == "orth" else 64, flops / n_groups / per / _dense(rows, cols, 5),
                    elems / n_groups / per / (rows * cols))
         words.append("%s:%d:%dx%d" % (layout, _log_int(rng, 1, max(1, most)), rows, cols))
