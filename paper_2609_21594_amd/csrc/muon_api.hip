@@ -903,8 +903,8 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
   };
   auto steps_of = [&](const Chunk& c) { return int(tables[size_t(c.cset)].size() / 3); };
   auto idle_of = [&](const Chunk& c) {
-    const bool tile = !ns_f32 && c.S % 256 == 0;
-    const int64_t t = tile ? c.S / 256 : c.S / 128;
+    const bool tile = muon::chunk_on_tiles(c.S, c.L, ns_f32, steps_of(c));
+    const int64_t t = tile ? (c.S + 255) / 256 : c.S / 128;
     const int64_t tiles = t * (t + 1) / 2 * c.count, slots = int64_t(tile ? cus : 2 * cus);
     return double(tiles) / double(((tiles + slots - 1) / slots) * slots) < 0.9;
   };

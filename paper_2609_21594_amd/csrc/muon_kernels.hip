@@ -396,8 +396,8 @@ struct GemmArgs {
   const char* Q;   int64_t q_mat;  int32_t ldq;
   int32_t k_slabs;                               // K * elem / 128
   int32_t tiles_m, tiles_n, syrk, tiles_per_mat;
+  int32_t m_ext, n_ext;                          // rows of P and of Q (tile kernel: multiples of 128)
   const char* E;   int64_t e_mat;  int32_t lde;   // epilogue input (A or X), bytes
-  const char* ET;  int64_t et_mat; int32_t ldet;  // the same values, transposed layout
   char* C;         int64_t c_mat;  int32_t ldc;   // output, direct orientation
   char* CT;        int64_t ct_mat; int32_t ldct;  // output, transposed orientation
   float alpha, beta;
@@ -703,10 +703,6 @@ __device__ __forceinline__ void store_out(u32x4_t* p, u32x4_t v) {
   if (MUON_NT) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
-__device__ __forceinline__ uint2 load_once(const uint2* p) {
-  if (MUON_NT) return uint2{__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y)};
-  return *p;
-}
 
 __device__ __forceinline__ uint2 pack_bf16x4(const float v[4]) {
   return uint2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
@@ -877,6 +873,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int wm = wave / WN, wn = wave % WN;
   static_assert(SLAB == 128 && NS == 2 && GPS == 4 && BM * 2 == 512 && BN * 2 == 512 && RPI == 8,
                 "slab geometry: 64 k of 256 rows, or 64 k-rows of 256 columns");
+  // The tile's rows of P and of Q inside the padded extents, which are
+  // multiples of 128: 256, or 128 in the last tile of an odd extent.  Loads
+  // of the rows (or columns) past them are sent 128 back, so they stay in
+  // bounds; what they produce is never written.
+  const int mv = min(BM, ga.m_ext - bm * BM), nv = min(BN, ga.n_ext - bn * BN);
 
   // ---- operand slabs ---------------------------------------------------------
   // A slab holds 64 consecutive k of the tile's 256 rows of P (and of Q), in
@@ -912,16 +913,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 #pragma unroll
   for (int i = 0; i < NLP; ++i) {
     const int r = wave * PR + RPI * i + lane / CPR;
-    pdo[i] = static_cast<uint32_t>(r * ga.ldp + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
+    pdo[i] = static_cast<uint32_t>((r < mv ? r : r - 128) * ga.ldp + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
     const int t = wave * (2 * NLP) + 2 * i + lane / 32;
-    pto[i] = static_cast<uint32_t>(t * ga.ldp + ((lane % 32) ^ ((t & 3) << 2)) * 16);
+    const int c = (lane % 32) ^ ((t & 3) << 2);
+    pto[i] = static_cast<uint32_t>(t * ga.ldp + (8 * c < mv ? c : c - 16) * 16);
   }
 #pragma unroll
   for (int i = 0; i < NLQ; ++i) {
     const int r = wave * QR + RPI * i + lane / CPR;
-    qdo[i] = static_cast<uint32_t>(r * ga.ldq + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
+    qdo[i] = static_cast<uint32_t>((r < nv ? r : r - 128) * ga.ldq + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
     const int t = wave * (2 * NLQ) + 2 * i + lane / 32;
-    qto[i] = static_cast<uint32_t>(t * ga.ldq + ((lane % 32) ^ ((t & 3) << 2)) * 16);
+    const int c = (lane % 32) ^ ((t & 3) << 2);
+    qto[i] = static_cast<uint32_t>(t * ga.ldq + (8 * c < nv ? c : c - 16) * 16);
   }
   const uint32_t lds0 = lds_offset(smem);
   // The loads of slab ks, one operand at a time: P's NLP instructions or Q's
@@ -1211,10 +1214,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   //    loop), except for a polynomial launched with e_loop = 0, which reads
   //    it here, through the staging area or coalesced in the direct layout.
   //  - Outputs are rounded to bfloat16 once and leave through LDS as whole
-  //    512-byte rows.  When the symmetric products must also write their
-  //    mirrored tile (see below), that one is staged instead and the direct
-  //    copy goes straight to memory.  X' needs no transposed copy, since the
-  //    next update reads X through transposing LDS reads.
+  //    512-byte rows.  The symmetric products write upper-triangle tiles only,
+  //    and X' needs no transposed copy: the next products read tiles below the
+  //    diagonal, and X, through transposing LDS reads.
   //  - The last step's parameter update runs in the parameter's layout:
   //    direct when it is s x l, natural when it is l x s.
   //  - Every load of the a*X (or A) term is issued before the first store,
@@ -1227,12 +1229,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int row_base = bm * BM + wm * (BM / WM) + 4 * fsel;
   const int col_base = bn * BN + wn * (BN / WN) + frow;
   char* const C = ga.C + mat * ga.c_mat;
-  char* const CT = ga.CT + mat * ga.ct_mat;
   const char* const E = ga.E + mat * ga.e_mat;
-  const char* const ET = ga.ET + mat * ga.et_mat;
-  constexpr int TST = BM * 2 + 8;             // staged transposed row, bytes
-  const bool stage_t = !QTR && ga.CT != nullptr;
-  const bool stage_c = !FINAL && !stage_t;
+  constexpr int TST = BM * 2 + 8;             // staged column, bytes
+  constexpr bool stage_c = !FINAL;
   const bool e_epi = EPI == EPI_POLY && !epoly;  // the term is read in the epilogue
   // Natural staging (the output tile, no epilogue input): each lane's 4
   // consecutive rows of one column go to LDS as they are, 8 bytes at
@@ -1253,70 +1252,36 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   }
 
   // Diagonal tiles of the symmetric products are written exactly symmetric:
-  // the value computed for (row, col) with row <= col also goes to (col, row).
-  // With a mirror (stage_t) this happens element by element in memory;
-  // otherwise in the LDS staging area below.
-  if (!FINAL && diag && stage_t) {
-    static_for<BI>([&](auto I) {
-      static_for<BJ>([&](auto J) {
-        static_for<4>([&](auto G) {
-          constexpr int i = decltype(I)::value, j = decltype(J)::value, g = decltype(G)::value;
-          const int row0 = row_base + i * 32 + 8 * g;
-          const int col = col_base + j * 32;
-          float v[4];
-          if (!e_epi) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = osc * acc[i][j][4 * g + q];
-          } else {
-            float e[4];
-            unpack_bf16x4(*reinterpret_cast<const uint2*>(ET + static_cast<int64_t>(col) * ga.ldet + row0 * 2), e);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              v[q] = EPI == EPI_POLY ? fmaf(ga.alpha, e[q], ga.beta * acc[i][j][4 * g + q])
-                                     : fmaf(ga.alpha, e[q], acc[i][j][4 * g + q]);
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int row = row0 + q;
-            if (row <= col) {
-              const uint16_t h = f32_to_bf16(v[q]);
-              *reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(row) * ga.ldc + col * 2) = h;
-              *reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(col) * ga.ldc + row * 2) = h;
-            }
-          }
-        });
-      });
-    });
-    return;
-  }
-
-  // The symmetric products also write the mirrored tile, staged through LDS,
-  // unless their consumers read the upper triangle only (CT null).  Without
-  // a mirror, the output tile itself goes through LDS (stage_c): the a*X (or
-  // A) tile is loaded into it as whole 512-byte rows by direct-to-LDS loads,
-  // every lane combines its values in place, and the result leaves as whole
-  // rows again, which measured faster than 64-byte row pieces to and from
-  // the registers.  Staged rows are 512 bytes; row r holds 16-byte chunk c at
-  // position c ^ 4*(r % 4), so the 8 rows x 64 bytes a lane instruction
-  // touches spread over all banks.
+  // the value computed for (row, col) with row <= col also goes to (col, row),
+  // in the LDS staging area.  The output tile goes through LDS because whole
+  // 512-byte rows measured faster than 64-byte row pieces from the registers;
+  // a polynomial with c = 0 also takes its A tile there, loaded as whole rows
+  // and combined in place.  Staged rows are then 512 bytes; row r holds
+  // 16-byte chunk c at position c ^ 4*(r % 4), so the 8 rows x 64 bytes a lane
+  // instruction touches spread over all banks.
   auto cpos = [](int r, int b) {  // staged byte position of tile row r, byte b
     return r * (BN * 2) + ((((b >> 4) ^ ((r & 3) << 2))) << 4) + (b & 15);
   };
-  // The last step with a bfloat16 parameter whose 256 x 256 block lies fully
-  // inside the matrix (and 16-byte rows): W goes through LDS the same way,
-  // loaded and written back as whole 512-byte rows of its own layout.  Its
-  // staged row r holds chunk c at c ^ key(r), key(r) = 4*(r % 4) + (r / 4) % 4,
-  // which spreads both the direct accesses (8 rows x 64 bytes) and the
-  // natural ones (32 rows x 16 bytes) over all banks.
+  // The last step with a bfloat16 parameter whose rows take 16-byte accesses:
+  // W goes through LDS the same way, loaded and written back as whole
+  // 512-byte rows of its own layout.  Its staged row r holds chunk c at
+  // c ^ key(r), key(r) = 4*(r % 4) + (r / 4) % 4, which spreads both the
+  // direct accesses (8 rows x 64 bytes) and the natural ones (32 rows x 16
+  // bytes) over all banks.  At the matrix's edge the block has wrv rows and
+  // wcv columns (a multiple of 8): loads past them repeat the last row or
+  // chunk, and only the block is written back.
   bool stage_w = false;
-  if constexpr (FINAL && FK == 0 && PDT == DT_BF16)
-    stage_w = v4 && md->cols % 8 == 0 && md->ld % 8 == 0 && md->rb >= md->rows &&
-              md->ld * 2 < kTileMaxRowBytes && (bm + 1) * BM <= ga.s && (bn + 1) * BN <= ga.l;
+  const int wr0 = tr ? bn * BN : bm * BM, wc0 = tr ? bm * BM : bn * BN;  // W block origin
+  int wrv = 0, wcv = 0;
+  if constexpr (FINAL && FK == 0 && PDT == DT_BF16) {
+    stage_w = v4 && md->cols % 8 == 0 && md->ld % 8 == 0 && md->rb >= md->rows && md->ld * 2 < kTileMaxRowBytes;
+    wrv = min(BM, md->rows - wr0);
+    wcv = min(BM, md->cols - wc0);
+  }
   auto wpos = [](int r, int b) {
     const int key = ((r & 3) << 2) | ((r >> 2) & 3);
     return r * 512 + (((b >> 4) ^ key) << 4) + (b & 15);
   };
-  const int wr0 = tr ? bn * BN : bm * BM, wc0 = tr ? bm * BM : bn * BN;  // W block origin
   // (every wave finished its operand-slab reads before the last slab's
   // barrier, so the staging area, which overlaps the slabs, is free)
   if (stage_w) {
@@ -1329,10 +1294,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     for (int k = 0; k < KW; ++k) {
       const int row = 2 * (wave * KW + k) + lane / 32;
       const int c = (lane % 32) ^ (((row & 3) << 2) | ((row >> 2) & 3));
-      load_lds16(wb, static_cast<uint32_t>(row) * ldw + static_cast<uint32_t>(c * 16), lds0 + (wave * KW + k) * 1024);
+      load_lds16(wb, static_cast<uint32_t>(min(row, wrv - 1)) * ldw + static_cast<uint32_t>(min(c * 16, wcv * 2 - 16)),
+                 lds0 + (wave * KW + k) * 1024);
     }
   }
-  if (e_epi && stage_c) {
+  if (e_epi) {
     // a wave instruction fills 2 staged rows (1 KB); lane l: row 2k + l/32,
     // position l % 32, which holds chunk (l % 32) ^ 4*(row % 4)
     constexpr int KE = BM * BN * 2 / 1024 / NW;   // load instructions per wave
@@ -1343,7 +1309,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     for (int k = 0; k < KE; ++k) {
       const int row = 2 * (wave * KE + k) + lane / 32;
       const int c = (lane % 32) ^ ((row & 3) << 2);
-      load_lds16(eb, static_cast<uint32_t>(row * ga.lde + c * 16), lds0 + (wave * KE + k) * 1024);
+      load_lds16(eb, static_cast<uint32_t>((row < mv ? row : row - 128) * ga.lde + (8 * c < nv ? c : c - 16) * 16),
+                 lds0 + (wave * KE + k) * 1024);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -1359,14 +1326,12 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
           constexpr int i = decltype(I)::value, j = decltype(J)::value, g = decltype(G)::value;
           const int row0 = row_base + i * 32 + 8 * g;
           const int c0 = col_base + j * 32 - q4;
-          if (e_epi && !stage_c)
-            ev[i][j][g] = load_once(reinterpret_cast<const uint2*>(E + static_cast<int64_t>(row0 + q4) * ga.lde + c0 * 2));
-          else if (e_epi && diag)  // the mirrored writes below reach other lanes' inputs
+          if (e_epi && diag)  // the mirrored writes below reach other lanes' inputs
             ev[i][j][g] = *reinterpret_cast<const uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2));
         });
       });
     });
-    if (e_epi && stage_c && diag) __syncthreads();
+    if (e_epi && diag) __syncthreads();
     if (stage_w) {  // the W block has landed in LDS
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -1392,7 +1357,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
           if (!FINAL || tr) {  // natural layout
             if (e_epi) {
               float e[4];
-              const uint2 ed = (stage_c && !diag) ? *reinterpret_cast<const uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2))
+              const uint2 ed = !diag ? *reinterpret_cast<const uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2))
                                                   : ev[i][j][g];
               unpack_bf16x4(quad_transpose_bf16(ed), e);
 #pragma unroll
@@ -1400,7 +1365,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
             }
             if (stage_n) {
               *reinterpret_cast<uint2*>(smem + (col - bn * BN) * TST + (row0 - bm * BM) * 2) = pack_bf16x4(v);
-            } else if (!FINAL && diag) {  // stage_c: (row, col) and (col, row) for row <= col
+            } else if (!FINAL && diag) {  // (row, col) and (col, row) for row <= col
               const int cl = col - bn * BN;
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
@@ -1414,12 +1379,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
             } else if (!FINAL) {
               const uint2 p = pack_bf16x4(v);
               const uint2 d = quad_transpose_bf16(p);  // row row0 + q4, columns c0 .. c0 + 3
-              if (stage_c) {
-                *reinterpret_cast<uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2)) = d;
-              } else {
-                *reinterpret_cast<uint2*>(smem + (col - bn * BN) * TST + (row0 - bm * BM) * 2) = p;
-                store_out(reinterpret_cast<uint2*>(C + static_cast<int64_t>(row0 + q4) * ga.ldc + c0 * 2), d);
-              }
+              *reinterpret_cast<uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2)) = d;
             } else if (stage_w) {      // parameter is l x s: elements (col, row0 .. row0 + 3)
               w_update(smem + wpos(col - wr0, (row0 - wc0) * 2), v);
             } else if (col < ga.l) {
@@ -1448,6 +1408,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     // updated W rows (512 bytes each) -> W, 16 bytes a thread
     for (int idx = threadIdx.x; idx < BM * 32; idx += 64 * NW) {
       const int r = idx >> 5, ch = idx & 31;
+      if (r >= wrv || ch * 8 >= wcv) continue;
       *reinterpret_cast<u32x4_t*>(static_cast<char*>(md->W) + (static_cast<int64_t>(wr0 + r) * md->ld + wc0) * 2 +
                                   ch * 16) = *reinterpret_cast<const u32x4_t*>(smem + wpos(r, ch * 16));
     }
@@ -1468,6 +1429,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     auto out_row = [&](int it, auto diagc) __attribute__((always_inline)) {
       const int task = it * NW + wave;                 // 4 rows x 128 columns
       const int R = 4 * (task >> 1), C0 = 128 * (task & 1) + 32 * G;
+      if (R >= mv || 128 * (task & 1) >= nv) return;   // (wave-uniform)
       const char* a = smem + C0 * TST + ra + 2 * R;
       const uint2 lo = tr_read_b64(a), hi = tr_read_b64(a + 4 * TST);
       u32x4_t v{lo.x, lo.y, hi.x, hi.y};
@@ -1499,22 +1461,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     constexpr int CH = BN * 2 / 16;
     for (int idx = threadIdx.x; idx < BM * CH; idx += 64 * NW) {
       const int r = idx / CH, ch = idx - r * CH;
+      if (r >= mv || ch * 8 >= nv) continue;
       store_out(reinterpret_cast<u32x4_t*>(C + static_cast<int64_t>(bm * BM + r) * ga.ldc + bn * BN * 2 + ch * 16),
                 *reinterpret_cast<const u32x4_t*>(smem + cpos(r, ch * 16)));
-    }
-    __syncthreads();  // the next tile's loads overwrite the staging area
-  }
-  if (stage_t) {
-    __syncthreads();
-    // transposed tile rows (BM bf16 = BM*2 bytes each) -> CT, 16 bytes a thread
-    constexpr int CH = BM * 2 / 16;
-    for (int idx = threadIdx.x; idx < BN * CH; idx += 64 * NW) {
-      const int c = idx / CH, ch = idx - c * CH;
-      const char* src = smem + c * TST + ch * 16;
-      const uint2 lo = *reinterpret_cast<const uint2*>(src);
-      const uint2 hi = *reinterpret_cast<const uint2*>(src + 8);
-      store_out(reinterpret_cast<u32x4_t*>(CT + static_cast<int64_t>(bn * BN + c) * ga.ldct + bm * BM * 2 + ch * 16),
-                u32x4_t{lo.x, lo.y, hi.x, hi.y});
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
   }
@@ -1626,8 +1575,10 @@ int device_cu_count() {
 template <class Cfg>
 hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   // ga arrives in 128 x 128 tiles and 128-byte slabs
-  ga.tiles_m = ga.tiles_m * kTile / Cfg::BM;
-  ga.tiles_n = ga.tiles_n * kTile / Cfg::BN;
+  ga.m_ext = ga.tiles_m * kTile;
+  ga.n_ext = ga.tiles_n * kTile;
+  ga.tiles_m = (ga.m_ext + Cfg::BM - 1) / Cfg::BM;
+  ga.tiles_n = (ga.n_ext + Cfg::BN - 1) / Cfg::BN;
   ga.tiles_per_mat = ga.syrk ? ga.tiles_m * (ga.tiles_m + 1) / 2 : ga.tiles_m * ga.tiles_n;
   ga.k_slabs = ga.k_slabs * 128 / Cfg::SLAB;
   ga.total_tiles = ga.tiles_per_mat * nmat;
@@ -1669,8 +1620,10 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
   gr.start[0] = 0;
   for (int c = 0; c < n; ++c) {
     GemmArgs ga = gas[c];
-    ga.tiles_m = ga.tiles_m * kTile / Cfg::BM;
-    ga.tiles_n = ga.tiles_n * kTile / Cfg::BN;
+    ga.m_ext = ga.tiles_m * kTile;
+    ga.n_ext = ga.tiles_n * kTile;
+    ga.tiles_m = (ga.m_ext + Cfg::BM - 1) / Cfg::BM;
+    ga.tiles_n = (ga.n_ext + Cfg::BN - 1) / Cfg::BN;
     ga.tiles_per_mat = ga.syrk ? ga.tiles_m * (ga.tiles_m + 1) / 2 : ga.tiles_m * ga.tiles_n;
     ga.k_slabs = ga.k_slabs * 128 / Cfg::SLAB;
     ga.total_tiles = ga.tiles_per_mat * nmats[c];
@@ -1702,16 +1655,10 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
   return hipGetLastError();
 }
 
-// The 256 x 256 kernel runs the bf16 products whose padded extents are
-// multiples of 256 (and whose rows fit its offsets): the symmetric ones when
-// S is, the update ones (which read X through transposing LDS reads) when S
-// and L are.  Everything else runs on the 128 x 128 kernel, whose update
-// reads X^T and whose offsets are 64-bit.
+// The products on the 128 x 128 kernel: fp32 Newton-Schulz, and bf16 rows
+// past the 256 x 256 kernel's 32-bit offsets (chunk_on_tiles).
 template <typename T>
 hipError_t launch_gemm(int epi, GemmArgs ga, int nmat, hipStream_t st) {
-  if (sizeof(T) == 2 && ga.tiles_m % 2 == 0 && ga.syrk && ga.ldp < kTileMaxRowBytes &&
-      ga.ldq < kTileMaxRowBytes && (!ga.E || ga.lde < kTileMaxRowBytes))
-    return launch_tile<CfgSquare>(epi, ga, nmat, st);
   const dim3 grid(static_cast<unsigned>(ga.tiles_per_mat) * nmat), block(256);
   switch (epi) {
     case EPI_GRAM: hipLaunchKernelGGL((k_gemm_nt<T, EPI_GRAM>), grid, block, 0, st, ga); break;
@@ -2221,10 +2168,10 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
   const int nparts = static_cast<int>(norm_tiles(cg.S, cg.L));
   const double gsz = sizeof(GT), xsz = sizeof(XT);
   const double psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
-  // bf16 with S and L multiples of 256: the update products run on the
-  // 256 x 256 kernel and read X through transposing LDS reads, so no X^T is
-  // kept (K = 0 applies X0 from whichever layout matches the parameter).
-  const bool qtr = !chunk_keeps_xt(cg.S, cg.L, sizeof(XT) == 4, K);
+  // On the 256 x 256 kernel the update products read X through transposing
+  // LDS reads, so no X^T is kept (K = 0 applies X0 from whichever layout
+  // matches the parameter).
+  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
   XT* const xt0 = qtr ? nullptr : static_cast<XT*>(wb.XT[0]);
   hipError_t e;
   XT* const x0 = static_cast<XT*>(wb.X[0]);
@@ -2284,7 +2231,7 @@ struct StepProducts {
 template <typename XT>
 StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb,
                            const StepScalars& sc, const float* coeffs, int K, int k, int cur) {
-  const bool qtr = !chunk_keeps_xt(cg.S, cg.L, sizeof(XT) == 4, K);
+  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
   const double nm = cg.nmat;
   const double s = cg.s, l = cg.l;
   const double xsz = sizeof(XT);
@@ -2294,18 +2241,11 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   const int64_t matA = static_cast<int64_t>(cg.S) * cg.S * es;
   const int ts = cg.S / kTile, tl = cg.L / kTile;
   // Work accounting: `flops` is the dense count of each product on the real
-  // extents (Eq. 1); `exec` is what the MFMAs execute: padded extents, and
-  // for the symmetric products the upper tiles of the kernel that runs them
-  // (256 x 256 tiles when bf16, S a multiple of 256 and the rows short
-  // enough, else 128 x 128; see launch_gemm).
-  auto upper_frac = [&](bool tile) {
-    const int t = tile ? cg.S / 256 : ts;
-    return double(t * (t + 1) / 2) / double(t * t);
-  };
-  const bool tile_sym = sizeof(XT) == 2 && cg.S % 256 == 0;
-  const double gram_frac = upper_frac(tile_sym && tile_rows_fit(cg.S, cg.L, es));
-  const double poly_frac = upper_frac(tile_sym && tile_rows_fit(cg.S, cg.S, es));
-  const double Sp = cg.S, Lp = cg.L;
+  // extents (Eq. 1); `exec` is what the MFMAs execute: whole tiles of the
+  // kernel that runs the products, and of the symmetric ones the upper tiles.
+  const int te = qtr ? 256 : kTile;
+  const double TS = (cg.S + te - 1) / te, TL = (cg.L + te - 1) / te;
+  const double upper = TS * (TS + 1) / 2 * te * te, Sp = cg.S, Lp = cg.L;
   StepProducts r{};
   const float a = coeffs[3 * k], b = coeffs[3 * k + 1], c = coeffs[3 * k + 2];
   const char* X = static_cast<const char*>(wb.X[cur]);
@@ -2322,7 +2262,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   // reads them as upper-triangle tiles (mode 1): no mirrored tile is
   // written.  Otherwise the lower triangle is written as the mirror.
   if (!qtr) { g.CT = g.C; g.ct_mat = matA; g.ldct = g.ldc; }
-  r.f[0] = nm * 2 * s * s * l; r.x[0] = nm * 2 * Sp * Sp * Lp * gram_frac; r.b[0] = nm * (s * l + s * s) * xsz;
+  r.f[0] = nm * 2 * s * s * l; r.x[0] = nm * 2 * upper * Lp; r.b[0] = nm * (s * l + s * s) * xsz;
   // B = b A + c A A^T: M = N = K = S.
   GemmArgs& pp = r.poly;
   pp = g;
@@ -2331,11 +2271,10 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   pp.Q = pp.P; pp.q_mat = matA; pp.ldq = pp.ldp;
   pp.k_slabs = cg.S * es / 128;
   pp.E = pp.P; pp.e_mat = matA; pp.lde = pp.ldp;
-  pp.ET = pp.P; pp.et_mat = matA; pp.ldet = pp.ldp;  // A is symmetric
   pp.C = static_cast<char*>(wb.B); pp.CT = qtr ? nullptr : pp.C;
   pp.p_mode = pp.q_mode = qtr ? 1 : 0;
   pp.alpha = b; pp.beta = c;
-  r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * Sp * Sp * Sp * poly_frac; r.b[1] = nm * 2 * s * s * xsz;
+  r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * upper * Sp; r.b[1] = nm * 2 * s * s * xsz;
   // X' = a X + B X: M = S, N = L, K = S.  The second operand is X^T (N x K,
   // K contiguous) on the 128 x 128 kernel, X itself (K x N) under qtr.
   GemmArgs& u = r.upd;
@@ -2353,7 +2292,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   u.alpha = a;
   u.s = cg.s; u.l = cg.l;
   u.xscale = k == 0 ? wb.xscale : nullptr;  // X1 = r (a X~ + B0 X~)
-  r.f[2] = nm * 2 * s * s * l; r.x[2] = nm * 2 * Sp * Sp * Lp;
+  r.f[2] = nm * 2 * s * s * l; r.x[2] = nm * 2 * (TS * te) * (TL * te) * Sp;
   r.last = k + 1 == K;
   if (!r.last) {
     u.C = static_cast<char*>(wb.X[cur ^ 1]); u.c_mat = matX; u.ldc = cg.L * es;
@@ -2375,27 +2314,28 @@ hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBu
   if (wb.sync) return run_small<GT, XT>(cg, d_desc, wb, sc, coeffs, K, st, timer);
   hipError_t e = run_prologue_t<GT, XT>(cg, d_desc, wb, sc, coeffs, K, st, timer);
   if (e != hipSuccess || K == 0) return e;
-  const bool qtr = !chunk_keeps_xt(cg.S, cg.L, sizeof(XT) == 4, K);
+  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
   const int nmat = cg.nmat;
+  auto launch = [&](int epi, const GemmArgs& ga) {
+    return qtr ? launch_tile<CfgSquare>(epi, ga, nmat, st) : launch_gemm<XT>(epi, ga, nmat, st);
+  };
   int cur = 0;
   for (int k = 0; k < K; ++k) {
     const StepProducts sp = step_products<XT>(cg, d_desc, wb, sc, coeffs, K, k, cur);
     {
       Timed tm(timer, KK_GRAM, st);
-      if ((e = launch_gemm<XT>(EPI_GRAM, sp.gram, nmat, st)) != hipSuccess) return e;
+      if ((e = launch(EPI_GRAM, sp.gram)) != hipSuccess) return e;
       tm.done(sp.f[0], sp.x[0], sp.b[0]);
     }
     {
       Timed tm(timer, KK_POLY, st);
-      if ((e = launch_gemm<XT>(EPI_POLY, sp.poly, nmat, st)) != hipSuccess) return e;
+      if ((e = launch(EPI_POLY, sp.poly)) != hipSuccess) return e;
       tm.done(sp.f[1], sp.x[1], sp.b[1]);
     }
     {
       const int epi = sp.last ? EPI_FINAL : EPI_UPDATE;
       Timed tm(timer, sp.last ? KK_FINAL : KK_UPDATE, st);
-      if ((e = qtr ? launch_tile<CfgSquare>(epi, sp.upd, nmat, st) : launch_gemm<XT>(epi, sp.upd, nmat, st)) !=
-          hipSuccess)
-        return e;
+      if ((e = launch(epi, sp.upd)) != hipSuccess) return e;
       tm.done(sp.f[2], sp.x[2], sp.b[2]);
     }
     cur ^= 1;
