@@ -22,6 +22,7 @@
 // every step (padded rows/columns of X, A and B stay exactly zero).
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -803,12 +804,17 @@ struct TileCfg {
   static constexpr int LDS = NS * (BM + BN) * SLAB;
   static_assert(LDS <= 160 * 1024, "LDS budget");
 };
-// 256 x 256, 8 wavefronts, one workgroup per CU (symmetric products).
+// 256 x 256, 8 wavefronts of 128 x 64, one workgroup per CU.
 #ifndef MUON_SQ_SLAB
 #define MUON_SQ_SLAB 128
 #define MUON_SQ_STAGES 2
 #endif
 using CfgSquare = TileCfg<256, 256, 2, 4, MUON_SQ_SLAB, MUON_SQ_STAGES, 2>;
+// 128 x 128, 4 wavefronts of 64 x 64, two workgroups per CU: for launches
+// whose 256 x 256 tiles would leave CUs without work (small_tiles).  Every
+// element sees the same operations in the same order on both, so the choice
+// never changes a result.
+using CfgQuarter = TileCfg<128, 128, 2, 2, 128, 2, 2>;
 
 // Tile `logical` of the launch: matrix-major; inside a matrix, banded
 // (GS / GM tile-rows per band, column by column inside a band).
@@ -871,8 +877,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  static_assert(SLAB == 128 && NS == 2 && GPS == 4 && BM * 2 == 512 && BN * 2 == 512 && RPI == 8,
-                "slab geometry: 64 k of 256 rows, or 64 k-rows of 256 columns");
+  static_assert(SLAB == 128 && NS == 2 && GPS == 4 && (BM == 256 || BM == 128) && BN == BM && RPI == 8,
+                "slab geometry: 64 k of BM rows, or 64 k-rows of BM columns");
+  constexpr int TRB = BM * 2;                 // bytes of a transposed slab row, of a staged tile row
+  constexpr int TRC = TRB / 16;               // its 16-byte chunks
+  constexpr int TRI = 1024 / TRB;             // transposed rows one wave load instruction fills
   // The tile's rows of P and of Q inside the padded extents, which are
   // multiples of 128: 256, or 128 in the last tile of an odd extent.  Loads
   // of the rows (or columns) past them are sent 128 back, so they stay in
@@ -914,16 +923,16 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   for (int i = 0; i < NLP; ++i) {
     const int r = wave * PR + RPI * i + lane / CPR;
     pdo[i] = static_cast<uint32_t>((r < mv ? r : r - 128) * ga.ldp + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
-    const int t = wave * (2 * NLP) + 2 * i + lane / 32;
-    const int c = (lane % 32) ^ ((t & 3) << 2);
+    const int t = wave * (TRI * NLP) + TRI * i + lane / TRC;
+    const int c = (lane % TRC) ^ ((t & 3) << 2);
     pto[i] = static_cast<uint32_t>(t * ga.ldp + (8 * c < mv ? c : c - 16) * 16);
   }
 #pragma unroll
   for (int i = 0; i < NLQ; ++i) {
     const int r = wave * QR + RPI * i + lane / CPR;
     qdo[i] = static_cast<uint32_t>((r < nv ? r : r - 128) * ga.ldq + ((lane % CPR) ^ ((r >> SH) & (CPR - 1))) * 16);
-    const int t = wave * (2 * NLQ) + 2 * i + lane / 32;
-    const int c = (lane % 32) ^ ((t & 3) << 2);
+    const int t = wave * (TRI * NLQ) + TRI * i + lane / TRC;
+    const int c = (lane % TRC) ^ ((t & 3) << 2);
     qto[i] = static_cast<uint32_t>(t * ga.ldq + (8 * c < nv ? c : c - 16) * 16);
   }
   const uint32_t lds0 = lds_offset(smem);
@@ -981,7 +990,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     const int G = lane >> 4, L = lane & 15;
     const int row = 8 * (G >> 1) + (L >> 2);
     const int cb = 2 * c0 + 32 * (G & 1) + 8 * (L & 3);
-    return row * 512 + (cb ^ ((L >> 2) << 6));
+    return row * TRB + (cb ^ ((L >> 2) << 6));
   };
   int tpo[BI], tqo[BJ];
 #pragma unroll
@@ -1008,11 +1017,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   constexpr int EPS = (BN / WN) / 64;           // P slabs holding a wave's columns of A
   static_assert(EPS == 1 || EPS == 2, "A term: one or two slabs per wave");
   constexpr int EJ = BJ / EPS;                  // 32-column blocks per such slab
+  constexpr int ERS = (BM / WM) / 64;           // Q slabs holding a wave's rows of X
+  static_assert(ERS * 2 == BI, "X term: whole slabs per wave");
   const bool epoly = EPI == EPI_POLY && ga.e_loop != 0;
   int e_ks0 = -1, e_ks1 = -1;
   if (EUPD) {
-    e_ks0 = bm * (BM / 64) + 2 * wm;
-    e_ks1 = e_ks0 + 1;
+    e_ks0 = bm * (BM / 64) + ERS * wm;
+    if (ERS > 1) e_ks1 = e_ks0 + 1;
   } else if (epoly) {
     // the wave's BN / WN columns are EPS slabs of 64 k
     e_ks0 = bn * (BN / 64) + wn * EPS;
@@ -1026,7 +1037,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 #pragma unroll
       for (int gp = 0; gp < 2; ++gp) {
         if (EUPD)  // Q slab: row k holds chunk c at c ^ 4(k % 4)
-          eo[j][gp] = OPQ + (4 * (G >> 1) + (L >> 2)) * 512 +
+          eo[j][gp] = OPQ + (4 * (G >> 1) + (L >> 2)) * TRB +
                       ((2 * (wn * (BN / WN) + 32 * j) + 32 * (G & 1) + 8 * (L & 3)) ^ ((L >> 2) << 6));
         else       // P slab: row r holds chunk c at c ^ ((r >> 1) % 8)
           eo[j][gp] = (wm * (BM / WM) + 4 * (G >> 1) + (L >> 2)) * SLAB +
@@ -1045,7 +1056,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       static_for<nj>([&](auto J) {
         static_for<4>([&](auto Gc) {
           constexpr int jj = decltype(J)::value, j = j0 + jj, g = decltype(Gc)::value;
-          ev[jj][g] = EUPD ? tr_read_b64(sp + eo[j][0] + (32 * (i & 1) + 8 * g) * 512)
+          ev[jj][g] = EUPD ? tr_read_b64(sp + eo[j][0] + (32 * (i & 1) + 8 * g) * TRB)
                            : tr_read_b64(sp + eo[j][g & 1] + (32 * i + 8 * g) * SLAB);
         });
       });
@@ -1075,8 +1086,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 #pragma unroll
     for (int i = 0; i < BI; ++i) {
       if (PT) {
-        const char* q = sp + tpo[i] + grp * 16 * 512;
-        const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * 512);
+        const char* q = sp + tpo[i] + grp * 16 * TRB;
+        const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * TRB);
         fa[set][i] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
       } else {
         fa[set][i] = *reinterpret_cast<const u32x4_t*>(sp + a_off + i * 32 * SLAB + pos);
@@ -1085,8 +1096,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
       if (QT) {
-        const char* q = sp + tqo[j] + grp * 16 * 512;
-        const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * 512);
+        const char* q = sp + tqo[j] + grp * 16 * TRB;
+        const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * TRB);
         fb[set][j] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
       } else {
         fb[set][j] = *reinterpret_cast<const u32x4_t*>(sp + b_off + j * 32 * SLAB + pos);
@@ -1134,7 +1145,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     if constexpr (decltype(ec)::value) {
       if (ks == e_ks0 || ks == e_ks1) {  // wave-uniform; at most twice a tile
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (EUPD) {
+        if constexpr (EUPD && ERS == 1) {
+          add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
+        } else if constexpr (EUPD) {
           if (ks == e_ks0) add_e(sp, I_<0>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
           else add_e(sp, I_<2>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
         } else if constexpr (EPS == 1) {
@@ -1222,6 +1235,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   //  - Every load of the a*X (or A) term is issued before the first store,
   //    so one memory latency is exposed instead of one per block.
   const bool diag = ga.syrk && bm == bn;
+  // The 256 x 256 kernel reads the diagonal 256 x 256 blocks of A and B
+  // whole: of such a block, the 128 x 128 kernel also writes the quarter below
+  // the diagonal, the mirror of its (even, odd) tile.
+  const bool pair_mirror = BM == 128 && ga.syrk && (bm & 1) == 0 && bn == bm + 1;
   const MatDesc* md = FINAL ? ga.desc + mat : nullptr;
   const bool tr = FINAL ? md->transposed != 0 : false;
   const bool v4 = FINAL ? md->vec4_ok != 0 : false;
@@ -1280,7 +1297,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   }
   auto wpos = [](int r, int b) {
     const int key = ((r & 3) << 2) | ((r >> 2) & 3);
-    return r * 512 + (((b >> 4) ^ key) << 4) + (b & 15);
+    return r * TRB + (((b >> 4) ^ key) << 4) + (b & 15);
   };
   // (every wave finished its operand-slab reads before the last slab's
   // barrier, so the staging area, which overlaps the slabs, is free)
@@ -1292,23 +1309,23 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     const uint32_t lds0 = lds_offset(smem);
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
-      const int row = 2 * (wave * KW + k) + lane / 32;
-      const int c = (lane % 32) ^ (((row & 3) << 2) | ((row >> 2) & 3));
+      const int row = TRI * (wave * KW + k) + lane / TRC;
+      const int c = (lane % TRC) ^ (((row & 3) << 2) | ((row >> 2) & 3));
       load_lds16(wb, static_cast<uint32_t>(min(row, wrv - 1)) * ldw + static_cast<uint32_t>(min(c * 16, wcv * 2 - 16)),
                  lds0 + (wave * KW + k) * 1024);
     }
   }
   if (e_epi) {
-    // a wave instruction fills 2 staged rows (1 KB); lane l: row 2k + l/32,
-    // position l % 32, which holds chunk (l % 32) ^ 4*(row % 4)
+    // a wave instruction fills TRI staged rows (1 KB); lane l: row
+    // TRI k + l / TRC, position l % TRC, which holds chunk (l % TRC) ^ 4*(row % 4)
     constexpr int KE = BM * BN * 2 / 1024 / NW;   // load instructions per wave
     static_assert(KE * NW * 1024 == BM * BN * 2, "E tile: whole instructions per wave");
     const char* eb = E + static_cast<int64_t>(bm) * BM * ga.lde + bn * BN * 2;
     const uint32_t lds0 = lds_offset(smem);
 #pragma unroll
     for (int k = 0; k < KE; ++k) {
-      const int row = 2 * (wave * KE + k) + lane / 32;
-      const int c = (lane % 32) ^ ((row & 3) << 2);
+      const int row = TRI * (wave * KE + k) + lane / TRC;
+      const int c = (lane % TRC) ^ ((row & 3) << 2);
       load_lds16(eb, static_cast<uint32_t>((row < mv ? row : row - 128) * ga.lde + (8 * c < nv ? c : c - 16) * 16),
                  lds0 + (wave * KE + k) * 1024);
     }
@@ -1405,9 +1422,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   blocks();
   if (stage_w) {
     __syncthreads();
-    // updated W rows (512 bytes each) -> W, 16 bytes a thread
-    for (int idx = threadIdx.x; idx < BM * 32; idx += 64 * NW) {
-      const int r = idx >> 5, ch = idx & 31;
+    // updated W rows -> W, 16 bytes a thread
+    for (int idx = threadIdx.x; idx < BM * TRC; idx += 64 * NW) {
+      const int r = idx / TRC, ch = idx % TRC;
       if (r >= wrv || ch * 8 >= wcv) continue;
       *reinterpret_cast<u32x4_t*>(static_cast<char*>(md->W) + (static_cast<int64_t>(wr0 + r) * md->ld + wc0) * 2 +
                                   ch * 16) = *reinterpret_cast<const u32x4_t*>(smem + wpos(r, ch * 16));
@@ -1428,8 +1445,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     static_assert(KC * NW * 1024 == BM * BN * 2, "copy-out: whole instructions per wave");
     auto out_row = [&](int it, auto diagc) __attribute__((always_inline)) {
       const int task = it * NW + wave;                 // 4 rows x 128 columns
-      const int R = 4 * (task >> 1), C0 = 128 * (task & 1) + 32 * G;
-      if (R >= mv || 128 * (task & 1) >= nv) return;   // (wave-uniform)
+      constexpr int CB = BN / 128;
+      const int R = 4 * (task / CB), C0 = 128 * (task % CB) + 32 * G;
+      if (R >= mv || 128 * (task % CB) >= nv) return;  // (wave-uniform)
       const char* a = smem + C0 * TST + ra + 2 * R;
       const uint2 lo = tr_read_b64(a), hi = tr_read_b64(a + 4 * TST);
       u32x4_t v{lo.x, lo.y, hi.x, hi.y};
@@ -1453,6 +1471,15 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     } else {
 #pragma unroll
       for (int it = 0; it < KC; ++it) out_row(it, std::false_type{});
+      if (pair_mirror) {  // its rows are the staged columns
+        for (int idx = threadIdx.x; idx < BN * TRC; idx += 64 * NW) {
+          const int c = idx / TRC, ch = idx % TRC;
+          const char* m = smem + c * TST + ch * 16;
+          const uint2 l0 = *reinterpret_cast<const uint2*>(m), l1 = *reinterpret_cast<const uint2*>(m + 8);
+          store_out(reinterpret_cast<u32x4_t*>(C + static_cast<int64_t>(bn * BN + c) * ga.ldc + bm * BM * 2 + ch * 16),
+                    u32x4_t{l0.x, l0.y, l1.x, l1.y});
+        }
+      }
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
   } else if (stage_c) {
@@ -1464,6 +1491,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       if (r >= mv || ch * 8 >= nv) continue;
       store_out(reinterpret_cast<u32x4_t*>(C + static_cast<int64_t>(bm * BM + r) * ga.ldc + bn * BN * 2 + ch * 16),
                 *reinterpret_cast<const u32x4_t*>(smem + cpos(r, ch * 16)));
+    }
+    if (pair_mirror) {
+      for (int idx = threadIdx.x; idx < BN * BM; idx += 64 * NW) {
+        const int c = idx / BM, r = idx % BM;
+        *reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(bn * BN + c) * ga.ldc + (bm * BM + r) * 2) =
+            *reinterpret_cast<const uint16_t*>(smem + cpos(r, c * 2));
+      }
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
   }
@@ -1653,6 +1687,29 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
     }
   }
   return hipGetLastError();
+}
+
+// Whether a launch runs on 128 x 128 tiles (CfgQuarter): where 256 x 256
+// tiles would leave many CUs idle, in a last round or in the only one.
+// The model is fitted to single launches on an MI355X (us, nk slabs of 64 k):
+//   256 x 256: each round of one tile per CU takes (1.15 + 0.4 f) nk + 4 + 8 f,
+//     f the share of the rounds' slots that have a tile (a full chip runs at
+//     a lower clock and misses more often in L2);
+//   128 x 128: a round of two tiles per CU takes nk + 5, a last round costs
+//     about half of one more, and a single round is a little cheaper.
+// Measured per launch, 256 / 128: Gram of 2048 x 5632, three matrices 119 / 89,
+// one 114 / 73; update of 512 x 512, one matrix 21 / 12, 256 matrices 104 /
+// 122; update of 4096 x 11008 319 / 387; Gram of 768 x 768, 48 matrices 54 / 39.
+bool small_tiles(const GemmArgs& ga, int nmat) {
+  const int64_t m1 = ga.tiles_m, n1 = ga.tiles_n, m2 = (m1 + 1) / 2, n2 = (n1 + 1) / 2;
+  const double t1 = double(nmat) * double(ga.syrk ? m1 * (m1 + 1) / 2 : m1 * n1);
+  const double t2 = double(nmat) * double(ga.syrk ? m2 * (m2 + 1) / 2 : m2 * n2);
+  const double cus = device_cu_count(), nk = ga.k_slabs;
+  const double rounds2 = std::ceil(t2 / cus), f = t2 / (rounds2 * cus);
+  const double r1 = t1 / (2.0 * cus), rounds1 = std::ceil(r1);
+  const double cost2 = rounds2 * ((1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f);
+  const double cost1 = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
+  return cost1 < cost2;
 }
 
 // The products on the 128 x 128 kernel: fp32 Newton-Schulz, and bf16 rows
@@ -2317,7 +2374,9 @@ hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBu
   const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
   const int nmat = cg.nmat;
   auto launch = [&](int epi, const GemmArgs& ga) {
-    return qtr ? launch_tile<CfgSquare>(epi, ga, nmat, st) : launch_gemm<XT>(epi, ga, nmat, st);
+    if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st);
+    return small_tiles(ga, nmat) ? launch_tile<CfgQuarter>(epi, ga, nmat, st)
+                                 : launch_tile<CfgSquare>(epi, ga, nmat, st);
   };
   int cur = 0;
   for (int k = 0; k < K; ++k) {
