@@ -409,11 +409,6 @@ struct GemmArgs {
   // operand storage, 256 x 256 kernel only: 0 row-major over K; 1 symmetric,
   // upper-triangle 256 x 256 tiles only; 2 (Q) stored K x N
   int32_t p_mode, q_mode;
-  // 256 x 256 kernel, polynomial product: the A term is added to the
-  // accumulators in the main loop (weight alpha = b/c, output beta * acc)
-  // instead of being read again in the epilogue.  The update products
-  // always add their a*X term that way on this kernel.
-  int32_t e_loop;
   // First Newton-Schulz step: X holds X~ = u unscaled, and the product is
   // scaled per matrix by xscale (the Gram product by its square); null after.
   const float* xscale;
@@ -668,23 +663,6 @@ __device__ __forceinline__ void quad_transpose(float x[4]) {
   for (int k = 0; k < 4; ++k) y[k] = __uint_as_float(quad_swap<kQuadXor2>(__float_as_uint(n[k])));
 #pragma unroll
   for (int r = 0; r < 4; ++r) x[r] = ((r ^ t) & 2) ? y[r ^ 2] : n[r];
-}
-
-// The same 4 x 4 transpose on packed bfloat16: d.x = M[t][0] | M[t][1] << 16,
-// d.y = M[t][2] | M[t][3] << 16 becomes d.x = M[0][t] | M[1][t] << 16,
-// d.y = M[2][t] | M[3][t] << 16.  Stage 1 swaps the off-diagonal 2 x 2
-// blocks (whole dwords, lanes t ^ 2); stage 2 transposes inside each block
-// (16-bit halves, lanes t ^ 1) with byte permutes.  8 VALU operations.
-__device__ __forceinline__ uint2 quad_transpose_bf16(uint2 d) {
-  const int t = threadIdx.x & 3;
-  const bool hi_pair = (t & 2) != 0, odd = (t & 1) != 0;
-  const uint32_t r1 = quad_swap<kQuadXor2>(hi_pair ? d.x : d.y);
-  const uint32_t x1 = hi_pair ? r1 : d.x, y1 = hi_pair ? d.y : r1;
-  // v_perm_b32(s0, s1, sel): selector bytes 0-3 pick bytes of s1, 4-7 of s0
-  const uint32_t send = __builtin_amdgcn_perm(y1, x1, odd ? 0x05040100u : 0x07060302u);
-  const uint32_t r2 = quad_swap<kQuadXor1>(send);
-  return uint2{__builtin_amdgcn_perm(r2, x1, odd ? 0x03020504u : 0x05040100u),
-               __builtin_amdgcn_perm(r2, y1, odd ? 0x03020706u : 0x07060100u)};
 }
 
 #ifndef MUON_NT
@@ -1012,14 +990,14 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // addresses row 4(G/2) + e, columns 16(G%2) + 4q .. +3 of the block's
   // register group, and lane t receives column 16(G%2) + t, rows 0..3.
   // The polynomial adds alpha = b/c times A and scales by beta = c at the
-  // end; with c = 0 the launch keeps the epilogue path (e_loop = 0).
+  // end (with c = 0 there is no product: k_scale_upper).
   constexpr bool EUPD = QTR;
   constexpr int EPS = (BN / WN) / 64;           // P slabs holding a wave's columns of A
   static_assert(EPS == 1 || EPS == 2, "A term: one or two slabs per wave");
   constexpr int EJ = BJ / EPS;                  // 32-column blocks per such slab
   constexpr int ERS = (BM / WM) / 64;           // Q slabs holding a wave's rows of X
   static_assert(ERS * 2 == BI, "X term: whole slabs per wave");
-  const bool epoly = EPI == EPI_POLY && ga.e_loop != 0;
+  constexpr bool epoly = EPI == EPI_POLY;
   int e_ks0 = -1, e_ks1 = -1;
   if (EUPD) {
     e_ks0 = bm * (BM / 64) + ERS * wm;
@@ -1224,16 +1202,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // layout: lane t = l % 4 holds row row0+t, columns c0..c0+3, and 8 lanes
   // cover 64 contiguous bytes of a row.
   //  - The a*X (or A) term is already in the accumulators (added in the main
-  //    loop), except for a polynomial launched with e_loop = 0, which reads
-  //    it here, through the staging area or coalesced in the direct layout.
+  //    loop).
   //  - Outputs are rounded to bfloat16 once and leave through LDS as whole
   //    512-byte rows.  The symmetric products write upper-triangle tiles only,
   //    and X' needs no transposed copy: the next products read tiles below the
   //    diagonal, and X, through transposing LDS reads.
   //  - The last step's parameter update runs in the parameter's layout:
   //    direct when it is s x l, natural when it is l x s.
-  //  - Every load of the a*X (or A) term is issued before the first store,
-  //    so one memory latency is exposed instead of one per block.
   const bool diag = ga.syrk && bm == bn;
   // The 256 x 256 kernel reads the diagonal 256 x 256 blocks of A and B
   // whole: of such a block, the 128 x 128 kernel also writes the quarter below
@@ -1246,23 +1221,19 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int row_base = bm * BM + wm * (BM / WM) + 4 * fsel;
   const int col_base = bn * BN + wn * (BN / WN) + frow;
   char* const C = ga.C + mat * ga.c_mat;
-  const char* const E = ga.E + mat * ga.e_mat;
   constexpr int TST = BM * 2 + 8;             // staged column, bytes
-  constexpr bool stage_c = !FINAL;
-  const bool e_epi = EPI == EPI_POLY && !epoly;  // the term is read in the epilogue
-  // Natural staging (the output tile, no epilogue input): each lane's 4
-  // consecutive rows of one column go to LDS as they are, 8 bytes at
-  // column-major position (col, row) with a 520-byte column pitch, and the
-  // copy-out reads whole rows back through transposing LDS reads.  No
-  // register transposes; diagonal tiles of the symmetric products take
+  // Natural staging of the output tile: each lane's 4 consecutive rows of one
+  // column go to LDS as they are, 8 bytes at column-major position (col, row)
+  // with a column pitch of TST bytes, and the copy-out reads whole rows back
+  // through transposing LDS reads.  No register transposes; diagonal tiles of the symmetric products take
   // their lower triangle from the mirrored column at copy-out.
-  const bool stage_n = stage_c && !e_epi;
+  constexpr bool stage_n = !FINAL;
   // The factor the accumulators leave with: c for a polynomial that added
   // (b/c) A in the main loop; on the first step, whose X holds u unscaled,
   // r^2 for the Gram product and r for the update products.
   float osc = 1.f;
   if (EPI == EPI_POLY) {
-    osc = epoly ? ga.beta : 1.f;
+    osc = ga.beta;
   } else if (ga.xscale) {
     const float r = ga.xscale[mat];
     osc = EPI == EPI_GRAM ? r * r : r;
@@ -1270,15 +1241,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 
   // Diagonal tiles of the symmetric products are written exactly symmetric:
   // the value computed for (row, col) with row <= col also goes to (col, row),
-  // in the LDS staging area.  The output tile goes through LDS because whole
-  // 512-byte rows measured faster than 64-byte row pieces from the registers;
-  // a polynomial with c = 0 also takes its A tile there, loaded as whole rows
-  // and combined in place.  Staged rows are then 512 bytes; row r holds
-  // 16-byte chunk c at position c ^ 4*(r % 4), so the 8 rows x 64 bytes a lane
-  // instruction touches spread over all banks.
-  auto cpos = [](int r, int b) {  // staged byte position of tile row r, byte b
-    return r * (BN * 2) + ((((b >> 4) ^ ((r & 3) << 2))) << 4) + (b & 15);
-  };
+  // at copy-out.  The output tile goes through LDS because whole 512-byte
+  // rows measured faster than 64-byte row pieces from the registers.
   // The last step with a bfloat16 parameter whose rows take 16-byte accesses:
   // W goes through LDS the same way, loaded and written back as whole
   // 512-byte rows of its own layout.  Its staged row r holds chunk c at
@@ -1315,40 +1279,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
                  lds0 + (wave * KW + k) * 1024);
     }
   }
-  if (e_epi) {
-    // a wave instruction fills TRI staged rows (1 KB); lane l: row
-    // TRI k + l / TRC, position l % TRC, which holds chunk (l % TRC) ^ 4*(row % 4)
-    constexpr int KE = BM * BN * 2 / 1024 / NW;   // load instructions per wave
-    static_assert(KE * NW * 1024 == BM * BN * 2, "E tile: whole instructions per wave");
-    const char* eb = E + static_cast<int64_t>(bm) * BM * ga.lde + bn * BN * 2;
-    const uint32_t lds0 = lds_offset(smem);
-#pragma unroll
-    for (int k = 0; k < KE; ++k) {
-      const int row = TRI * (wave * KE + k) + lane / TRC;
-      const int c = (lane % TRC) ^ ((row & 3) << 2);
-      load_lds16(eb, static_cast<uint32_t>((row < mv ? row : row - 128) * ga.lde + (8 * c < nv ? c : c - 16) * 16),
-                 lds0 + (wave * KE + k) * 1024);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  }
   // (The loads and the per-block work sit in one lambda: inlined that way the
   // compiler keeps every value in registers; written at function scope it
   // spilled.)
   auto blocks = [&]() {
-    uint2 ev[BI][BJ][4];
-    static_for<BI>([&](auto I) {
-      static_for<BJ>([&](auto J) {
-        static_for<4>([&](auto G) {
-          constexpr int i = decltype(I)::value, j = decltype(J)::value, g = decltype(G)::value;
-          const int row0 = row_base + i * 32 + 8 * g;
-          const int c0 = col_base + j * 32 - q4;
-          if (e_epi && diag)  // the mirrored writes below reach other lanes' inputs
-            ev[i][j][g] = *reinterpret_cast<const uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2));
-        });
-      });
-    });
-    if (e_epi && diag) __syncthreads();
     if (stage_w) {  // the W block has landed in LDS
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -1370,33 +1304,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
           const int c0 = col - q4;                     // direct layout: columns c0 .. c0 + 3
           float v[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * g + q] * (e_epi ? 1.f : osc);
+          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * g + q] * osc;
           if (!FINAL || tr) {  // natural layout
-            if (e_epi) {
-              float e[4];
-              const uint2 ed = !diag ? *reinterpret_cast<const uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2))
-                                                  : ev[i][j][g];
-              unpack_bf16x4(quad_transpose_bf16(ed), e);
-#pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] = fmaf(ga.alpha, e[q], ga.beta * v[q]);
-            }
             if (stage_n) {
               *reinterpret_cast<uint2*>(smem + (col - bn * BN) * TST + (row0 - bm * BM) * 2) = pack_bf16x4(v);
-            } else if (!FINAL && diag) {  // (row, col) and (col, row) for row <= col
-              const int cl = col - bn * BN;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const int rl = row0 + q - bm * BM;
-                if (rl <= cl) {
-                  const uint16_t h = f32_to_bf16(v[q]);
-                  *reinterpret_cast<uint16_t*>(smem + cpos(rl, cl * 2)) = h;
-                  *reinterpret_cast<uint16_t*>(smem + cpos(cl, rl * 2)) = h;
-                }
-              }
-            } else if (!FINAL) {
-              const uint2 p = pack_bf16x4(v);
-              const uint2 d = quad_transpose_bf16(p);  // row row0 + q4, columns c0 .. c0 + 3
-              *reinterpret_cast<uint2*>(smem + cpos(row0 + q4 - bm * BM, (c0 - bn * BN) * 2)) = d;
             } else if (stage_w) {      // parameter is l x s: elements (col, row0 .. row0 + 3)
               w_update(smem + wpos(col - wr0, (row0 - wc0) * 2), v);
             } else if (col < ga.l) {
@@ -1482,27 +1393,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       }
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
-  } else if (stage_c) {
-    __syncthreads();
-    // output tile rows (BN bf16 = 512 bytes each) -> C, 16 bytes a thread
-    constexpr int CH = BN * 2 / 16;
-    for (int idx = threadIdx.x; idx < BM * CH; idx += 64 * NW) {
-      const int r = idx / CH, ch = idx - r * CH;
-      if (r >= mv || ch * 8 >= nv) continue;
-      store_out(reinterpret_cast<u32x4_t*>(C + static_cast<int64_t>(bm * BM + r) * ga.ldc + bn * BN * 2 + ch * 16),
-                *reinterpret_cast<const u32x4_t*>(smem + cpos(r, ch * 16)));
-    }
-    if (pair_mirror) {
-      for (int idx = threadIdx.x; idx < BN * BM; idx += 64 * NW) {
-        const int c = idx / BM, r = idx % BM;
-        *reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(bn * BN + c) * ga.ldc + (bm * BM + r) * 2) =
-            *reinterpret_cast<const uint16_t*>(smem + cpos(r, c * 2));
-      }
-    }
-    __syncthreads();  // the next tile's loads overwrite the staging area
   }
 }
-
 
 // Persistent launch: one workgroup per CU slot loops over tiles in rounds.
 // Workgroup b runs on XCD b % 8; in round r the XCD's workgroups take the
@@ -1560,6 +1452,24 @@ void k_gemm_group(GroupArgs gr) {
   }
 }
 
+// B = b A for a step with c = 0 (cubic tables): no product, one pass over the
+// stored (upper-triangle 256 x 256) tiles of A, a 128 x 128 block a workgroup.
+__global__ __launch_bounds__(256) void k_scale_upper(GemmArgs ga, int t) {
+  const int mat = blockIdx.x / (t * t), b = blockIdx.x % (t * t), bm = b / t, bn = b % t;
+  if (bn / 2 < bm / 2) return;
+  const char* E = ga.E + mat * ga.e_mat + static_cast<int64_t>(bm) * 128 * ga.lde + bn * 256;
+  char* C = ga.C + mat * ga.c_mat + static_cast<int64_t>(bm) * 128 * ga.ldc + bn * 256;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = i * 16 + (threadIdx.x >> 4), col = (threadIdx.x & 15) * 8;
+    float v[8];
+    load8(reinterpret_cast<const uint16_t*>(E + static_cast<int64_t>(row) * ga.lde), col, v);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] *= ga.alpha;
+    store8(reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(row) * ga.ldc), col, v);
+  }
+}
+
 // Update from X0 when K = 0: O is X0 in the caller's layout (the direct
 // buffer), one thread per element of the u-domain; grid = (ceil(rows*cols /
 // 256), matrices).
@@ -1606,6 +1516,13 @@ int device_cu_count() {
   return cache[dev];
 }
 
+hipError_t launch_scale_upper(const GemmArgs& ga, int nmat, hipStream_t st) {
+  const int t = ga.m_ext / 128;
+  hipLaunchKernelGGL(k_scale_upper, dim3(static_cast<unsigned>(t * t) * static_cast<unsigned>(nmat)), dim3(256), 0,
+                     st, ga, t);
+  return hipGetLastError();
+}
+
 template <class Cfg>
 hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   // ga arrives in 128 x 128 tiles and 128-byte slabs
@@ -1617,9 +1534,9 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   ga.k_slabs = ga.k_slabs * 128 / Cfg::SLAB;
   ga.total_tiles = ga.tiles_per_mat * nmat;
   // B = b A + c A^2 = c (A^2 + (b/c) A): the A term joins the accumulators
-  // in the main loop unless c = 0
-  if (epi == EPI_POLY && ga.beta != 0.f) {
-    ga.e_loop = 1;
+  // in the main loop
+  if (epi == EPI_POLY) {
+    if (ga.beta == 0.f) return launch_scale_upper(ga, nmat, st);
     ga.alpha = ga.alpha / ga.beta;
   }
   // one workgroup per CU slot (persistent), never more workgroups than tiles
@@ -1650,27 +1567,33 @@ template <class Cfg>
 hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   GroupArgs gr{};
-  gr.n = n;
   gr.start[0] = 0;
-  for (int c = 0; c < n; ++c) {
-    GemmArgs ga = gas[c];
+  for (int i = 0; i < n; ++i) {
+    GemmArgs ga = gas[i];
+    const int c = gr.n;
     ga.m_ext = ga.tiles_m * kTile;
     ga.n_ext = ga.tiles_n * kTile;
     ga.tiles_m = (ga.m_ext + Cfg::BM - 1) / Cfg::BM;
     ga.tiles_n = (ga.n_ext + Cfg::BN - 1) / Cfg::BN;
     ga.tiles_per_mat = ga.syrk ? ga.tiles_m * (ga.tiles_m + 1) / 2 : ga.tiles_m * ga.tiles_n;
     ga.k_slabs = ga.k_slabs * 128 / Cfg::SLAB;
-    ga.total_tiles = ga.tiles_per_mat * nmats[c];
-    if (epi == EPI_POLY && ga.beta != 0.f) {
-      ga.e_loop = 1;
+    ga.total_tiles = ga.tiles_per_mat * nmats[i];
+    if (epi == EPI_POLY) {
+      if (ga.beta == 0.f) {
+        const hipError_t e = launch_scale_upper(ga, nmats[i], st);
+        if (e != hipSuccess) return e;
+        continue;
+      }
       ga.alpha = ga.alpha / ga.beta;
     }
     if (c > 0 && (ga.final_kind != gr.ga[0].final_kind || ga.param_dtype != gr.ga[0].param_dtype))
       return hipErrorInvalidValue;
     gr.ga[c] = ga;
     gr.start[c + 1] = gr.start[c] + ga.total_tiles;
+    gr.n = c + 1;
   }
-  const int total = gr.start[n];
+  const int total = gr.start[gr.n];
+  if (total == 0) return hipSuccess;
   const int slots = device_cu_count() * (160 * 1024 / Cfg::LDS);
   const dim3 grid(static_cast<unsigned>(min(total, slots))), block(64 * Cfg::NW);
   switch (epi) {
