@@ -84,7 +84,9 @@ typedef enum { MUON_F32 = 0, MUON_BF16 = 1 } muon_dtype_t;
 
 /* Arithmetic of the Newton-Schulz products: bf16 operands with fp32
  * accumulation (intermediates X, A = X X^T, B = bA + cA^2 stored as bf16),
- * or fp32 throughout.  Momentum, norm and update are fp32 in both. */
+ * or fp32 (intermediates held to 24 bits, fp32 accumulation; beyond short
+ * sides of 128 each product runs as bf16 matrix products of exact three-way
+ * splits).  Momentum, norm and update are fp32 in both. */
 typedef enum { MUON_NS_BF16 = 0, MUON_NS_F32 = 1 } muon_ns_precision_t;
 
 /* One parameter entry: `batch` matrices of rows x cols (Sec. 6.3: a stacked

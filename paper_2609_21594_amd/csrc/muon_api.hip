@@ -582,6 +582,12 @@ void layout_chunk(Chunk& c, bool ns_f32, int K) {
   }
   c.off_A = off; off += ab;
   c.off_B = off; off += ab;
+  if (ns_f32 && !small && muon::chunk_on_tiles(c.S, c.L, K)) {
+    // X, X', A and B in three bf16 planes each, over the same bytes
+    const size_t x3 = xb / 4 * 6, a3 = ab / 4 * 6;  // (extents are multiples of 128)
+    c.off_X[0] = 0; c.off_X[1] = x3;
+    c.off_A = 2 * x3; c.off_B = 2 * x3 + a3;
+  }
   c.off_part = off; off += pb;
   c.off_r = off; off += align256(size_t(c.count) * 12);  // rscale (fp64), then xscale (fp32)
   c.off_sync = off; off += small ? size_t(muon::kSmallSyncBytes) : 0;
@@ -903,7 +909,7 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
   };
   auto steps_of = [&](const Chunk& c) { return int(tables[size_t(c.cset)].size() / 3); };
   auto idle_of = [&](const Chunk& c) {
-    const bool tile = muon::chunk_on_tiles(c.S, c.L, ns_f32, steps_of(c));
+    const bool tile = muon::chunk_on_tiles(c.S, c.L, steps_of(c));
     const int64_t t = tile ? (c.S + 255) / 256 : c.S / 128;
     const int64_t tiles = t * (t + 1) / 2 * c.count, slots = int64_t(tile ? cus : 2 * cus);
     return double(tiles) / double(((tiles + slots - 1) / slots) * slots) < 0.9;

@@ -109,22 +109,23 @@ constexpr int64_t kTileMaxRowBytes = (int64_t(1) << 31) / 256;
 inline bool tile_rows_fit(int64_t S, int64_t L, int es) {
   return S * es < kTileMaxRowBytes && L * es < kTileMaxRowBytes;
 }
-// A chunk's products run on the 256 x 256 kernel: bf16 Newton-Schulz, at
-// least one step, rows within that kernel's offsets.  S and L are multiples
-// of 128; a last tile of 128 rows or columns is computed whole and written by
-// half.  (48 matrices of 1408 x 2048 on an MI355X: 9.57 ms per step on the
-// 128 x 128 kernel, which stages through registers, 4.23 ms on this one; 96
-// of 128 x 4096: 1.83 and 0.92 ms.)
-inline bool chunk_on_tiles(int64_t S, int64_t L, bool ns_f32, int K) {
-  return !ns_f32 && K > 0 && tile_rows_fit(S, L, 2);
-}
-// A chunk reserves X^T (two more X-sized workspace buffers) unless S and L
-// are multiples of 256 and the products run on the 256 x 256 kernel, which
-// reads X itself through transposing LDS reads.  (With odd multiples of 128
-// the buffers are reserved and not used: what a call needs of a limited
-// workspace is part of the interface.)
+// A chunk's products run on the tile kernel: at least one step, rows within
+// that kernel's offsets.  S and L are multiples of 128; a last 256 x 256 tile
+// of 128 rows or columns is computed whole and written by half.  (48 matrices
+// of 1408 x 2048 on an MI355X: 9.57 ms per step on the 128 x 128 kernel, which
+// stages through registers, 4.23 ms on this one; 96 of 128 x 4096: 1.83 and
+// 0.92 ms.)  fp32 Newton-Schulz runs there on values split into three
+// bfloat16 planes (Split3).
+inline bool chunk_on_tiles(int64_t S, int64_t L, int K) { return K > 0 && tile_rows_fit(S, L, 2); }
+// A chunk reserves X^T (two more X-sized workspace buffers) unless it is bf16
+// with S and L multiples of 256 on the tile kernel, which reads X itself
+// through transposing LDS reads.  Other chunks on the tile kernel keep the
+// reservation, since what a call needs of a limited workspace is part of the
+// interface: with fp32 Newton-Schulz it holds the third planes of X, A and B
+// (12 S (L + S) bytes of 16 S L + 8 S S, as L >= S); with odd multiples of 128
+// it is not used.
 inline bool chunk_keeps_xt(int64_t S, int64_t L, bool ns_f32, int K) {
-  return !chunk_on_tiles(S, L, ns_f32, K) || S % 256 != 0 || L % 256 != 0;
+  return ns_f32 || !chunk_on_tiles(S, L, K) || S % 256 != 0 || L % 256 != 0;
 }
 // A chunk runs as one fused launch (k_ns_small: momentum, norm, every
 // Newton-Schulz step and the update) when its short side is at most 128 and

@@ -102,6 +102,38 @@ __device__ __forceinline__ void store8(T* base, int64_t i, const float in[8]) {
   }
 }
 
+// An fp32 value kept as three bfloat16 planes, x = h + m + l: h is x rounded,
+// m the rest rounded, l what then remains (at most 8 bits of x's 24, so the
+// sum is exact unless l falls below bfloat16's range).  The fp32
+// Newton-Schulz products on the tile kernel take their operands in this form.
+struct Split3 {};
+// How an iterate is stored: element type, planes, and the type its tiles take
+// in the prologue's LDS transpose.
+template <typename XT> struct Store { using E = XT; using L = XT; static constexpr int planes = 1; };
+template <> struct Store<Split3> { using E = uint16_t; using L = float; static constexpr int planes = 3; };
+
+template <typename XT>
+__device__ __forceinline__ void store8x(typename Store<XT>::E* base, int64_t i, int64_t plane, const float in[8]) {
+  if constexpr (std::is_same<XT, Split3>::value) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = in[q];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      u32x4_t raw;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        raw[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
+        v[2 * q] -= __uint_as_float(raw[q] << 16);
+        v[2 * q + 1] -= __uint_as_float(raw[q] & 0xffff0000u);
+      }
+      *reinterpret_cast<u32x4_t*>(base + p * plane + i) = raw;
+    }
+  } else {
+    store8(base, i, in);
+  }
+}
+
 // Fixed-order sum over a 256-thread block: butterfly within each 64-lane
 // wavefront, then the four wave sums in wave order.  Deterministic.  In fp64:
 // the sums of u^2 stay finite for every finite u (|u| < 2^128 and at most
@@ -157,11 +189,13 @@ struct TileStage {
 // u, its two destinations and their row strides.
 template <typename XT>
 struct TileDst {
+  using E = typename Store<XT>::E;
   int ur0, uc0;
-  XT* D;       // u's own layout (X when u is s x l, X^T when l x s), or null
+  E* D;        // u's own layout (X when u is s x l, X^T when l x s), or null
   int ldD;
-  XT* Tb;      // the transpose, through LDS, or null
+  E* Tb;       // the transpose, through LDS, or null
   int ldT;
+  int64_t plane;  // elements from one plane of X to the next
 };
 
 // Tile tt (row-major over the (S/64) x (L/64) grid) of matrix m.  A matrix
@@ -170,28 +204,29 @@ struct TileDst {
 // write more contiguously; `wide` says which.
 template <typename XT>
 __device__ __forceinline__ TileDst<XT> tile_dst(const MatDesc& md, const ChunkGeom& cg, int m, int i0, int j0,
-                                                XT* X, XT* XTb);
+                                                typename Store<XT>::E* X, typename Store<XT>::E* XTb);
 
 template <typename XT>
-__device__ __forceinline__ TileDst<XT> tile_of(const MatDesc& md, const ChunkGeom& cg, int m, int tt, XT* X,
-                                               XT* XTb, bool& wide) {
+__device__ __forceinline__ TileDst<XT> tile_of(const MatDesc& md, const ChunkGeom& cg, int m, int tt,
+                                               typename Store<XT>::E* X, typename Store<XT>::E* XTb, bool& wide) {
   wide = md.transposed == 0 && XTb == nullptr;
   if (wide) {
     const int tx = cg.L / 128;
-    return tile_dst(md, cg, m, (tt / tx) * 32, (tt % tx) * 128, X, XTb);
+    return tile_dst<XT>(md, cg, m, (tt / tx) * 32, (tt % tx) * 128, X, XTb);
   }
   const int tx = cg.L / 64;
-  return tile_dst(md, cg, m, (tt / tx) * 64, (tt % tx) * 64, X, XTb);
+  return tile_dst<XT>(md, cg, m, (tt / tx) * 64, (tt % tx) * 64, X, XTb);
 }
 
 template <typename XT>
 __device__ __forceinline__ TileDst<XT> tile_dst(const MatDesc& md, const ChunkGeom& cg, int m, int i0, int j0,
-                                                XT* X, XT* XTb) {
+                                                typename Store<XT>::E* X, typename Store<XT>::E* XTb) {
   const bool tr = md.transposed != 0;
-  const int64_t matX = static_cast<int64_t>(cg.S) * cg.L;
-  XT* Xm = X + m * matX;
-  XT* XTm = XTb ? XTb + m * matX : nullptr;
+  const int64_t plane = static_cast<int64_t>(cg.S) * cg.L, matX = plane * Store<XT>::planes;
+  auto* Xm = X + m * matX;
+  auto* XTm = XTb ? XTb + m * matX : nullptr;
   TileDst<XT> t;
+  t.plane = plane;
   t.ur0 = tr ? j0 : i0;
   t.uc0 = tr ? i0 : j0;
   t.D = tr ? XTm : Xm;
@@ -203,16 +238,17 @@ __device__ __forceinline__ TileDst<XT> tile_dst(const MatDesc& md, const ChunkGe
 
 // Phase 2 of a tile: rows of the transpose out of LDS, 16 bytes a thread.
 template <typename XT>
-__device__ __forceinline__ void write_transposed(const XT* tile, const TileDst<XT>& t) {
-  constexpr int LDT = TileStage<XT>::LDT;
+__device__ __forceinline__ void write_transposed(const typename Store<XT>::L* tile, const TileDst<XT>& t) {
+  using L = typename Store<XT>::L;
+  constexpr int LDT = TileStage<L>::LDT;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int c = threadIdx.x + 256 * k;          // row c / 8 of the transpose, 8 (c % 8) ..
     const int trow = c >> 3, r8 = (c & 7) * 8;
     float v[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = to_f32<XT>(tile[(r8 + q) * LDT + trow]);
-    store8(t.Tb, static_cast<int64_t>(t.uc0 + trow) * t.ldT + t.ur0 + r8, v);
+    for (int q = 0; q < 8; ++q) v[q] = to_f32<L>(tile[(r8 + q) * LDT + trow]);
+    store8x<XT>(t.Tb, static_cast<int64_t>(t.uc0 + trow) * t.ldT + t.ur0 + r8, t.plane, v);
   }
 }
 
@@ -221,8 +257,9 @@ __device__ __forceinline__ void write_transposed(const XT* tile, const TileDst<X
 // thread's sum of u^2 (fp64).  out = (u * s1) * s2.
 template <typename GT, typename XT, bool MOM, bool UPDATE_MOM, bool WIDE>
 __device__ __forceinline__ double prologue_tile(const MatDesc& md, const StepScalars& sc, const TileDst<XT>& t,
-                                                float s1, float s2, XT* tile) {
-  constexpr int LDT = TileStage<XT>::LDT;
+                                                float s1, float s2, typename Store<XT>::L* tile) {
+  using L = typename Store<XT>::L;
+  constexpr int LDT = TileStage<L>::LDT;
   constexpr int CPR = WIDE ? 16 : 8;              // 8-element chunks per tile row
   const GT* __restrict__ g = static_cast<const GT*>(md.g);
   const float beta = sc.beta, omb = sc.one_minus_beta;
@@ -277,10 +314,10 @@ __device__ __forceinline__ double prologue_tile(const MatDesc& md, const StepSca
         }
       }
     }
-    if (t.D) store8(t.D, static_cast<int64_t>(ur) * t.ldD + uc, v);
+    if (t.D) store8x<XT>(t.D, static_cast<int64_t>(ur) * t.ldD + uc, t.plane, v);
     if (!WIDE && t.Tb) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) tile[row * LDT + col + q] = from_f32<XT>(v[q]);
+      for (int q = 0; q < 8; ++q) tile[row * LDT + col + q] = from_f32<L>(v[q]);
     }
   }
   return acc;
@@ -288,14 +325,15 @@ __device__ __forceinline__ double prologue_tile(const MatDesc& md, const StepSca
 
 template <typename GT, typename XT, bool MOM>
 __global__ __launch_bounds__(256) void k_prologue(const MatDesc* __restrict__ desc, StepScalars sc, ChunkGeom cg,
-                                                  XT* __restrict__ X, XT* __restrict__ XTb,
+                                                  typename Store<XT>::E* __restrict__ X,
+                                                  typename Store<XT>::E* __restrict__ XTb,
                                                   double* __restrict__ partials) {
-  __shared__ XT tile[64 * TileStage<XT>::LDT];
+  __shared__ typename Store<XT>::L tile[64 * TileStage<typename Store<XT>::L>::LDT];
   __shared__ double red4[4];
   const int m = blockIdx.z;
   const MatDesc md = desc[m];
   bool wide;
-  const TileDst<XT> t = tile_of(md, cg, m, blockIdx.y * gridDim.x + blockIdx.x, X, XTb, wide);
+  const TileDst<XT> t = tile_of<XT>(md, cg, m, blockIdx.y * gridDim.x + blockIdx.x, X, XTb, wide);
   const double acc = wide ? prologue_tile<GT, XT, MOM, true, true>(md, sc, t, 1.f, 1.f, tile)
                           : prologue_tile<GT, XT, MOM, true, false>(md, sc, t, 1.f, 1.f, tile);
   const double s = block_sum_256(acc, red4);  // (its barrier also publishes the LDS tile)
@@ -303,7 +341,7 @@ __global__ __launch_bounds__(256) void k_prologue(const MatDesc* __restrict__ de
     partials[static_cast<int64_t>(m) * (gridDim.x * gridDim.y) + blockIdx.y * gridDim.x + blockIdx.x] = s;
   if (!t.Tb) return;  // uniform over the block
   __syncthreads();
-  write_transposed(tile, t);
+  write_transposed<XT>(tile, t);
 }
 
 // r = 1 / (sqrt(sum of partials) + eps), one workgroup per matrix, in fp64,
@@ -348,8 +386,9 @@ __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ pa
 template <typename GT, typename XT, bool MOM>
 __global__ __launch_bounds__(256) void k_rescale(const MatDesc* __restrict__ desc, const double* __restrict__ rscale,
                                                  const float* __restrict__ xscale, StepScalars sc, ChunkGeom cg,
-                                                 XT* __restrict__ X, XT* __restrict__ XTb) {
-  __shared__ XT tile[64 * TileStage<XT>::LDT];
+                                                 typename Store<XT>::E* __restrict__ X,
+                                                 typename Store<XT>::E* __restrict__ XTb) {
+  __shared__ typename Store<XT>::L tile[64 * TileStage<typename Store<XT>::L>::LDT];
   const int m = blockIdx.y;
   const double r = rscale[m];
   if (xscale[m] != 1.0f || r == 1.0) return;  // uniform over the block
@@ -359,12 +398,12 @@ __global__ __launch_bounds__(256) void k_rescale(const MatDesc* __restrict__ des
   const int ntiles = (cg.L / 64) * (cg.S / 64);
   for (int tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
     bool wide;
-    const TileDst<XT> t = tile_of(md, cg, m, tt, X, XTb, wide);
+    const TileDst<XT> t = tile_of<XT>(md, cg, m, tt, X, XTb, wide);
     if (wide) (void)prologue_tile<GT, XT, MOM, false, true>(md, sc, t, s1, s2, tile);
     else (void)prologue_tile<GT, XT, MOM, false, false>(md, sc, t, s1, s2, tile);
     if (t.Tb) {  // uniform over the block
       __syncthreads();
-      write_transposed(tile, t);
+      write_transposed<XT>(tile, t);
       __syncthreads();  // the next tile overwrites the LDS tile
     }
   }
@@ -409,6 +448,8 @@ struct GemmArgs {
   // operand storage, 256 x 256 kernel only: 0 row-major over K; 1 symmetric,
   // upper-triangle 256 x 256 tiles only; 2 (Q) stored K x N
   int32_t p_mode, q_mode;
+  // SPLIT kernels: bytes from one plane of the operand or output to the next
+  int64_t p_plane, q_plane, c_plane;
   // First Newton-Schulz step: X holds X~ = u unscaled, and the product is
   // scaled per matrix by xscale (the Gram product by its square); null after.
   const float* xscale;
@@ -834,7 +875,20 @@ __device__ __forceinline__ void tile_from_logical(const GemmArgs& ga, int logica
   }
 }
 
-template <int EPI, class Cfg>
+// SPLIT: the operands and outputs are fp32 values in three bfloat16 planes
+// (Split3), and each product of values is the six bfloat16 products whose
+// weight is above 2^-24.  A first pass over k adds the five small ones, per
+// slab of 64 k in the order
+//   (P, Q) = (h, l) (h, m) (m, m) (m, h) (l, h),
+// in which one operand changes at a time (six operand slabs loaded for five
+// slabs of MFMA work); a second pass adds (h, h).  The sums are thus rounded
+// at their full size once per 16 k, where one pass over all six pairs would
+// round them six times (and the fp32 instruction eight times).  The MFMA rate
+// for bf16 is 16 times that for fp32, so the six cost 0.375 of the fp32
+// instruction; what the pairs (m, l), (l, m), (l, l) would add is below the
+// rounding of the fp32 accumulation.  Error of an orthogonalised matrix
+// against 64 bits: see tests/test_split_error_gpu.py.
+template <int EPI, class Cfg, bool SPLIT>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, int mat, int bm, int bn) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, WM = Cfg::WM, WN = Cfg::WN, NW = Cfg::NW;
   constexpr int SLAB = Cfg::SLAB, NS = Cfg::NS;
@@ -916,33 +970,33 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const uint32_t lds0 = lds_offset(smem);
   // The loads of slab ks, one operand at a time: P's NLP instructions or Q's
   // NLQ, into the slab's stage.
-  auto issue_op = [&](auto qc, int ks) __attribute__((always_inline)) {
-    const uint32_t base = lds0 + (ks & 1) * STAGE;
+  auto issue_op = [&](auto qc, int ks, int at, int64_t plane = 0) __attribute__((always_inline)) {
+    const uint32_t base = lds0 + at;   // the stage's byte offset
     if constexpr (!decltype(qc)::value) {
       if (CAN_PT && ks < p_tr_end) {
-        const char* b = Pt + static_cast<int64_t>(ks) * 64 * ga.ldp;
+        const char* b = Pt + plane + static_cast<int64_t>(ks) * 64 * ga.ldp;
 #pragma unroll
         for (int i = 0; i < NLP; ++i) load_lds16(b, pto[i], base + (wave * PR + RPI * i) * SLAB);
       } else {
-        const char* b = Pd + ks * SLAB;
+        const char* b = Pd + plane + ks * SLAB;
 #pragma unroll
         for (int i = 0; i < NLP; ++i) load_lds16(b, pdo[i], base + (wave * PR + RPI * i) * SLAB);
       }
     } else {
       if (CAN_QT && (!CAN_QD || ks < q_tr_end)) {
-        const char* b = Qt + static_cast<int64_t>(ks) * 64 * ga.ldq;
+        const char* b = Qt + plane + static_cast<int64_t>(ks) * 64 * ga.ldq;
 #pragma unroll
         for (int i = 0; i < NLQ; ++i) load_lds16(b, qto[i], base + OPQ + (wave * QR + RPI * i) * SLAB);
       } else {
-        const char* b = Qd + ks * SLAB;
+        const char* b = Qd + plane + ks * SLAB;
 #pragma unroll
         for (int i = 0; i < NLQ; ++i) load_lds16(b, qdo[i], base + OPQ + (wave * QR + RPI * i) * SLAB);
       }
     }
   };
   auto issue = [&](int ks) __attribute__((always_inline)) {
-    issue_op(std::false_type{}, ks);
-    issue_op(std::true_type{}, ks);
+    issue_op(std::false_type{}, ks, (ks & 1) * STAGE);
+    issue_op(std::true_type{}, ks, (ks & 1) * STAGE);
   };
 
   f32x16_t acc[BI][BJ];
@@ -991,6 +1045,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // register group, and lane t receives column 16(G%2) + t, rows 0..3.
   // The polynomial adds alpha = b/c times A and scales by beta = c at the
   // end (with c = 0 there is no product: k_scale_upper).
+  // SPLIT adds the term after the last slab instead, plane by plane from
+  // slabs loaded again: an fp32 sum that starts from its largest term rounds
+  // every later product to that term's last bit (measured: up to 8 times the
+  // error where a*X dominates), and b/c would be a rounded coefficient.
   constexpr bool EUPD = QTR;
   constexpr int EPS = (BN / WN) / 64;           // P slabs holding a wave's columns of A
   static_assert(EPS == 1 || EPS == 2, "A term: one or two slabs per wave");
@@ -1023,6 +1081,16 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
                       8 * (L & 1);
       }
   }
+  // The factor the accumulators leave with: c for a polynomial; on the first step, whose X holds u unscaled,
+  // r^2 for the Gram product and r for the update products.
+  float osc = 1.f;
+  if (EPI == EPI_POLY) {
+    osc = ga.beta;
+  } else if (ga.xscale) {
+    const float r = ga.xscale[mat];
+    osc = EPI == EPI_GRAM ? r * r : r;
+  }
+  const float alpha = SPLIT && EUPD ? ga.alpha * osc : ga.alpha;
   // Rows [i0, i0 + ni) and 32-column blocks [j0, j0 + nj) of the wave's
   // accumulators take the term from the slab at sp.
   auto add_e = [&](const char* sp, auto i0c, auto nic, auto j0c, auto njc) __attribute__((always_inline)) {
@@ -1044,10 +1112,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
           float e[4];
           unpack_bf16x4(ev[jj][g], e);
           f32x16_t& c = acc[i][j];
-          c[4 * g + 0] = fmaf(ga.alpha, e[0], c[4 * g + 0]);
-          c[4 * g + 1] = fmaf(ga.alpha, e[1], c[4 * g + 1]);
-          c[4 * g + 2] = fmaf(ga.alpha, e[2], c[4 * g + 2]);
-          c[4 * g + 3] = fmaf(ga.alpha, e[3], c[4 * g + 3]);
+          c[4 * g + 0] = fmaf(alpha, e[0], c[4 * g + 0]);
+          c[4 * g + 1] = fmaf(alpha, e[1], c[4 * g + 1]);
+          c[4 * g + 2] = fmaf(alpha, e[2], c[4 * g + 2]);
+          c[4 * g + 3] = fmaf(alpha, e[3], c[4 * g + 3]);
         });
       });
     });
@@ -1057,28 +1125,28 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // register set while group g's MFMAs issue, one LDS read between
   // consecutive MFMAs; the slab barrier sits before the last group's MFMAs.
   u32x4_t fa[2][BI], fb[2][BJ];
-  auto rd = [&](auto ptc, auto qtc, const char* sp, auto grpc, auto setc) __attribute__((always_inline)) {
+  auto rd = [&](auto ptc, auto qtc, const char* sP, const char* sQ, auto grpc, auto setc) __attribute__((always_inline)) {
     constexpr bool PT = decltype(ptc)::value, QT = decltype(qtc)::value;
     constexpr int grp = decltype(grpc)::value, set = decltype(setc)::value;
     const int pos = ((2 * grp + fsel) ^ fsw) * 16;
 #pragma unroll
     for (int i = 0; i < BI; ++i) {
       if (PT) {
-        const char* q = sp + tpo[i] + grp * 16 * TRB;
+        const char* q = sP + tpo[i] + grp * 16 * TRB;
         const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * TRB);
         fa[set][i] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
       } else {
-        fa[set][i] = *reinterpret_cast<const u32x4_t*>(sp + a_off + i * 32 * SLAB + pos);
+        fa[set][i] = *reinterpret_cast<const u32x4_t*>(sP + a_off + i * 32 * SLAB + pos);
       }
     }
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
       if (QT) {
-        const char* q = sp + tqo[j] + grp * 16 * TRB;
+        const char* q = sQ + tqo[j] + grp * 16 * TRB;
         const uint2 lo = tr_read_b64(q), hi = tr_read_b64(q + 4 * TRB);
         fb[set][j] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
       } else {
-        fb[set][j] = *reinterpret_cast<const u32x4_t*>(sp + b_off + j * 32 * SLAB + pos);
+        fb[set][j] = *reinterpret_cast<const u32x4_t*>(sQ + b_off + j * 32 * SLAB + pos);
       }
     }
   };
@@ -1113,45 +1181,98 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // Splitting the burst by operand measured 2-3% faster on the step than
   // issuing a slab at once; splitting each operand in halves, or P later,
   // measured slower.
-  constexpr bool EARLY = EPI == EPI_GRAM;
+  constexpr bool EARLY = EPI == EPI_GRAM && !SPLIT;
+  // The a*X (or A) term of slab ks, if it holds some of this wave's.
+  auto take_e = [&](const char* sp, int ks) __attribute__((always_inline)) {
+    if (ks == e_ks0 || ks == e_ks1) {  // wave-uniform; at most twice a tile
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (EUPD && ERS == 1) {
+        add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
+      } else if constexpr (EUPD) {
+        // (the comments keep the compiler from merging the two calls into one
+        // with a run-time row block, which would put the accumulators in memory)
+        if (ks == e_ks0) {
+          add_e(sp, I_<0>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
+          asm volatile("; row blocks 0, 1");
+        } else {
+          add_e(sp, I_<2>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
+          asm volatile("; row blocks 2, 3");
+        }
+      } else if constexpr (EPS == 1) {
+        add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
+      } else {
+        if (ks == e_ks0) add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<EJ>{});
+        else add_e(sp, I_<0>{}, I_<BI>{}, I_<EJ>{}, I_<EJ>{});
+      }
+    }
+  };
   auto slab = [&](auto ptc, auto qtc, auto nextc, auto ec, int ks) __attribute__((always_inline)) {
     const char* sp = smem + (ks & 1) * STAGE;
     if (ks + 1 < nk) {
-      if (!EARLY) issue_op(std::true_type{}, ks + 1);
-      else if (ks >= 1) issue_op(std::false_type{}, ks + 1);  // slab 1 went out whole with slab 0
+      if (!EARLY) issue_op(std::true_type{}, ks + 1, ((ks + 1) & 1) * STAGE);
+      else if (ks >= 1) issue_op(std::false_type{}, ks + 1, ((ks + 1) & 1) * STAGE);  // slab 1 went out whole with slab 0
     }
-    if constexpr (decltype(ec)::value) {
-      if (ks == e_ks0 || ks == e_ks1) {  // wave-uniform; at most twice a tile
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (EUPD && ERS == 1) {
-          add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
-        } else if constexpr (EUPD) {
-          if (ks == e_ks0) add_e(sp, I_<0>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
-          else add_e(sp, I_<2>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
-        } else if constexpr (EPS == 1) {
-          add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
-        } else {
-          if (ks == e_ks0) add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<EJ>{});
-          else add_e(sp, I_<0>{}, I_<BI>{}, I_<EJ>{}, I_<EJ>{});
-        }
-      }
-    }
+    if constexpr (decltype(ec)::value) take_e(sp, ks);
     __builtin_amdgcn_sched_barrier(0);
-    rd(ptc, qtc, sp, I_<1>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
+    rd(ptc, qtc, sp, sp, I_<1>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
-    if (!EARLY && ks + 1 < nk) issue_op(std::false_type{}, ks + 1);
+    if (!EARLY && ks + 1 < nk) issue_op(std::false_type{}, ks + 1, ((ks + 1) & 1) * STAGE);
     __builtin_amdgcn_sched_barrier(0);
-    rd(ptc, qtc, sp, I_<2>{}, I_<0>{}); mm(I_<1>{}); interleave(ptc, qtc);
+    rd(ptc, qtc, sp, sp, I_<2>{}, I_<0>{}); mm(I_<1>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
-    rd(ptc, qtc, sp, I_<3>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
+    rd(ptc, qtc, sp, sp, I_<3>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // slab ks + 1 has landed
     __syncthreads();
     // every wave is done with slab ks: its stage can take slab ks + 2
-    if (EARLY && ks + 2 < nk) issue_op(std::true_type{}, ks + 2);
+    if (EARLY && ks + 2 < nk) issue_op(std::true_type{}, ks + 2, (ks & 1) * STAGE);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (decltype(nextc)::value) {
-      rd(ptc, qtc, smem + ((ks + 1) & 1) * STAGE, I_<0>{}, I_<0>{});
+      const char* sn = smem + ((ks + 1) & 1) * STAGE;
+      rd(ptc, qtc, sn, sn, I_<0>{}, I_<0>{});
+      mm(I_<1>{}); interleave(ptc, qtc);
+    } else {
+      mm(I_<1>{});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // SPLIT: one slab of one plane pair, (pass, slab, phase) = (pass, sks, ph),
+  // P in buffer pb and Q in qb.  An operand that changes for the next step is
+  // loaded during this one into its other buffer, whose last reader ended at
+  // least a step ago.  The step is a run-time value: unrolled, the phases'
+  // addresses are hoisted out of the loop and spill.
+  int pass = 0, sks = 0, ph = 0, pb = 0, qb = 0;
+  auto step = [&](auto ptc, auto qtc, auto nextc) __attribute__((always_inline)) {
+    int npass = pass, nks = sks, nph = ph + 1;
+    if (pass == 1 || ph == 4) {
+      nph = 0;
+      nks = sks + 1;
+      if (pass == 0 && nks == nk) { npass = 1; nks = 0; }
+    }
+    const bool more = nks < nk, both = nph == 0, newq = both || (nph & 1) != 0, newp = both || (nph & 1) == 0;
+    const int npb = pb ^ (newp ? 1 : 0), nqb = qb ^ (newq ? 1 : 0);
+    const int pplane = nph >> 1, qplane = npass == 1 ? 0 : (nph == 0 ? 2 : (nph == 1 ? 1 : 0));
+    const char* sP = smem + pb * STAGE;
+    const char* sQ = smem + qb * STAGE;
+    if (more) {
+      if (newq) issue_op(std::true_type{}, nks, nqb * STAGE, qplane * ga.q_plane);
+      else issue_op(std::false_type{}, nks, npb * STAGE, pplane * ga.p_plane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    rd(ptc, qtc, sP, sQ, I_<1>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
+    __builtin_amdgcn_sched_barrier(0);
+    if (more && both) issue_op(std::false_type{}, nks, npb * STAGE, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    rd(ptc, qtc, sP, sQ, I_<2>{}, I_<0>{}); mm(I_<1>{}); interleave(ptc, qtc);
+    __builtin_amdgcn_sched_barrier(0);
+    rd(ptc, qtc, sP, sQ, I_<3>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next step's operands have landed
+    __syncthreads();
+    pass = npass; sks = nks; ph = nph; pb = npb; qb = nqb;
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (decltype(nextc)::value) {
+      rd(ptc, qtc, smem + pb * STAGE, smem + qb * STAGE, I_<0>{}, I_<0>{});
       mm(I_<1>{}); interleave(ptc, qtc);
     } else {
       mm(I_<1>{});
@@ -1164,14 +1285,24 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // With ec, the run may hold the slabs that carry the a*X (or A) term.
   auto run = [&](auto ptc, auto qtc, auto ec, int a, int b) __attribute__((always_inline)) {
     if (a >= b) return;
-    rd(ptc, qtc, smem + (a & 1) * STAGE, I_<0>{}, I_<0>{});
-    for (int ks = a; ks < b - 1; ++ks) slab(ptc, qtc, std::true_type{}, ec, ks);
-    slab(ptc, qtc, std::false_type{}, ec, b - 1);
+    if constexpr (SPLIT) {
+      rd(ptc, qtc, smem + pb * STAGE, smem + qb * STAGE, I_<0>{}, I_<0>{});
+#pragma unroll 1
+      for (int t = (pass == 0 ? 5 : 1) * (b - a) - 1; t > 0; --t) step(ptc, qtc, std::true_type{});
+      step(ptc, qtc, std::false_type{});
+    } else {
+      rd(ptc, qtc, smem + (a & 1) * STAGE, smem + (a & 1) * STAGE, I_<0>{}, I_<0>{});
+      for (int ks = a; ks < b - 1; ++ks) slab(ptc, qtc, std::true_type{}, ec, ks);
+      slab(ptc, qtc, std::false_type{}, ec, b - 1);
+    }
   };
   using T_ = std::true_type;
   using F_ = std::false_type;
-  issue(0);
-  if (EARLY && nk > 1) {
+  if constexpr (SPLIT) {
+    issue_op(F_{}, 0, 0, 0);
+    issue_op(T_{}, 0, 0, 2 * ga.q_plane);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else if (issue(0); EARLY && nk > 1) {
     issue(1);
     // slab 0 has landed, slab 1 (NLP + NLQ loads) may not
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLP + NLQ) : "memory");
@@ -1184,6 +1315,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // products Q transposed throughout).
   // The term's slabs lie in the last run (k >= 256 bm for the update
   // products, k >= 256 bn for the polynomial).
+#pragma unroll 1
+  for (int sweep = 0; sweep < (SPLIT ? 2 : 1); ++sweep) {
   if constexpr (EPI == EPI_GRAM) {
     run(F_{}, F_{}, F_{}, 0, nk);
   } else if constexpr (QTR) {
@@ -1193,6 +1326,35 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     run(T_{}, T_{}, F_{}, 0, p_tr_end);
     run(F_{}, T_{}, F_{}, p_tr_end, q_tr_end);
     run(F_{}, F_{}, T_{}, max(p_tr_end, q_tr_end), nk);
+  }
+  }
+
+  if constexpr (SPLIT && EPI != EPI_GRAM) {
+    static_for<BI>([&](auto I) {
+      static_for<BJ>([&](auto J) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[I.value][J.value][q] *= osc;
+      });
+    });
+    constexpr int NE = BM / 64, OPSZ = BM * SLAB;   // slabs that hold the term, and their size
+    const int k0 = (EUPD ? bm : bn) * NE;
+    const int64_t plane = EUPD ? ga.q_plane : ga.p_plane;
+#pragma unroll 1
+    for (int pl = 2; pl >= 0; --pl) {               // smallest first
+#pragma unroll
+      for (int j = 0; j < NE; ++j)
+        if (k0 + j < nk) issue_op(std::bool_constant<EUPD>{}, k0 + j, EUPD ? j * OPSZ - OPQ : j * OPSZ, pl * plane);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if constexpr (EUPD) {
+        take_e(smem + ERS * wm * OPSZ - OPQ, e_ks0);
+        if (ERS > 1) take_e(smem + (ERS * wm + 1) * OPSZ - OPQ, e_ks1);
+      } else {
+        static_assert(EPS == 1, "A term: one slab per wave");
+        take_e(smem + wn * OPSZ, e_ks0);
+      }
+      __syncthreads();
+    }
   }
 
   // ---- epilogue from registers ----------------------------------------------
@@ -1220,7 +1382,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int q4 = lane & 3;
   const int row_base = bm * BM + wm * (BM / WM) + 4 * fsel;
   const int col_base = bn * BN + wn * (BN / WN) + frow;
-  char* const C = ga.C + mat * ga.c_mat;
+  char* C = ga.C + mat * ga.c_mat;
   constexpr int TST = BM * 2 + 8;             // staged column, bytes
   // Natural staging of the output tile: each lane's 4 consecutive rows of one
   // column go to LDS as they are, 8 bytes at column-major position (col, row)
@@ -1228,17 +1390,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // through transposing LDS reads.  No register transposes; diagonal tiles of the symmetric products take
   // their lower triangle from the mirrored column at copy-out.
   constexpr bool stage_n = !FINAL;
-  // The factor the accumulators leave with: c for a polynomial that added
-  // (b/c) A in the main loop; on the first step, whose X holds u unscaled,
-  // r^2 for the Gram product and r for the update products.
-  float osc = 1.f;
-  if (EPI == EPI_POLY) {
-    osc = ga.beta;
-  } else if (ga.xscale) {
-    const float r = ga.xscale[mat];
-    osc = EPI == EPI_GRAM ? r * r : r;
-  }
-
   // Diagonal tiles of the symmetric products are written exactly symmetric:
   // the value computed for (row, col) with row <= col also goes to (col, row),
   // at copy-out.  The output tile goes through LDS because whole 512-byte
@@ -1282,7 +1433,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // (The loads and the per-block work sit in one lambda: inlined that way the
   // compiler keeps every value in registers; written at function scope it
   // spilled.)
-  auto blocks = [&]() {
+  auto blocks = [&](float scale) {
     if (stage_w) {  // the W block has landed in LDS
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -1304,10 +1455,17 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
           const int c0 = col - q4;                     // direct layout: columns c0 .. c0 + 3
           float v[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * g + q] * osc;
+          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * g + q] * scale;
           if (!FINAL || tr) {  // natural layout
             if (stage_n) {
-              *reinterpret_cast<uint2*>(smem + (col - bn * BN) * TST + (row0 - bm * BM) * 2) = pack_bf16x4(v);
+              const uint2 h = pack_bf16x4(v);
+              *reinterpret_cast<uint2*>(smem + (col - bn * BN) * TST + (row0 - bm * BM) * 2) = h;
+              if constexpr (SPLIT) {  // what the next plane holds
+                float e[4];
+                unpack_bf16x4(h, e);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[i][j][4 * g + q] = v[q] - e[q];
+              }
             } else if (stage_w) {      // parameter is l x s: elements (col, row0 .. row0 + 3)
               w_update(smem + wpos(col - wr0, (row0 - wc0) * 2), v);
             } else if (col < ga.l) {
@@ -1330,7 +1488,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       });
     });
   };
-  blocks();
+  if constexpr (FINAL) blocks(SPLIT ? 1.f : osc);
   if (stage_w) {
     __syncthreads();
     // updated W rows -> W, 16 bytes a thread
@@ -1342,8 +1500,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
   }
-  if (stage_n) {
+  if constexpr (stage_n) {
+#pragma unroll 1
+  for (int plane = 0; plane < (SPLIT ? 3 : 1); ++plane) {
+    blocks(plane == 0 && !(SPLIT && EPI != EPI_GRAM) ? osc : 1.f);
     __syncthreads();
+    int ow = wave;
+    if constexpr (SPLIT) asm volatile("" : "+s"(ow));  // (keeps the row addresses inside the loop: hoisted, they spill)
     // Copy-out: a wave instruction writes 4 rows x 256 bytes.  In each
     // 16-lane group G, lane t (r = t / 4, q = t % 4) addresses the 8 bytes
     // (rows R .. R + 3) of column C0 + 8 q + r, then of column C0 + 8 q + 4 + r;
@@ -1355,7 +1518,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     constexpr int KC = BM * BN * 2 / 1024 / NW;   // store instructions per wave
     static_assert(KC * NW * 1024 == BM * BN * 2, "copy-out: whole instructions per wave");
     auto out_row = [&](int it, auto diagc) __attribute__((always_inline)) {
-      const int task = it * NW + wave;                 // 4 rows x 128 columns
+      const int task = it * NW + ow;                   // 4 rows x 128 columns
       constexpr int CB = BN / 128;
       const int R = 4 * (task / CB), C0 = 128 * (task % CB) + 32 * G;
       if (R >= mv || 128 * (task % CB) >= nv) return;  // (wave-uniform)
@@ -1392,7 +1555,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
         }
       }
     }
-    __syncthreads();  // the next tile's loads overwrite the staging area
+    __syncthreads();  // the next plane, or the next tile's loads, overwrite the staging area
+    C += ga.c_plane;
+  }
   }
 }
 
@@ -1401,7 +1566,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 // contiguous logical range r*G + (b % 8)*(G/8) + [0, G/8), i.e. a compact
 // block of the banded order, and start it together, so the tiles of a block
 // stay in step and share each operand slab through the XCD's L2.
-template <int EPI, class Cfg>
+template <int EPI, class Cfg, bool SPLIT>
 __global__ __launch_bounds__(64 * Cfg::NW) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE)))
 void k_gemm_tile(GemmArgs ga) {
   // epilogue staging: the output tile (direct rows) or the mirrored tile
@@ -1415,7 +1580,7 @@ void k_gemm_tile(GemmArgs ga) {
     if (logical >= ga.total_tiles) break;
     int mat, bm, bn;
     tile_from_logical(ga, logical, mat, bm, bn);
-    gemm_tile_body<EPI, Cfg>(ga, smem, mat, bm, bn);
+    gemm_tile_body<EPI, Cfg, SPLIT>(ga, smem, mat, bm, bn);
   }
 }
 
@@ -1448,12 +1613,13 @@ void k_gemm_group(GroupArgs gr) {
     const GemmArgs& ga = gr.ga[c];
     int mat, bm, bn;
     tile_from_logical(ga, logical - gr.start[c], mat, bm, bn);
-    gemm_tile_body<EPI, Cfg>(ga, smem, mat, bm, bn);
+    gemm_tile_body<EPI, Cfg, false>(ga, smem, mat, bm, bn);
   }
 }
 
 // B = b A for a step with c = 0 (cubic tables): no product, one pass over the
 // stored (upper-triangle 256 x 256) tiles of A, a 128 x 128 block a workgroup.
+template <typename XT>
 __global__ __launch_bounds__(256) void k_scale_upper(GemmArgs ga, int t) {
   const int mat = blockIdx.x / (t * t), b = blockIdx.x % (t * t), bm = b / t, bn = b % t;
   if (bn / 2 < bm / 2) return;
@@ -1462,11 +1628,17 @@ __global__ __launch_bounds__(256) void k_scale_upper(GemmArgs ga, int t) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int row = i * 16 + (threadIdx.x >> 4), col = (threadIdx.x & 15) * 8;
-    float v[8];
-    load8(reinterpret_cast<const uint16_t*>(E + static_cast<int64_t>(row) * ga.lde), col, v);
+    float v[8], w[8];
+    const char* e = E + static_cast<int64_t>(row) * ga.lde;
+    load8(reinterpret_cast<const uint16_t*>(e), col, v);
+    for (int p = 1; p < Store<XT>::planes; ++p) {
+      load8(reinterpret_cast<const uint16_t*>(e + p * ga.p_plane), col, w);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] += w[q];
+    }
 #pragma unroll
     for (int q = 0; q < 8; ++q) v[q] *= ga.alpha;
-    store8(reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(row) * ga.ldc), col, v);
+    store8x<XT>(reinterpret_cast<uint16_t*>(C + static_cast<int64_t>(row) * ga.ldc), col, ga.c_plane / 2, v);
   }
 }
 
@@ -1516,14 +1688,15 @@ int device_cu_count() {
   return cache[dev];
 }
 
+template <typename XT>
 hipError_t launch_scale_upper(const GemmArgs& ga, int nmat, hipStream_t st) {
   const int t = ga.m_ext / 128;
-  hipLaunchKernelGGL(k_scale_upper, dim3(static_cast<unsigned>(t * t) * static_cast<unsigned>(nmat)), dim3(256), 0,
+  hipLaunchKernelGGL(k_scale_upper<XT>, dim3(static_cast<unsigned>(t * t) * static_cast<unsigned>(nmat)), dim3(256), 0,
                      st, ga, t);
   return hipGetLastError();
 }
 
-template <class Cfg>
+template <class Cfg, bool SPLIT>
 hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   // ga arrives in 128 x 128 tiles and 128-byte slabs
   ga.m_ext = ga.tiles_m * kTile;
@@ -1536,23 +1709,23 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   // B = b A + c A^2 = c (A^2 + (b/c) A): the A term joins the accumulators
   // in the main loop
   if (epi == EPI_POLY) {
-    if (ga.beta == 0.f) return launch_scale_upper(ga, nmat, st);
-    ga.alpha = ga.alpha / ga.beta;
+    if (ga.beta == 0.f) return launch_scale_upper<std::conditional_t<SPLIT, Split3, uint16_t>>(ga, nmat, st);
+    if (!SPLIT) ga.alpha = ga.alpha / ga.beta;
   }
   // one workgroup per CU slot (persistent), never more workgroups than tiles
   const int slots = device_cu_count() * (160 * 1024 / Cfg::LDS);
   const int g = MUON_PERSISTENT ? min(ga.total_tiles, slots) : ga.total_tiles;
   const dim3 grid(static_cast<unsigned>(g)), block(64 * Cfg::NW);
   switch (epi) {
-    case EPI_GRAM: hipLaunchKernelGGL((k_gemm_tile<EPI_GRAM, Cfg>), grid, block, 0, st, ga); break;
-    case EPI_POLY: hipLaunchKernelGGL((k_gemm_tile<EPI_POLY, Cfg>), grid, block, 0, st, ga); break;
-    case EPI_UPDATE: hipLaunchKernelGGL((k_gemm_tile<EPI_UPDATE, Cfg>), grid, block, 0, st, ga); break;
+    case EPI_GRAM: hipLaunchKernelGGL((k_gemm_tile<EPI_GRAM, Cfg, SPLIT>), grid, block, 0, st, ga); break;
+    case EPI_POLY: hipLaunchKernelGGL((k_gemm_tile<EPI_POLY, Cfg, SPLIT>), grid, block, 0, st, ga); break;
+    case EPI_UPDATE: hipLaunchKernelGGL((k_gemm_tile<EPI_UPDATE, Cfg, SPLIT>), grid, block, 0, st, ga); break;
     default: {
       const bool o = ga.final_kind != 0, f32 = ga.param_dtype == DT_F32;
-      if (!o && !f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_BF16, Cfg>), grid, block, 0, st, ga);
-      else if (!o) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_F32, Cfg>), grid, block, 0, st, ga);
-      else if (!f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_BF16, Cfg>), grid, block, 0, st, ga);
-      else hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_F32, Cfg>), grid, block, 0, st, ga);
+      if (!o && !f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_BF16, Cfg, SPLIT>), grid, block, 0, st, ga);
+      else if (!o) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_F32, Cfg, SPLIT>), grid, block, 0, st, ga);
+      else if (!f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_BF16, Cfg, SPLIT>), grid, block, 0, st, ga);
+      else hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_F32, Cfg, SPLIT>), grid, block, 0, st, ga);
       break;
     }
   }
@@ -1580,7 +1753,7 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
     ga.total_tiles = ga.tiles_per_mat * nmats[i];
     if (epi == EPI_POLY) {
       if (ga.beta == 0.f) {
-        const hipError_t e = launch_scale_upper(ga, nmats[i], st);
+        const hipError_t e = launch_scale_upper<uint16_t>(ga, nmats[i], st);
         if (e != hipSuccess) return e;
         continue;
       }
@@ -1623,11 +1796,11 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
 // Measured per launch, 256 / 128: Gram of 2048 x 5632, three matrices 119 / 89,
 // one 114 / 73; update of 512 x 512, one matrix 21 / 12, 256 matrices 104 /
 // 122; update of 4096 x 11008 319 / 387; Gram of 768 x 768, 48 matrices 54 / 39.
-bool small_tiles(const GemmArgs& ga, int nmat) {
+bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
   const int64_t m1 = ga.tiles_m, n1 = ga.tiles_n, m2 = (m1 + 1) / 2, n2 = (n1 + 1) / 2;
   const double t1 = double(nmat) * double(ga.syrk ? m1 * (m1 + 1) / 2 : m1 * n1);
   const double t2 = double(nmat) * double(ga.syrk ? m2 * (m2 + 1) / 2 : m2 * n2);
-  const double cus = device_cu_count(), nk = ga.k_slabs;
+  const double cus = device_cu_count(), nk = ga.k_slabs * (split ? 6 : 1);
   const double rounds2 = std::ceil(t2 / cus), f = t2 / (rounds2 * cus);
   const double r1 = t1 / (2.0 * cus), rounds1 = std::ceil(r1);
   const double cost2 = rounds2 * ((1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f);
@@ -2137,6 +2310,13 @@ hipError_t run_small(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
   return hipSuccess;
 }
 
+// Whether a chunk stored as XT runs its products on the tile kernel.
+template <typename XT>
+bool runs_on_tiles(const ChunkGeom& cg, int K) {
+  if (std::is_same<XT, Split3>::value) return true;
+  return !std::is_same<XT, float>::value && chunk_on_tiles(cg.S, cg.L, K);
+}
+
 template <typename GT, typename XT>
 hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb,
                        const StepScalars& sc, const float* coeffs, int K, hipStream_t st,
@@ -2146,15 +2326,16 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
   const int64_t numel = static_cast<int64_t>(cg.s) * cg.l;
   const double ne = double(numel);
   const int nparts = static_cast<int>(norm_tiles(cg.S, cg.L));
-  const double gsz = sizeof(GT), xsz = sizeof(XT);
+  using E = typename Store<XT>::E;
+  const double gsz = sizeof(GT), xsz = sizeof(E) * Store<XT>::planes;
   const double psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
   // On the 256 x 256 kernel the update products read X through transposing
   // LDS reads, so no X^T is kept (K = 0 applies X0 from whichever layout
   // matches the parameter).
-  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
-  XT* const xt0 = qtr ? nullptr : static_cast<XT*>(wb.XT[0]);
+  const bool qtr = runs_on_tiles<XT>(cg, K);
+  E* const xt0 = qtr ? nullptr : static_cast<E*>(wb.XT[0]);
   hipError_t e;
-  XT* const x0 = static_cast<XT*>(wb.X[0]);
+  E* const x0 = static_cast<E*>(wb.X[0]);
   {
     Timed tm(timer, KK_PARTIALS, st);
     const dim3 grid(cg.L / 64, cg.S / 64, nmat);
@@ -2186,7 +2367,7 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
     tm.done(0, 0, nm * 12.0);  // nothing else unless a norm is out of range
   }
 
-  if (K == 0) {
+  if constexpr (!std::is_same<XT, Split3>::value) if (K == 0) {
     Timed tm(timer, KK_APPLY_X0, st);
     const int64_t blocks = (numel + 255) / 256;
     hipLaunchKernelGGL((k_apply_x0<XT>), dim3(static_cast<unsigned>(blocks), nmat), dim3(256), 0, st,
@@ -2211,14 +2392,16 @@ struct StepProducts {
 template <typename XT>
 StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb,
                            const StepScalars& sc, const float* coeffs, int K, int k, int cur) {
-  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
+  const bool qtr = runs_on_tiles<XT>(cg, K);
   const double nm = cg.nmat;
   const double s = cg.s, l = cg.l;
-  const double xsz = sizeof(XT);
+  constexpr int planes = Store<XT>::planes;
+  constexpr int pairs = planes == 3 ? 6 : 1;  // products of planes per product of values
+  const int es = static_cast<int>(sizeof(typename Store<XT>::E));
+  const double xsz = es * planes;
   const double psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
-  const int es = static_cast<int>(sizeof(XT));
-  const int64_t matX = static_cast<int64_t>(cg.S) * cg.L * es;
-  const int64_t matA = static_cast<int64_t>(cg.S) * cg.S * es;
+  const int64_t planeX = static_cast<int64_t>(cg.S) * cg.L * es, matX = planeX * planes;
+  const int64_t planeA = static_cast<int64_t>(cg.S) * cg.S * es, matA = planeA * planes;
   const int ts = cg.S / kTile, tl = cg.L / kTile;
   // Work accounting: `flops` is the dense count of each product on the real
   // extents (Eq. 1); `exec` is what the MFMAs execute: whole tiles of the
@@ -2237,12 +2420,13 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   g.k_slabs = cg.L * es / 128;
   g.tiles_m = ts; g.tiles_n = ts; g.syrk = 1; g.tiles_per_mat = ts * (ts + 1) / 2;
   g.C = static_cast<char*>(wb.A); g.c_mat = matA; g.ldc = cg.S * es;
+  g.p_plane = g.q_plane = planeX; g.c_plane = planeA;
   g.xscale = k == 0 ? wb.xscale : nullptr;  // A0 = r^2 X~ X~^T
   // Under qtr every consumer of A and B runs on the 256 x 256 kernel and
   // reads them as upper-triangle tiles (mode 1): no mirrored tile is
   // written.  Otherwise the lower triangle is written as the mirror.
   if (!qtr) { g.CT = g.C; g.ct_mat = matA; g.ldct = g.ldc; }
-  r.f[0] = nm * 2 * s * s * l; r.x[0] = nm * 2 * upper * Lp; r.b[0] = nm * (s * l + s * s) * xsz;
+  r.f[0] = nm * 2 * s * s * l; r.x[0] = nm * 2 * pairs * upper * Lp; r.b[0] = nm * (s * l + s * s) * xsz;
   // B = b A + c A A^T: M = N = K = S.
   GemmArgs& pp = r.poly;
   pp = g;
@@ -2253,8 +2437,9 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   pp.E = pp.P; pp.e_mat = matA; pp.lde = pp.ldp;
   pp.C = static_cast<char*>(wb.B); pp.CT = qtr ? nullptr : pp.C;
   pp.p_mode = pp.q_mode = qtr ? 1 : 0;
+  pp.p_plane = pp.q_plane = planeA;
   pp.alpha = b; pp.beta = c;
-  r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * upper * Sp; r.b[1] = nm * 2 * s * s * xsz;
+  r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * pairs * upper * Sp; r.b[1] = nm * 2 * s * s * xsz;
   // X' = a X + B X: M = S, N = L, K = S.  The second operand is X^T (N x K,
   // K contiguous) on the 128 x 128 kernel, X itself (K x N) under qtr.
   GemmArgs& u = r.upd;
@@ -2266,13 +2451,14 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   } else {
     u.Q = XTc; u.q_mat = matX; u.ldq = cg.S * es;
   }
+  u.p_plane = planeA; u.q_plane = u.c_plane = planeX;
   u.k_slabs = cg.S * es / 128;
   u.tiles_m = ts; u.tiles_n = tl; u.syrk = 0; u.tiles_per_mat = ts * tl;
   u.E = X; u.e_mat = matX; u.lde = cg.L * es;
   u.alpha = a;
   u.s = cg.s; u.l = cg.l;
   u.xscale = k == 0 ? wb.xscale : nullptr;  // X1 = r (a X~ + B0 X~)
-  r.f[2] = nm * 2 * s * s * l; r.x[2] = nm * 2 * (TS * te) * (TL * te) * Sp;
+  r.f[2] = nm * 2 * s * s * l; r.x[2] = nm * 2 * pairs * (TS * te) * (TL * te) * Sp;
   r.last = k + 1 == K;
   if (!r.last) {
     u.C = static_cast<char*>(wb.X[cur ^ 1]); u.c_mat = matX; u.ldc = cg.L * es;
@@ -2291,15 +2477,21 @@ template <typename GT, typename XT>
 hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb,
                        const StepScalars& sc, const float* coeffs, int K, hipStream_t st,
                        LaunchTimer* timer) {
-  if (wb.sync) return run_small<GT, XT>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+  constexpr bool split = std::is_same<XT, Split3>::value;
+  if constexpr (!split)
+    if (wb.sync) return run_small<GT, XT>(cg, d_desc, wb, sc, coeffs, K, st, timer);
   hipError_t e = run_prologue_t<GT, XT>(cg, d_desc, wb, sc, coeffs, K, st, timer);
   if (e != hipSuccess || K == 0) return e;
-  const bool qtr = chunk_on_tiles(cg.S, cg.L, sizeof(XT) == 4, K);
+  const bool qtr = runs_on_tiles<XT>(cg, K);
   const int nmat = cg.nmat;
   auto launch = [&](int epi, const GemmArgs& ga) {
-    if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st);
-    return small_tiles(ga, nmat) ? launch_tile<CfgQuarter>(epi, ga, nmat, st)
-                                 : launch_tile<CfgSquare>(epi, ga, nmat, st);
+    if constexpr (!split)
+      if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st);
+    if constexpr (std::is_same<XT, float>::value)
+      return hipErrorInvalidValue;
+    else
+      return small_tiles(ga, nmat, split) ? launch_tile<CfgQuarter, split>(epi, ga, nmat, st)
+                                          : launch_tile<CfgSquare, split>(epi, ga, nmat, st);
   };
   int cur = 0;
   for (int k = 0; k < K; ++k) {
@@ -2331,6 +2523,10 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
                      const StepScalars& sc, const float* coeffs, int K, hipStream_t st,
                      LaunchTimer* timer) {
   const bool gbf = cg.grad_dtype == DT_BF16;
+  if (cg.ns_f32 && !wb.sync && chunk_on_tiles(cg.S, cg.L, K)) {
+    return gbf ? run_chunk_t<uint16_t, Split3>(cg, d_desc, wb, sc, coeffs, K, st, timer)
+               : run_chunk_t<float, Split3>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+  }
   if (cg.ns_f32) {
     return gbf ? run_chunk_t<uint16_t, float>(cg, d_desc, wb, sc, coeffs, K, st, timer)
                : run_chunk_t<float, float>(cg, d_desc, wb, sc, coeffs, K, st, timer);
