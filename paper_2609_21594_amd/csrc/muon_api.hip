@@ -569,7 +569,7 @@ void layout_chunk(Chunk& c, bool ns_f32, int K) {
   const size_t es = ns_f32 ? 4 : 2;
   const size_t xb = align256(size_t(c.count) * size_t(c.S) * size_t(c.L) * es);
   const size_t ab = align256(size_t(c.count) * size_t(c.S) * size_t(c.S) * es);
-  const bool small = muon::chunk_is_small(c.s, c.l, ns_f32);
+  const bool small = muon::chunk_reserves_small(c.s, c.l, ns_f32);
   const size_t parts = std::max<size_t>(size_t(muon::norm_tiles(c.S, c.L)), small ? muon::kSmallMaxGroup : 0);
   const size_t pb = align256(size_t(c.count) * parts * 8);
   c.keeps_xt = muon::chunk_keeps_xt(c.S, c.L, ns_f32, K);
@@ -582,7 +582,7 @@ void layout_chunk(Chunk& c, bool ns_f32, int K) {
   }
   c.off_A = off; off += ab;
   c.off_B = off; off += ab;
-  if (ns_f32 && !small && muon::chunk_on_tiles(c.S, c.L, K)) {
+  if (ns_f32 && !muon::chunk_is_small(c.s, c.l, ns_f32, K) && muon::chunk_on_tiles(c.S, c.L, K)) {
     // X, X', A and B in three bf16 planes each, over the same bytes
     const size_t x3 = xb / 4 * 6, a3 = ab / 4 * 6;  // (extents are multiples of 128)
     c.off_X[0] = 0; c.off_X[1] = x3;
@@ -1035,6 +1035,7 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
       const bool odd = on_side[ui] != 0;
       char* const base = static_cast<char*>(h->ws) + (odd ? slot : 0);
       const hipStream_t cs = odd ? h->side : s;
+      const int K = steps_of(plan.chunks[u.members[0]]);
       muon::GroupMember gm[muon::kGroupMax];
       for (size_t mi = 0; mi < u.members.size(); ++mi) {
         const Chunk& c = plan.chunks[u.members[mi]];
@@ -1047,11 +1048,10 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
         b.partials = reinterpret_cast<double*>(ws + c.off_part);
         b.rscale = reinterpret_cast<double*>(ws + c.off_r);
         b.xscale = reinterpret_cast<float*>(b.rscale + c.count);
-        b.sync = muon::chunk_is_small(c.s, c.l, ns_f32) ? reinterpret_cast<unsigned*>(ws + c.off_sync) : nullptr;
+        b.sync = muon::chunk_is_small(c.s, c.l, ns_f32, K) ? reinterpret_cast<unsigned*>(ws + c.off_sync) : nullptr;
         gm[mi] = muon::GroupMember{geom_of(c), d_desc + c.first, b, tables[size_t(c.cset)].data()};
       }
       muon::LaunchTimer* const tmr = h->profiling ? &h->timer : nullptr;
-      const int K = steps_of(plan.chunks[u.members[0]]);
       if (u.members.size() == 1)
         launch_err = muon::run_chunk(gm[0].geom, gm[0].desc, gm[0].wb, sc, gm[0].coeffs, K, cs, tmr);
       else
@@ -1688,7 +1688,7 @@ muon_status_t ns_orthogonalize_batched_noalloc(muon_handle_t h, const void* cons
     b.partials = reinterpret_cast<double*>(ws + c.off_part);
     b.rscale = reinterpret_cast<double*>(ws + c.off_r);
     b.xscale = reinterpret_cast<float*>(b.rscale + c.count);
-    b.sync = muon::chunk_is_small(c.s, c.l, f32) ? reinterpret_cast<unsigned*>(ws + c.off_sync) : nullptr;
+    b.sync = muon::chunk_is_small(c.s, c.l, f32, K) ? reinterpret_cast<unsigned*>(ws + c.off_sync) : nullptr;
     if ((e = muon::run_chunk(g, d_desc + c.first, b, sc, ct, K, stream, nullptr)) != hipSuccess)
       return device_fail(h, "kernel launch", e);
   }

@@ -127,20 +127,32 @@ inline bool chunk_on_tiles(int64_t S, int64_t L, int K) { return K > 0 && tile_r
 inline bool chunk_keeps_xt(int64_t S, int64_t L, bool ns_f32, int K) {
   return ns_f32 || !chunk_on_tiles(S, L, K) || S % 256 != 0 || L % 256 != 0;
 }
-// A chunk runs as one fused launch (k_ns_small: momentum, norm, every
-// Newton-Schulz step and the update) when its short side is at most 128 and
-// the fused launch is the faster one for its shape: always for fp32 NS; for
-// bf16 NS when the short side is at most 64 or the long side at most 512
-// (measured: 64 matrices of 128 x 2048 run twice as fast as 128 x 128 tiles,
-// whose operand units carry four times the flops per byte).  The choice
-// depends on the shape alone, so a matrix gets the same bits in any batch.
-// Such a chunk also needs the group counters (kSmallSyncBytes) and
-// kSmallMaxGroup norm partials per matrix.
+// A chunk whose short side is at most 128 runs in one of two ways, by its
+// shape alone, so that a matrix gets the same bits in any batch:
+//  - as one fused launch (k_ns_small: momentum, norm, every Newton-Schulz step
+//    and the update, the workgroups of a matrix meeting at barriers): fp32
+//    Newton-Schulz, K = 0, and bf16 matrices of at most 64 x 384 or 128 x 256;
+//  - as column slices (k_slice_*: two launches a step over all matrices): the
+//    other bf16 ones, with at least one step.
+// Measured on an MI355X (us per call, bf16 orthogonalisation, fused / slices):
+// one 16 x 128 38 / 40, 16 x 1024 97 / 51, 64 x 300 56 / 62, 64 x 512 63 / 64,
+// 128 x 256 51 / 76, 128 x 512 71 / 77; 64 matrices of 64 x 300 121 / 130, of
+// 64 x 512 150 / 132, of 128 x 512 288 / 130, of 64 x 4096 1029 / 184.
+// The fused launch needs group counters (kSmallSyncBytes) and kSmallMaxGroup
+// norm partials per matrix.  chunk_reserves_small says which chunks reserve
+// them: also some that now run as slices, since what a call needs of a
+// limited workspace is part of the interface.
 constexpr int kSmallMaxGroup = 32;
 constexpr int64_t kSmallSyncBytes = 64 * 1024;
-inline bool chunk_is_small(int64_t s, int64_t l, bool ns_f32) {
+inline bool chunk_reserves_small(int64_t s, int64_t l, bool ns_f32) {
   if (s > 128 || l > (int64_t(1) << 16)) return false;
   return ns_f32 || s <= 64 || l <= 512;
+}
+inline bool chunk_is_small(int64_t s, int64_t l, bool ns_f32, int K) {
+  return chunk_reserves_small(s, l, ns_f32) && (ns_f32 || K == 0 || l <= (s <= 32 || s > 64 ? 256 : 384));
+}
+inline bool chunk_is_sliced(int64_t s, int64_t l, bool ns_f32, int K) {
+  return !ns_f32 && s <= 128 && chunk_on_tiles(128, round_up(l, kPad), K) && !chunk_is_small(s, l, ns_f32, K);
 }
 
 // A group: chunks whose products of each Newton-Schulz step run as one

@@ -2258,6 +2258,559 @@ __global__ __launch_bounds__(256) void k_ns_small(SmallArgs sa) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// bf16 Newton-Schulz for short sides up to 128 (k_slice_*).  The tile kernel
+// has one Gram tile per such matrix (64 slabs of k on one compute unit for
+// 128 x 4096) and half-empty update tiles; here X is cut into column slices
+// of 64 KB, one per workgroup, and a step is two launches over all matrices:
+//   k_slice_reduce  A = sum of the slices' Gram partials (fp32, in slice
+//                   order; r^2 on the first step), stored as bf16, whole;
+//   k_slice_step    per slice: B = b A + c A A (32 KB of A: cheaper to form
+//                   in each workgroup than to launch for), X' = a X + B X in
+//                   LDS, X' to memory, and the Gram partial of X'; the last
+//                   step writes the parameter (or output) instead.
+// k_slice_first does the prologue (momentum, u, its square sum) and the first
+// Gram partial while the slice is in LDS.  The slice width is a function of
+// the short side alone, so results do not depend on the batch.
+// What bounds it: the launches (about 4 us each, 2 K + 2 of them) for a few
+// matrices, HBM and L2 traffic of the slices for many.
+//
+// RB: 32-row blocks of the padded short side (1, 2 or 4).  A slice has
+// w = 1024 / RB columns; wavefront v of 8 owns columns [v w/8, (v + 1) w/8)
+// in the update.  LDS row r of a slice holds 16-byte chunk c at position
+// c ^ key(r), key(r) = 4 (r % 4) + (r / 4) % 4: the transposing reads of
+// 32 columns x 4 rows, the fragment reads of 32 rows x 16 bytes and the 8-byte
+// accesses of 32 rows all spread over the banks.
+// ---------------------------------------------------------------------------
+struct SliceArgs {
+  const MatDesc* desc;
+  StepScalars sc;
+  int32_t s, l, L;
+  int32_t nsl, np;           // slices and Gram partials per matrix
+  int32_t first;
+  uint16_t* X;               // per matrix: S x L (matX elements), rows of stride L
+  int64_t matX;
+  float* part;               // per matrix: np x NB x 1024, MFMA output order
+  uint16_t* A;               // per matrix: Sx x Sx
+  double* norm;              // per matrix: nsl
+  float a, b, c;
+};
+
+template <int RB>
+struct SliceCfg {
+  static constexpr int Sx = 32 * RB, W = 1024 / RB, PITCH = 2 * W;   // PITCH: bytes of a slice row
+  static constexpr int SW = W / 8;                                   // columns of a wavefront
+  static constexpr int NB = RB * (RB + 1) / 2;                       // upper 32 x 32 blocks of A
+  static constexpr int AP = 2 * Sx, ABYTES = Sx * AP;                // A row, A
+  static constexpr bool KSPLIT = RB < 4;  // Gram: each wavefront its own columns (a partial each), else output blocks
+  static constexpr int PPS = KSPLIT ? 8 : 1;                         // partials of a full slice
+};
+__device__ __forceinline__ int slice_key(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+// LDS byte of column col (in elements) of slice row r
+template <int RB>
+__device__ __forceinline__ int slice_at(int r, int col) {
+  return r * SliceCfg<RB>::PITCH + (((col >> 3) ^ slice_key(r)) << 4) + (col & 7) * 2;
+}
+// LDS byte of element (r, c) of A or B
+template <int RB>
+__device__ __forceinline__ int slice_a_at(int r, int c) {
+  return r * SliceCfg<RB>::AP + (((c >> 3) ^ (slice_key(r) & (4 * RB - 1))) << 4) + (c & 7) * 2;
+}
+
+// r = 1 / (||u|| + eps) from a matrix's slice sums, by all 256 or 512 threads
+// of the workgroup in a fixed order (red: one double per wavefront).
+__device__ __forceinline__ double slice_r(const double* norm, int n, float eps, double* red) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256)
+    if (threadIdx.x < 256) v += norm[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const double s = ((red[0] + red[1]) + red[2]) + red[3];
+  return 1.0 / (sqrt(s) + static_cast<double>(eps));
+}
+// The first step's scale: r itself where r^2 u u^T stays well inside the fp32
+// range, else 1 (X then holds r u, see k_slice_first<RESCALE>).
+__device__ __forceinline__ bool slice_folds(double r) { return r >= 0x1p-40 && r <= 0x1p40; }
+
+// The Gram partial(s) of the slice in LDS (nv columns, a multiple of 128).
+template <int RB>
+__device__ __forceinline__ void slice_gram(const char* xs, int nv, float* part) {
+  using C = SliceCfg<RB>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto frag = [&](int rb, int col) {
+    return *reinterpret_cast<const u32x4_t*>(xs + slice_at<RB>(32 * rb + (lane & 31), col + 8 * (lane >> 5)));
+  };
+  auto put = [&](float* p, const f32x16_t& v) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(p + g * 256 + lane * 4) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+  };
+  if constexpr (C::KSPLIT) {
+    const int c0 = wave * C::SW;
+    if (c0 >= nv) return;
+    f32x16_t acc[C::NB] = {};
+#pragma unroll
+    for (int g = 0; g < C::SW / 16; ++g) {
+      u32x4_t f[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) f[i] = frag(i, c0 + 16 * g);
+#pragma unroll
+      for (int j = 0; j < RB; ++j)
+#pragma unroll
+        for (int i = 0; i <= j; ++i) Mma<uint16_t>::run(f[i], f[j], acc[j * (j + 1) / 2 + i]);
+    }
+    float* p = part + static_cast<int64_t>(wave) * C::NB * 1024;
+#pragma unroll
+    for (int n = 0; n < C::NB; ++n) put(p + n * 1024, acc[n]);
+  } else {
+    // wavefront (wm, wn): row blocks 2 wm and 2 wm + 1 of column block wn, those on or above the diagonal
+    const int wm = wave >> 2, wn = wave & 3;
+    if (2 * wm > wn) return;
+    const bool two = 2 * wm + 1 <= wn;
+    f32x16_t acc[2] = {};
+    for (int g = 0; g < nv / 16; ++g) {
+      const u32x4_t q = frag(wn, 16 * g);
+      Mma<uint16_t>::run(frag(2 * wm, 16 * g), q, acc[0]);
+      if (two) Mma<uint16_t>::run(frag(2 * wm + 1, 16 * g), q, acc[1]);
+    }
+    float* p = part + (wn * (wn + 1) / 2 + 2 * wm) * 1024;
+    put(p, acc[0]);
+    if (two) put(p + 1024, acc[1]);
+  }
+}
+
+// The slice in LDS -> memory, 16 bytes a thread.
+template <int RB>
+__device__ __forceinline__ void slice_store(const char* xs, int nv, uint16_t* X, int L) {
+  using C = SliceCfg<RB>;
+  for (int i = threadIdx.x; i < C::Sx * (C::W / 8); i += 512) {
+    const int r = i / (C::W / 8), ch = i % (C::W / 8);
+    if (8 * ch >= nv) continue;
+    *reinterpret_cast<u32x4_t*>(X + static_cast<int64_t>(r) * L + 8 * ch) =
+        *reinterpret_cast<const u32x4_t*>(xs + slice_at<RB>(r, 8 * ch));
+  }
+}
+
+// Prologue: momentum in place, u (zero outside the matrix) as bf16 into LDS
+// and X, its square sum, the first Gram partial.  RESCALE: the matrices whose
+// r cannot be applied to the products get X0 = r u and its Gram partial
+// instead (the momentum is already advanced); all others return at once.
+template <typename GT, int RB, bool MOM, bool RESCALE>
+__global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
+  using C = SliceCfg<RB>;
+  __shared__ __attribute__((aligned(16))) char xs[C::Sx * C::PITCH];
+  __shared__ double red[8];
+  const int m = blockIdx.x / sa.nsl, j = blockIdx.x % sa.nsl;
+  const int c0 = j * C::W, nv = min(C::W, sa.L - c0);
+  float s1 = 1.f, s2 = 1.f;
+  if (RESCALE) {
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    if (slice_folds(r)) return;
+    split_scale(r, s1, s2);
+  }
+  const MatDesc md = sa.desc[m];
+  const bool tr = md.transposed != 0;
+  const GT* g = static_cast<const GT*>(md.g);
+  const float beta = sa.sc.beta, omb = sa.sc.one_minus_beta;
+  double acc = 0.0;
+  // units of 8 consecutive elements of a row of u: 8 columns of X (u s x l), or
+  // 8 rows of X (u l x s)
+  const int upr = tr ? C::Sx / 8 : nv / 8;                 // units per row of u
+  const int nu = tr ? nv * upr : C::Sx * upr;
+  for (int i = threadIdx.x; i < nu; i += 512) {
+    const int a = i / upr, e = (i - a * upr) * 8;
+    const int ur = tr ? c0 + a : a, uc = tr ? e : c0 + e;
+    float v[8];
+    if (md.row8_ok && ur < md.rows && uc + 8 <= md.cols) {
+      float gv[8], bv[8];
+      load8(g, view_index(md, ur, uc), gv);
+      if (MOM) {
+        const int64_t ib = buf_index(md, ur, uc);
+        load8(md.buf, ib, bv);
+        if (!RESCALE) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) bv[q] = fmaf(beta, bv[q], omb * gv[q]);
+          store8(md.buf, ib, bv);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = sa.sc.nesterov ? fmaf(beta, bv[q], omb * gv[q]) : bv[q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = gv[q];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        acc = fma(static_cast<double>(v[q]), static_cast<double>(v[q]), acc);
+        v[q] = (v[q] * s1) * s2;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        v[q] = 0.f;  // padding stays exactly zero, whatever the scale
+        if (ur < md.rows && uc + q < md.cols) {
+          const float gv = to_f32<GT>(g[view_index(md, ur, uc + q)]);
+          v[q] = gv;
+          if (MOM) {
+            const int64_t ib = buf_index(md, ur, uc + q);
+            float bn = md.buf[ib];
+            if (!RESCALE) {
+              bn = fmaf(beta, bn, omb * gv);
+              md.buf[ib] = bn;
+            }
+            v[q] = sa.sc.nesterov ? fmaf(beta, bn, omb * gv) : bn;
+          }
+          acc = fma(static_cast<double>(v[q]), static_cast<double>(v[q]), acc);
+          v[q] = (v[q] * s1) * s2;
+        }
+      }
+    }
+    if (tr) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint16_t*>(xs + slice_at<RB>(e + q, a)) = f32_to_bf16(v[q]);
+    } else {
+      store8(reinterpret_cast<uint16_t*>(xs + slice_at<RB>(a, e)), 0, v);
+    }
+  }
+  if (!RESCALE) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  }
+  __syncthreads();
+  if (!RESCALE && threadIdx.x == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) t += red[w];
+    sa.norm[static_cast<int64_t>(m) * sa.nsl + j] = t;
+  }
+  slice_store<RB>(xs, nv, sa.X + m * sa.matX + c0, sa.L);
+  slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
+}
+
+// A = sum of the partials (times r^2 on the first step), one 32 x 32 block
+// per workgroup, written on both sides of the diagonal.
+template <int RB>
+__global__ __launch_bounds__(256) void k_slice_reduce(SliceArgs sa) {
+  using C = SliceCfg<RB>;
+  __shared__ double red[4];
+  const int m = blockIdx.x / C::NB, nb = blockIdx.x % C::NB;
+  float scale = 1.f;
+  if (sa.first) {
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    const float rf = slice_folds(r) ? static_cast<float>(r) : 1.f;
+    scale = rf * rf;
+  }
+  constexpr int64_t PS = C::NB * 1024;
+  const float* p = sa.part + static_cast<int64_t>(m) * sa.np * PS + nb * 1024 + threadIdx.x * 4;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < sa.np; i += 8) {
+    float4 t[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (i + q < sa.np) t[q] = *reinterpret_cast<const float4*>(p + (i + q) * PS);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (i + q < sa.np) {
+        v[0] += t[q].x; v[1] += t[q].y; v[2] += t[q].z; v[3] += t[q].w;
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] *= scale;
+  int bj = 0;
+  while ((bj + 1) * (bj + 2) / 2 <= nb) ++bj;
+  const int bi = nb - bj * (bj + 1) / 2, lane = threadIdx.x & 63;
+  const int row = 32 * bi + 8 * (threadIdx.x >> 6) + 4 * (lane >> 5), col = 32 * bj + (lane & 31);
+  uint16_t* A = sa.A + static_cast<int64_t>(m) * C::Sx * C::Sx;
+  const uint2 h = pack_bf16x4(v);
+  *reinterpret_cast<uint2*>(A + col * C::Sx + row) = h;
+  if (bi != bj) {
+    A[row * C::Sx + col] = static_cast<uint16_t>(h.x);
+    A[(row + 1) * C::Sx + col] = static_cast<uint16_t>(h.x >> 16);
+    A[(row + 2) * C::Sx + col] = static_cast<uint16_t>(h.y);
+    A[(row + 3) * C::Sx + col] = static_cast<uint16_t>(h.y >> 16);
+  }
+}
+
+// 4 elements of the parameter as they lie in memory, and as fp32.
+template <int PDT> struct Quad { using T = uint2; };
+template <> struct Quad<DT_F32> { using T = float4; };
+__device__ __forceinline__ void quad_get(uint2 t, float v[4]) { unpack_bf16x4(t, v); }
+__device__ __forceinline__ void quad_get(float4 t, float v[4]) { v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
+__device__ __forceinline__ void quad_put(uint2* p, const float v[4]) { *p = pack_bf16x4(v); }
+__device__ __forceinline__ void quad_put(float4* p, const float v[4]) { *p = make_float4(v[0], v[1], v[2], v[3]); }
+
+// FK: -1 a middle step; 0 the last, updating W; 1 the last, writing out (both
+// of dtype PDT).
+template <int RB, int FK, int PDT>
+__global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
+  using C = SliceCfg<RB>;
+  constexpr bool FINAL = FK >= 0;
+  constexpr int XB = C::Sx * C::PITCH;                     // 64 KB
+  __shared__ __attribute__((aligned(1024))) char smem[XB + C::ABYTES];
+  __shared__ double red[4];
+  char* const xs = smem;
+  char* const as = smem + XB;
+  const int m = blockIdx.x / sa.nsl, j = blockIdx.x % sa.nsl;
+  const int c0 = j * C::W, nv = min(C::W, sa.L - c0);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds0 = lds_offset(smem);
+  uint16_t* const X = sa.X + m * sa.matX + c0;
+  const char* const Ag = reinterpret_cast<const char*>(sa.A + static_cast<int64_t>(m) * C::Sx * C::Sx);
+  float osc = 1.f;
+  if (sa.first) {
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    if (slice_folds(r)) osc = static_cast<float>(r);
+  }
+  // ---- A and the slice into LDS: 1 KB per wavefront instruction, lane i the
+  // 16 bytes at 16 i; each lane fetches the chunk that belongs there ----------
+  constexpr int ACH = C::AP / 16, AI = C::ABYTES / 1024;   // chunks of an A row; instructions
+#pragma unroll
+  for (int k = 0; k < (AI + 7) / 8; ++k) {
+    const int t = wave + 8 * k;
+    if (t < AI) {
+      const int p = t * 64 + lane, r = p / ACH;
+      load_lds16(Ag, static_cast<uint32_t>(r * C::AP + ((p % ACH) ^ (slice_key(r) & (ACH - 1))) * 16),
+                 lds0 + XB + t * 1024);
+    }
+  }
+  constexpr int XCH = C::PITCH / 16;                       // chunks of a slice row
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int t = wave + 8 * k, p = t * 64 + lane, r = p / XCH;
+    int ch = (p % XCH) ^ slice_key(r);
+    if (8 * ch >= nv) ch &= 15;                            // past the matrix: any chunk of the row (not used)
+    load_lds16(reinterpret_cast<const char*>(X), static_cast<uint32_t>(r) * static_cast<uint32_t>(sa.L * 2) + ch * 16,
+               lds0 + t * 1024);
+  }
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");         // A has landed, the slice may not
+  __syncthreads();
+  // ---- B = b A + c A A, in place --------------------------------------------
+  constexpr int PB = RB == 4 ? 2 : 1;                      // 32 x 32 blocks of B per wavefront
+  const int pi = RB == 4 ? 2 * (wave >> 2) : wave / RB, pj = RB == 4 ? (wave & 3) : wave % RB;
+  const bool pact = RB == 4 || wave < RB * RB;
+  uint2 bh[PB][4];
+  if (pact) {
+    auto afrag = [&](int rb, int g) {
+      return *reinterpret_cast<const u32x4_t*>(as + slice_a_at<RB>(32 * rb + (lane & 31), 16 * g + 8 * (lane >> 5)));
+    };
+    f32x16_t acc[PB] = {};
+#pragma unroll
+    for (int g = 0; g < C::Sx / 16; ++g) {
+      const u32x4_t q = afrag(pj, g);
+#pragma unroll
+      for (int i = 0; i < PB; ++i) Mma<uint16_t>::run(afrag(pi + i, g), q, acc[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        // rows row .. row + 3 of column col; A is symmetric, so they lie in row col
+        const int row = 32 * (pi + i) + 8 * g + 4 * (lane >> 5), col = 32 * pj + (lane & 31);
+        float e[4], v[4];
+        unpack_bf16x4(*reinterpret_cast<const uint2*>(as + slice_a_at<RB>(col, row)), e);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = fmaf(sa.b, e[q], sa.c * acc[i][4 * g + q]);
+        bh[i][g] = pack_bf16x4(v);
+      }
+  }
+  __syncthreads();                                         // every read of A is done
+  if (pact) {
+#pragma unroll
+    for (int i = 0; i < PB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int row = 32 * (pi + i) + 8 * g + 4 * (lane >> 5), col = 32 * pj + (lane & 31);
+        *reinterpret_cast<uint2*>(as + slice_a_at<RB>(col, row)) = bh[i][g];  // B is symmetric too
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the slice has landed
+  __syncthreads();
+  // the last step: this half's part of the matrix in the parameter's layout,
+  // and its W values, read ahead
+  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
+  using QT = typename Quad<PDT>::T;
+  constexpr int HW = C::W / 2, NU = C::Sx * HW / 4 / 512;  // half a slice; its accesses per thread
+  const MatDesc* md = FINAL ? sa.desc + m : nullptr;
+  const bool tr = FINAL && md->transposed != 0, vec = FINAL && md->vec4_ok != 0;
+  auto half_rows = [&](int half) { return tr ? min(HW, sa.l - c0 - half * HW) : sa.s; };
+  auto half_cols = [&](int half) { return tr ? sa.s : min(HW, sa.l - c0 - half * HW); };
+  auto w_index = [&](int half, int r, int c) {
+    const int x0 = c0 + half * HW;
+    return tr ? view_index(*md, x0 + r, c) : view_index(*md, r, x0 + c);
+  };
+  QT wv[NU];
+  auto read_w = [&](int half) __attribute__((always_inline)) {
+    if constexpr (FK == 0) {
+      if (!vec) return;
+      const int rows = half_rows(half), cols = half_cols(half);
+#pragma unroll
+      for (int t = 0; t < NU; ++t) {
+        const int i = threadIdx.x + 512 * t, r = tr ? i / (C::Sx / 4) : i / (HW / 4);
+        const int c = (tr ? i % (C::Sx / 4) : i % (HW / 4)) * 4;
+        if (r < rows && c + 4 <= cols)
+          wv[t] = *reinterpret_cast<const QT*>(static_cast<const PT*>(md->W) + w_index(half, r, c));
+      }
+    }
+  };
+  if constexpr (FINAL) read_w(0);
+  // ---- X'^T = a X^T + X^T B over the wavefront's columns: a lane gets 4
+  // consecutive columns of one row ----------------------------------------------
+  constexpr int CBW = C::SW / 32;                          // 32-column blocks of a wavefront
+  const int w0 = wave * C::SW;
+  f32x16_t acc[CBW][RB] = {};
+  if (w0 < nv) {
+    const int G = lane >> 4, Lq = lane & 15;
+#pragma unroll
+    for (int g = 0; g < C::Sx / 16; ++g) {
+      u32x4_t bf[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        bf[i] = *reinterpret_cast<const u32x4_t*>(as + slice_a_at<RB>(32 * i + (lane & 31), 16 * g + 8 * (lane >> 5)));
+#pragma unroll
+      for (int k = 0; k < CBW; ++k) {
+        const int row = 16 * g + 8 * (G >> 1) + (Lq >> 2), col = w0 + 32 * k + 16 * (G & 1) + 4 * (Lq & 3);
+        const uint2 lo = tr_read_b64(xs + slice_at<RB>(row, col)), hi = tr_read_b64(xs + slice_at<RB>(row + 4, col));
+        const u32x4_t xf{lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+        for (int i = 0; i < RB; ++i) Mma<uint16_t>::run(xf, bf[i], acc[k][i]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < CBW; ++k)
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int row = 32 * i + (lane & 31), col = w0 + 32 * k + 8 * g + 4 * (lane >> 5);
+          char* p = xs + slice_at<RB>(row, col);
+          float e[4], v[4];
+          unpack_bf16x4(*reinterpret_cast<const uint2*>(p), e);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = osc * fmaf(sa.a, e[q], acc[k][i][4 * g + q]);
+          if constexpr (FINAL) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[k][i][4 * g + q] = v[q];
+          } else {
+            *reinterpret_cast<uint2*>(p) = pack_bf16x4(v);
+          }
+        }
+  }
+  __syncthreads();
+  if constexpr (!FINAL) {
+    slice_store<RB>(xs, nv, X, sa.L);
+    slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
+  } else {
+    // ---- the parameter (or output), half a slice at a time: O in fp32 through
+    // LDS in the parameter's layout, whole rows back, 4 elements a thread and
+    // access.  W is read ahead, 8 accesses in flight a thread: read one by one
+    // it took most of the step (96 matrices of 128 x 4096: 251 us). ----------------
+    float* const os = reinterpret_cast<float*>(smem);
+    // row-major [Sx][HW], 16-byte chunk ch of row r at ch ^ (r % 16); or [HW][Sx] (parameter l x s)
+    auto oat = [](int r, int c) { return r * HW + ((((c >> 2) ^ (r & 15)) << 2) | (c & 3)); };
+    for (int half = 0; half < 2; ++half) {
+      if (half) __syncthreads();
+      const int h0 = half * HW;
+      if (w0 >= h0 && w0 < h0 + HW && w0 < nv) {
+#pragma unroll
+        for (int k = 0; k < CBW; ++k)
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const int row = 32 * i + (lane & 31), col = w0 - h0 + 32 * k + 8 * g + 4 * (lane >> 5);
+              const f32x16_t& o = acc[k][i];
+              if (tr) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) os[(col + q) * C::Sx + row] = o[4 * g + q];
+              } else {
+                *reinterpret_cast<float4*>(os + oat(row, col)) =
+                    make_float4(o[4 * g], o[4 * g + 1], o[4 * g + 2], o[4 * g + 3]);
+              }
+            }
+      }
+      __syncthreads();
+      const int rows = half_rows(half), cols = half_cols(half);
+      if (rows > 0 && cols > 0) {
+#pragma unroll
+        for (int t = 0; t < NU; ++t) {
+          const int i = threadIdx.x + 512 * t, r = tr ? i / (C::Sx / 4) : i / (HW / 4);
+          const int c = (tr ? i % (C::Sx / 4) : i % (HW / 4)) * 4, n = min(4, cols - c);
+          if (r >= rows || n <= 0) continue;
+          const float4 ov = *reinterpret_cast<const float4*>(os + (tr ? r * C::Sx + c : oat(r, c)));
+          const float o[4] = {ov.x, ov.y, ov.z, ov.w};
+          const int64_t idx = w_index(half, r, c);
+          if (vec && n == 4) {
+            float w[4] = {0.f, 0.f, 0.f, 0.f}, v[4];
+            if (FK == 0) quad_get(wv[t], w);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = FK == 0 ? fmaf(md->decay, w[q], -md->upd_scale * o[q]) : o[q];
+            quad_put(reinterpret_cast<QT*>(static_cast<PT*>(FK == 0 ? md->W : md->out) + idx), v);
+          } else {
+            apply_tail<FK == 0 ? 0 : 1, PDT>(md, idx, o[0], o[1], o[2], o[3], n);
+          }
+        }
+      }
+      if (half == 0) read_w(1);
+    }
+  }
+}
+
+template <typename GT, int RB>
+hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb, const StepScalars& sc,
+                      const float* coeffs, int K, hipStream_t st) {
+  using C = SliceCfg<RB>;
+  SliceArgs sa{};
+  sa.desc = d_desc;
+  sa.sc = sc;
+  sa.s = cg.s; sa.l = cg.l; sa.L = cg.L;
+  sa.nsl = (cg.L + C::W - 1) / C::W;
+  sa.np = C::KSPLIT ? cg.L / C::SW : sa.nsl;
+  sa.X = static_cast<uint16_t*>(wb.X[0]);
+  sa.matX = static_cast<int64_t>(cg.S) * cg.L;
+  sa.part = static_cast<float*>(wb.X[1]);                  // over X[1], XT[0] and XT[1]
+  sa.A = static_cast<uint16_t*>(wb.A);
+  sa.norm = wb.partials;
+  const dim3 slices(static_cast<unsigned>(sa.nsl) * static_cast<unsigned>(cg.nmat));
+  const dim3 blocks(static_cast<unsigned>(C::NB) * static_cast<unsigned>(cg.nmat));
+  if (sc.momentum) {
+    hipLaunchKernelGGL((k_slice_first<GT, RB, true, false>), slices, dim3(512), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, RB, true, true>), slices, dim3(512), 0, st, sa);
+  } else {
+    hipLaunchKernelGGL((k_slice_first<GT, RB, false, false>), slices, dim3(512), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, RB, false, true>), slices, dim3(512), 0, st, sa);
+  }
+  for (int k = 0; k < K; ++k) {
+    sa.first = k == 0 ? 1 : 0;
+    sa.a = coeffs[3 * k]; sa.b = coeffs[3 * k + 1]; sa.c = coeffs[3 * k + 2];
+    hipLaunchKernelGGL((k_slice_reduce<RB>), blocks, dim3(256), 0, st, sa);
+    const bool o = sc.final_kind != 0, f32 = cg.param_dtype == DT_F32;
+    if (k + 1 < K) hipLaunchKernelGGL((k_slice_step<RB, -1, DT_BF16>), slices, dim3(512), 0, st, sa);
+    else if (!o && !f32) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_BF16>), slices, dim3(512), 0, st, sa);
+    else if (!o) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_F32>), slices, dim3(512), 0, st, sa);
+    else if (!f32) hipLaunchKernelGGL((k_slice_step<RB, 1, DT_BF16>), slices, dim3(512), 0, st, sa);
+    else hipLaunchKernelGGL((k_slice_step<RB, 1, DT_F32>), slices, dim3(512), 0, st, sa);
+  }
+  return hipGetLastError();
+}
+
+template <typename GT>
+hipError_t run_sliced_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb, const StepScalars& sc,
+                            const float* coeffs, int K, hipStream_t st, LaunchTimer* timer) {
+  Timed tm(timer, KK_SMALL, st);
+  const int Sx = cg.s <= 32 ? 32 : cg.s <= 64 ? 64 : 128;
+  const hipError_t e = Sx == 32   ? run_slices<GT, 1>(cg, d_desc, wb, sc, coeffs, K, st)
+                       : Sx == 64 ? run_slices<GT, 2>(cg, d_desc, wb, sc, coeffs, K, st)
+                                  : run_slices<GT, 4>(cg, d_desc, wb, sc, coeffs, K, st);
+  if (e != hipSuccess) return e;
+  const double nm = cg.nmat, s = cg.s, l = cg.l, L = cg.L;
+  const double gsz = sizeof(GT), psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
+  tm.done(nm * K * (4.0 * s * s * l + 2.0 * s * s * s), nm * K * (4.0 * Sx * Sx * L + 2.0 * Sx * Sx * Sx),
+          nm * s * l * (gsz + (sc.momentum ? 8.0 : 0.0) + (sc.final_kind == 0 ? 2.0 * psz : psz)));
+  return hipSuccess;
+}
+
 // Zeroes n words (the group counters before a fused launch).
 __global__ __launch_bounds__(256) void k_zero_words(unsigned* p, int n) {
   for (int i = threadIdx.x; i < n; i += 256) p[i] = 0u;
@@ -2523,6 +3076,10 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
                      const StepScalars& sc, const float* coeffs, int K, hipStream_t st,
                      LaunchTimer* timer) {
   const bool gbf = cg.grad_dtype == DT_BF16;
+  if (chunk_is_sliced(cg.s, cg.l, cg.ns_f32 != 0, K)) {
+    return gbf ? run_sliced_chunk<uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer)
+               : run_sliced_chunk<float>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+  }
   if (cg.ns_f32 && !wb.sync && chunk_on_tiles(cg.S, cg.L, K)) {
     return gbf ? run_chunk_t<uint16_t, Split3>(cg, d_desc, wb, sc, coeffs, K, st, timer)
                : run_chunk_t<float, Split3>(cg, d_desc, wb, sc, coeffs, K, st, timer);
@@ -2537,7 +3094,7 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
 
 bool group_eligible(const ChunkGeom& cg, int K) {
   return !cg.ns_f32 && K > 0 && cg.S % 256 == 0 && cg.L % 256 == 0 && tile_rows_fit(cg.S, cg.L, 2) &&
-         !chunk_is_small(cg.s, cg.l, false);
+         !chunk_is_small(cg.s, cg.l, false, K) && !chunk_is_sliced(cg.s, cg.l, false, K);
 }
 
 hipError_t run_group(const GroupMember* m, int n, const StepScalars& sc, int K, hipStream_t st,

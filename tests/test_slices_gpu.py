@@ -1,0 +1,91 @@
+"""bf16 Newton-Schulz of short sides up to 128 in column slices: the edges of
+the row blocks (32, 64, 128) and of the slices (256, 512, 1024 columns, and a
+last one of 128), both orientations, K = 1 and 5, norms that the first step's
+products cannot take (out of [2^-40, 2^40]), strided views, W rows with and
+without vector accesses, against the oracle with the gates of the bf16 path;
+and each result in a batch bit for bit the one it has alone.
+
+A wide matrix of few rows has nearly equal singular values, which take the
+roundings of X, A and B coherently: bf16 storage alone, emulated on the CPU,
+leaves 2.7e-2 on the 32 x 2100 input here.  The gate is therefore the flat
+2e-2 or 1.25 times the emulated storage error of the very input, whichever is
+more (the factor of tests/bf16_pipeline.py, for sums in another order)."""
+import numpy as np
+import pytest
+
+from oracle import muon_ref as ref
+from paper_2609_21594_amd import synth
+from tests.bf16_pipeline import FEW_SV_MARGIN, storage_error
+from tests.gpu_util import MOMENTUM_TOL, decode, o_gate, rel, require_gpu, to_bits, to_dev, to_host, tol_for, w_gate
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(16, 257), (17, 1030), (32, 2100), (33, 400), (64, 385), (64, 1100), (65, 260), (100, 700), (128, 257),
+          (128, 1152), (1300, 24), (600, 50), (520, 128), (300, 127)]
+
+
+@pytest.fixture(scope="module")
+def muon():
+    require_gpu()
+    from paper_2609_21594_amd.binding import Muon
+    m = Muon(0)
+    yield m
+    m.close()
+
+
+def rng(*key):
+    return np.random.Generator(np.random.PCG64(np.random.SeedSequence([synth.ROOT_SEED, 8600, *key])))
+
+
+@pytest.mark.parametrize("steps", [5, 1])
+@pytest.mark.parametrize("scale", [1.0, 1e14, 1e-14])
+def test_slices_match_oracle_and_do_not_depend_on_the_batch(muon, steps, scale):
+    import torch
+    G = [synth.draw(s, 1.0, "f32", rng(steps, i)) * np.float32(scale) for i, s in enumerate(SHAPES)]
+    ins = [to_dev(g, "f32") for g in G for _ in range(3)]
+    outs = [torch.full_like(t, float("nan")) for t in ins]
+    muon.orthogonalize(ins, outs, ns_steps=steps)
+    torch.cuda.synchronize()
+    for i, (s, g) in enumerate(zip(SHAPES, G)):
+        one = torch.full_like(ins[3 * i], float("nan"))
+        muon.orthogonalize([ins[3 * i]], [one], ns_steps=steps)
+        torch.cuda.synchronize()
+        for k in range(3):
+            assert np.array_equal(to_bits(outs[3 * i + k]), to_bits(one)), (s, k)
+        x = decode(g, "f32")
+        err, gate = o_gate(to_host(one), ref.orthogonalize(x, steps), "f32", "bf16", steps, G=x)
+        gate = max(gate, FEW_SV_MARGIN * storage_error(x, steps))
+        print(f"slices K={steps} x{scale:g} {s}: O err {err:.2e}", flush=True)
+        assert err <= gate, (s, err, gate)
+
+
+@pytest.mark.parametrize("pdt,gdt", [("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")])
+def test_slices_step_matches_oracle(muon, pdt, gdt):
+    import torch
+    hp = ref.MuonHParams(lr=0.02, beta=0.95, weight_decay=0.1, nesterov=True)
+    Ws = [synth.draw(s, 0.02, pdt, rng(30, i, 0)) for i, s in enumerate(SHAPES)]
+    gs = [synth.draw(s, 1e-3, gdt, rng(30, i, 1)) for i, s in enumerate(SHAPES)]
+    bs = [synth.draw(s, 1e-3, "f32", rng(30, i, 2)) for i, s in enumerate(SHAPES)]
+    dW, dg, db = [to_dev(w, pdt) for w in Ws], [to_dev(g, gdt) for g in gs], [to_dev(b, "f32") for b in bs]
+
+    def wide(t):  # the same matrix as the left columns of a wider buffer
+        big = torch.full((t.shape[0], t.shape[1] + 24), 7.0, dtype=t.dtype, device=t.device)
+        big[:, :t.shape[1]] = t
+        return big, big[:, :t.shape[1]]
+
+    vW, vg, vb = [[wide(t) for t in ts] for ts in (dW, dg, db)]
+    kw = dict(lr=hp.lr, beta=hp.beta, weight_decay=hp.weight_decay)
+    muon.step(dW, dg, db, **kw)
+    muon.step([v for _, v in vW], [v for _, v in vg], [v for _, v in vb], **kw)
+    torch.cuda.synchronize()
+    for s, W, g, b, w_dev, b_dev, (bigw, w_view), (bigb, b_view) in zip(SHAPES, Ws, gs, bs, dW, db, vW, vb):
+        W0 = decode(W, pdt)
+        r = ref.muon_step_matrix(W0, decode(g, gdt), np.asarray(b, np.float64), hp)
+        err, rho = w_gate(to_host(w_dev), r.W_new, W0, pdt)
+        print(f"slices step {pdt}/{gdt} {s}: W err {err:.2e} (rho {rho:.1e})", flush=True)
+        u = 0.05 * decode(g, gdt) + 0.95 * r.buf_new
+        assert err <= max(tol_for("bf16", s), FEW_SV_MARGIN * storage_error(u)) + rho, (s, err, rho)
+        assert rel(to_host(b_dev), r.buf_new) <= MOMENTUM_TOL, s
+        assert np.array_equal(to_bits(w_view.contiguous()), to_bits(w_dev)), s
+        assert np.array_equal(to_bits(b_view.contiguous()), to_bits(b_dev)), s
+        assert bool((bigw[:, s[1]:] == 7.0).all()) and bool((bigb[:, s[1]:] == 7.0).all()), s
