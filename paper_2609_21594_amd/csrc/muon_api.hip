@@ -905,6 +905,12 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
     g.ns_f32 = ns_f32 ? 1 : 0;
     g.grad_dtype = c.gdt == MUON_BF16 ? muon::DT_BF16 : muon::DT_F32;
     g.param_dtype = c.pdt == MUON_BF16 ? muon::DT_BF16 : muon::DT_F32;
+    g.w_rows16 = c.pdt == MUON_BF16;
+    for (int64_t p = c.first; p < c.first + c.count && g.w_rows16; ++p) {
+      const Item& it = items[size_t(plan.order[size_t(p)])];
+      g.w_rows16 = it.W && (reinterpret_cast<uintptr_t>(it.W) & 15) == 0 && it.cols % 8 == 0 && it.ld % 8 == 0 &&
+                   it.rb >= it.rows && it.ld * 2 < muon::kTileMaxRowBytes;
+    }
     return g;
   };
   auto steps_of = [&](const Chunk& c) { return int(tables[size_t(c.cset)].size() / 3); };

@@ -61,6 +61,8 @@ struct ChunkGeom {
   int32_t ns_f32;       // 1: fp32 NS arithmetic, 0: bf16 operands
   int32_t grad_dtype;   // DType of desc.g
   int32_t param_dtype;  // DType of desc.W / desc.out
+  int32_t w_rows16;     // every W is one block of rows that start 16-byte aligned, cols % 8 == 0, ld within
+                        // kTileMaxRowBytes: a bf16 W can be staged as whole rows by direct-to-LDS loads
 };
 
 // Chunk workspace: four X buffers (X, X^T and their successors), A, B, and

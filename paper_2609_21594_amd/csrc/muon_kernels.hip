@@ -429,7 +429,8 @@ __global__ __launch_bounds__(256) void k_rescale(const MatDesc* __restrict__ des
 // ---------------------------------------------------------------------------
 enum Epi : int { EPI_GRAM = 0, EPI_POLY = 1, EPI_UPDATE = 2, EPI_FINAL = 3,
                  // final-step variants of the 256-tile kernel: update W / write out, bf16 / fp32
-                 EPI_FINAL_W_BF16 = 4, EPI_FINAL_W_F32 = 5, EPI_FINAL_O_BF16 = 6, EPI_FINAL_O_F32 = 7 };
+                 EPI_FINAL_W_BF16 = 4, EPI_FINAL_W_F32 = 5, EPI_FINAL_O_BF16 = 6, EPI_FINAL_O_F32 = 7,
+                 EPI_FINAL_W_BF16_ANY = 8 };  // 4: W rows of 16-byte accesses (w_rows16); 8: any
 
 struct GemmArgs {
   const char* P;   int64_t p_mat;  int32_t ldp;   // bytes
@@ -442,7 +443,7 @@ struct GemmArgs {
   char* CT;        int64_t ct_mat; int32_t ldct;  // output, transposed orientation
   float alpha, beta;
   const MatDesc* desc;
-  int32_t final_kind, param_dtype;
+  int32_t final_kind, param_dtype, w_rows16;
   int32_t s, l;
   int32_t total_tiles;                           // tiles_per_mat * matrices
   // operand storage, 256 x 256 kernel only: 0 row-major over K; 1 symmetric,
@@ -732,54 +733,93 @@ __device__ __forceinline__ void unpack_bf16x4(uint2 p, float v[4]) {
   v[2] = __uint_as_float(p.y << 16); v[3] = __uint_as_float(p.y & 0xffff0000u);
 }
 
-// Ragged-edge tail of apply4 (kept out of line: it is rare, and keeping the
-// epilogue small lets the compiler hold every accumulator in registers).
-template <int FK, int PDT>
-__device__ __noinline__ void apply_tail(const MatDesc* md, int64_t idx, float o0, float o1, float o2,
-                                        float o3, int n) {
-  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
-  PT* dst = static_cast<PT*>(FK == 0 ? md->W : md->out);
-  const float o[4] = {o0, o1, o2, o3};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (q < n) {
-      const float r = FK == 0 ? fmaf(md->decay, to_f32<PT>(dst[idx + q]), -md->upd_scale * o[q]) : o[q];
-      dst[idx + q] = from_f32<PT>(r);
-    }
-  }
+// The matrix that a last step writes, in registers: read through the
+// descriptor's pointer, its fields would be loaded again after every store.
+struct WView {
+  void* dst;                 // W, or out
+  int64_t ld, bstride;
+  int32_t rb, rows;
+  float decay, upd;
+  bool vec8, vec4;           // 8 (4) consecutive elements at multiples of 8 (4) columns are aligned for vector accesses
+};
+template <int FK>
+__device__ __forceinline__ WView w_view(const MatDesc* md) {
+  WView v;
+  v.dst = FK == 0 ? md->W : md->out;
+  v.ld = md->ld; v.bstride = md->bstride;
+  v.rb = md->rb; v.rows = md->rows;
+  v.decay = md->decay; v.upd = md->upd_scale;
+  v.vec4 = md->vec4_ok != 0;
+  v.vec8 = v.vec4 && md->cols % 8 == 0 && md->ld % 8 == 0 && (md->rb >= md->rows || md->bstride % 8 == 0);
+  return v;
+}
+__device__ __forceinline__ int64_t w_index(const WView& v, int32_t i, int32_t j) {
+  if (v.rb >= v.rows) return i * v.ld + j;
+  const int32_t q = i / v.rb;
+  return q * v.bstride + static_cast<int64_t>(i - q * v.rb) * v.ld + j;
 }
 
-// W[idx .. idx+3] = decay*W - upd*o (FK = 0) or out[idx ..] = o (FK = 1), 4
-// consecutive elements of dtype PDT: one vector access when `vec`, else
-// element by element up to `n`.  The parameter is read and written with
-// ordinary (cached) accesses, each load right before its store: measured
-// faster than streaming accesses or loads hoisted ahead of the stores.
-template <int FK, int PDT>
-__device__ __forceinline__ void apply4(const MatDesc* md, int64_t idx, const float o[4], bool vec, int n) {
-  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
-  PT* dst = static_cast<PT*>(FK == 0 ? md->W : md->out);
-  const float decay = md->decay, upd = md->upd_scale;
-  if (vec) {
-    float w[4] = {0.f, 0.f, 0.f, 0.f}, r[4];
-    if constexpr (PDT == DT_BF16) {
-      uint2* p = reinterpret_cast<uint2*>(dst + idx);
-      if (FK == 0) unpack_bf16x4(*p, w);
+// W[idx ..] = decay*W - upd*o (FK = 0) or out[idx ..] = o (FK = 1) for 8
+// consecutive elements, of which n are inside the matrix; `w` holds W's when
+// vec8 and n = 8 (read ahead by read8).
+template <typename PT>
+struct Raw8 { u32x4_t q[sizeof(PT) / 2]; };
+template <typename PT>
+__device__ __forceinline__ Raw8<PT> read8(const WView& v, int64_t idx) {
+  const u32x4_t* p = reinterpret_cast<const u32x4_t*>(static_cast<const PT*>(v.dst) + idx);
+  Raw8<PT> r;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = FK == 0 ? fmaf(decay, w[q], -upd * o[q]) : o[q];
-      *p = pack_bf16x4(r);
-    } else {
-      float4* p = reinterpret_cast<float4*>(dst + idx);
-      if (FK == 0) {
-        const float4 raw = *p;
-        w[0] = raw.x; w[1] = raw.y; w[2] = raw.z; w[3] = raw.w;
+  for (int h = 0; h < static_cast<int>(sizeof(PT)) / 2; ++h) r.q[h] = p[h];
+  return r;
+}
+template <int FK, typename PT>
+__device__ __forceinline__ void apply8(const WView& v, int64_t idx, float o[8], int n, const Raw8<PT>& w) {
+  PT* dst = static_cast<PT*>(v.dst) + idx;
+  if (v.vec8 && n == 8) {
+    if constexpr (FK == 0) {
+      float wf[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if constexpr (sizeof(PT) == 2) {
+          const uint32_t d = w.q[0][q / 2];
+          wf[q] = __uint_as_float(q % 2 ? d & 0xffff0000u : d << 16);
+        } else {
+          wf[q] = __uint_as_float(w.q[q / 4][q % 4]);
+        }
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = FK == 0 ? fmaf(decay, w[q], -upd * o[q]) : o[q];
-      *p = make_float4(r[0], r[1], r[2], r[3]);
+      for (int q = 0; q < 8; ++q) o[q] = fmaf(v.decay, wf[q], -v.upd * o[q]);
     }
+    store8(dst, 0, o);
     return;
   }
-  apply_tail<FK, PDT>(md, idx, o[0], o[1], o[2], o[3], n);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int m = min(4, n - 4 * h);
+    if (m <= 0) return;
+    if (v.vec4 && m == 4) {
+      float t[4];
+      if constexpr (sizeof(PT) == 2) {
+        uint2* p = reinterpret_cast<uint2*>(dst + 4 * h);
+        if (FK == 0) unpack_bf16x4(*p, t);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] = FK == 0 ? fmaf(v.decay, t[q], -v.upd * o[4 * h + q]) : o[4 * h + q];
+        *p = pack_bf16x4(t);
+      } else {
+        float4* p = reinterpret_cast<float4*>(dst + 4 * h);
+        if (FK == 0) { const float4 r = *p; t[0] = r.x; t[1] = r.y; t[2] = r.z; t[3] = r.w; }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] = FK == 0 ? fmaf(v.decay, t[q], -v.upd * o[4 * h + q]) : o[4 * h + q];
+        *p = make_float4(t[0], t[1], t[2], t[3]);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q < m)
+          dst[4 * h + q] = from_f32<PT>(FK == 0 ? fmaf(v.decay, to_f32<PT>(dst[4 * h + q]), -v.upd * o[4 * h + q])
+                                                : o[4 * h + q]);
+    }
+  }
 }
 
 // Byte offset of an LDS object.
@@ -906,6 +946,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   constexpr bool FINAL = EPI >= EPI_FINAL_W_BF16;
   constexpr int FK = (EPI == EPI_FINAL_O_BF16 || EPI == EPI_FINAL_O_F32) ? 1 : 0;
   constexpr int PDT = (EPI == EPI_FINAL_W_F32 || EPI == EPI_FINAL_O_F32) ? DT_F32 : DT_BF16;
+  static_assert(!FINAL || FK == 1 || EPI == EPI_FINAL_W_BF16 || EPI == EPI_FINAL_W_F32 || EPI == EPI_FINAL_W_BF16_ANY,
+                "last-step variants");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -1378,7 +1420,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const bool pair_mirror = BM == 128 && ga.syrk && (bm & 1) == 0 && bn == bm + 1;
   const MatDesc* md = FINAL ? ga.desc + mat : nullptr;
   const bool tr = FINAL ? md->transposed != 0 : false;
-  const bool v4 = FINAL ? md->vec4_ok != 0 : false;
+  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
+  WView wv{};
+  if constexpr (FINAL) wv = w_view<FK>(md);
   const int q4 = lane & 3;
   const int row_base = bm * BM + wm * (BM / WM) + 4 * fsel;
   const int col_base = bn * BN + wn * (BN / WN) + frow;
@@ -1402,11 +1446,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // bytes) over all banks.  At the matrix's edge the block has wrv rows and
   // wcv columns (a multiple of 8): loads past them repeat the last row or
   // chunk, and only the block is written back.
-  bool stage_w = false;
+  constexpr bool stage_w = EPI == EPI_FINAL_W_BF16;
   const int wr0 = tr ? bn * BN : bm * BM, wc0 = tr ? bm * BM : bn * BN;  // W block origin
   int wrv = 0, wcv = 0;
-  if constexpr (FINAL && FK == 0 && PDT == DT_BF16) {
-    stage_w = v4 && md->cols % 8 == 0 && md->ld % 8 == 0 && md->rb >= md->rows && md->ld * 2 < kTileMaxRowBytes;
+  if constexpr (stage_w) {
     wrv = min(BM, md->rows - wr0);
     wcv = min(BM, md->cols - wc0);
   }
@@ -1416,11 +1459,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   };
   // (every wave finished its operand-slab reads before the last slab's
   // barrier, so the staging area, which overlaps the slabs, is free)
-  if (stage_w) {
+  if constexpr (stage_w) {
     constexpr int KW = BM * BN * 2 / 1024 / NW;   // load instructions per wave
     static_assert(KW * NW * 1024 == BM * BN * 2, "W tile: whole instructions per wave");
-    const char* wb = static_cast<const char*>(md->W) + (static_cast<int64_t>(wr0) * md->ld + wc0) * 2;
-    const uint32_t ldw = static_cast<uint32_t>(md->ld) * 2;
+    const char* wb = static_cast<const char*>(wv.dst) + (static_cast<int64_t>(wr0) * wv.ld + wc0) * 2;
+    const uint32_t ldw = static_cast<uint32_t>(wv.ld) * 2;
     const uint32_t lds0 = lds_offset(smem);
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
@@ -1434,16 +1477,15 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // compiler keeps every value in registers; written at function scope it
   // spilled.)
   auto blocks = [&](float scale) {
-    if (stage_w) {  // the W block has landed in LDS
+    if constexpr (stage_w) {  // the W block has landed in LDS
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
     }
-    const float decay = FINAL ? md->decay : 0.f, upd = FINAL ? md->upd_scale : 0.f;
     auto w_update = [&](char* p, const float o[4]) {  // 4 staged W values, in place
       float w[4], r[4];
       unpack_bf16x4(*reinterpret_cast<const uint2*>(p), w);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = fmaf(decay, w[q], -upd * o[q]);
+      for (int q = 0; q < 4; ++q) r[q] = fmaf(wv.decay, w[q], -wv.upd * o[q]);
       *reinterpret_cast<uint2*>(p) = pack_bf16x4(r);
     };
     static_for<BI>([&](auto I) {
@@ -1466,39 +1508,98 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[i][j][4 * g + q] = v[q] - e[q];
               }
-            } else if (stage_w) {      // parameter is l x s: elements (col, row0 .. row0 + 3)
+            } else {                   // parameter is l x s: elements (col, row0 .. row0 + 3)
               w_update(smem + wpos(col - wr0, (row0 - wc0) * 2), v);
-            } else if (col < ga.l) {
-              const int n = min(4, ga.s - row0);
-              if (n > 0)
-                apply4<FK, PDT>(md, view_index(*md, col, row0), v, v4 && n == 4, n);
             }
           } else {             // parameter is s x l: elements (row0 + q4, c0 .. c0 + 3)
             quad_transpose(v);
-            const int row = row0 + q4;
-            if (stage_w) {
-              w_update(smem + wpos(row - wr0, (c0 - wc0) * 2), v);
-            } else if (row < ga.s) {
-              const int n = min(4, ga.l - c0);
-              if (n > 0)
-                apply4<FK, PDT>(md, view_index(*md, row, c0), v, v4 && n == 4, n);
-            }
+            w_update(smem + wpos(row0 + q4 - wr0, (c0 - wc0) * 2), v);
           }
         });
       });
     });
   };
-  if constexpr (FINAL) blocks(SPLIT ? 1.f : osc);
-  if (stage_w) {
+  if constexpr (stage_w) {
+    blocks(SPLIT ? 1.f : osc);
     __syncthreads();
     // updated W rows -> W, 16 bytes a thread
     for (int idx = threadIdx.x; idx < BM * TRC; idx += 64 * NW) {
       const int r = idx / TRC, ch = idx % TRC;
       if (r >= wrv || ch * 8 >= wcv) continue;
-      *reinterpret_cast<u32x4_t*>(static_cast<char*>(md->W) + (static_cast<int64_t>(wr0 + r) * md->ld + wc0) * 2 +
+      *reinterpret_cast<u32x4_t*>(static_cast<char*>(wv.dst) + (static_cast<int64_t>(wr0 + r) * wv.ld + wc0) * 2 +
                                   ch * 16) = *reinterpret_cast<const u32x4_t*>(smem + wpos(r, ch * 16));
     }
     __syncthreads();  // the next tile's loads overwrite the staging area
+  }
+  if constexpr (FINAL && !stage_w) {
+    // Outputs, fp32 parameters and parameters without 16-byte rows: O goes
+    // through LDS in fp32, half a tile at a time (the rows of the wavefronts
+    // wm = half), in the parameter's layout, and leaves as whole rows, 8
+    // elements a thread and unit, W read up to 4 units ahead.  Straight from
+    // the registers (16-byte pieces of 32 rows, or 64 to 128 bytes of 8) the
+    // last step of 72 fp32 parameters of hidden 768 took 325 us a launch, this
+    // way 177; of 512 mixed bf16 outputs 2.60 and 1.5 ms in all.
+    constexpr int HR = BM / WM;                            // rows of X in a half
+    constexpr int NUN = HR * BN / 8 / (64 * NW);           // units per thread
+    float* const os = reinterpret_cast<float*>(smem);
+    static_assert(HR * BN * 4 <= BN * (BM * 2 + 8) || HR * BN * 4 <= Cfg::LDS, "half a tile in fp32");
+    // element (row, col) of the half: row-major, or (parameter l x s) by
+    // columns with 16-byte chunk k of column c at k ^ (c % 16)
+    auto oat = [](int r, int c) { return r * BN + c; };
+    auto oat_t = [](int c, int r) { return c * HR + ((((r >> 2) ^ (c & 15)) << 2) | (r & 3)); };
+    const int ush = 31 - __builtin_clz((tr ? HR : BN) / 8);  // units per row: a power of two
+#pragma unroll 1
+    for (int half = 0; half < WM; ++half) {
+      if (wm == half) {
+        const float sc = SPLIT ? 1.f : osc;
+        static_for<BI>([&](auto I) {
+          static_for<BJ>([&](auto J) {
+            static_for<4>([&](auto G) {
+              constexpr int i = decltype(I)::value, j = decltype(J)::value, g = decltype(G)::value;
+              const int r = i * 32 + 8 * g + 4 * fsel, c = wn * (BN / WN) + j * 32 + frow;
+              const f32x16_t& o = acc[i][j];
+              if (tr) {
+                *reinterpret_cast<float4*>(os + oat_t(c, r)) =
+                    make_float4(sc * o[4 * g], sc * o[4 * g + 1], sc * o[4 * g + 2], sc * o[4 * g + 3]);
+              } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) os[oat(r + q, c)] = sc * o[4 * g + q];
+              }
+            });
+          });
+        });
+      }
+      __syncthreads();
+      const int r0 = bm * BM + half * HR, x0 = bn * BN;    // the half's origin in X
+      const int wr = tr ? x0 : r0, wc = tr ? r0 : x0;      // and in the parameter
+      const int rows = tr ? min(BN, ga.l - x0) : min(HR, ga.s - r0), cols = tr ? min(HR, ga.s - r0) : min(BN, ga.l - x0);
+      constexpr int AH = 4;
+#pragma unroll 1
+      for (int t0 = 0; t0 < NUN; t0 += AH) {
+        Raw8<PT> w[AH];
+        int r[AH], c[AH];
+#pragma unroll
+        for (int t = 0; t < AH; ++t) {
+          const int u = threadIdx.x + 64 * NW * (t0 + t);
+          r[t] = u >> ush;
+          c[t] = (u & ((1 << ush) - 1)) * 8;
+          if (FK == 0 && wv.vec8 && r[t] < rows && c[t] + 8 <= cols) w[t] = read8<PT>(wv, w_index(wv, wr + r[t], wc + c[t]));
+        }
+#pragma unroll
+        for (int t = 0; t < AH; ++t) {
+          const int n = min(8, cols - c[t]);
+          if (r[t] >= rows || n <= 0) continue;
+          float o[8];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float4 v = *reinterpret_cast<const float4*>(os + (tr ? oat_t(r[t], c[t] + 4 * h) : oat(r[t], c[t] + 4 * h)));
+            o[4 * h] = v.x; o[4 * h + 1] = v.y; o[4 * h + 2] = v.z; o[4 * h + 3] = v.w;
+          }
+          apply8<FK, PT>(wv, w_index(wv, wr + r[t], wc + c[t]), o, n, w[t]);
+        }
+      }
+      __syncthreads();  // the next half, or the next tile's loads, overwrite the staging area
+    }
   }
   if constexpr (stage_n) {
 #pragma unroll 1
@@ -1722,7 +1823,8 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
     case EPI_UPDATE: hipLaunchKernelGGL((k_gemm_tile<EPI_UPDATE, Cfg, SPLIT>), grid, block, 0, st, ga); break;
     default: {
       const bool o = ga.final_kind != 0, f32 = ga.param_dtype == DT_F32;
-      if (!o && !f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_BF16, Cfg, SPLIT>), grid, block, 0, st, ga);
+      if (!o && !f32 && ga.w_rows16) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_BF16, Cfg, SPLIT>), grid, block, 0, st, ga);
+      else if (!o && !f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_BF16_ANY, Cfg, SPLIT>), grid, block, 0, st, ga);
       else if (!o) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_W_F32, Cfg, SPLIT>), grid, block, 0, st, ga);
       else if (!f32) hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_BF16, Cfg, SPLIT>), grid, block, 0, st, ga);
       else hipLaunchKernelGGL((k_gemm_tile<EPI_FINAL_O_F32, Cfg, SPLIT>), grid, block, 0, st, ga);
@@ -1741,6 +1843,7 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   GroupArgs gr{};
   gr.start[0] = 0;
+  bool rows16 = true;
   for (int i = 0; i < n; ++i) {
     GemmArgs ga = gas[i];
     const int c = gr.n;
@@ -1761,6 +1864,7 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
     }
     if (c > 0 && (ga.final_kind != gr.ga[0].final_kind || ga.param_dtype != gr.ga[0].param_dtype))
       return hipErrorInvalidValue;
+    rows16 = rows16 && ga.w_rows16;
     gr.ga[c] = ga;
     gr.start[c + 1] = gr.start[c] + ga.total_tiles;
     gr.n = c + 1;
@@ -1775,7 +1879,8 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
     case EPI_UPDATE: hipLaunchKernelGGL((k_gemm_group<EPI_UPDATE, Cfg>), grid, block, 0, st, gr); break;
     default: {
       const bool o = gr.ga[0].final_kind != 0, f32 = gr.ga[0].param_dtype == DT_F32;
-      if (!o && !f32) hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_W_BF16, Cfg>), grid, block, 0, st, gr);
+      if (!o && !f32 && rows16) hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_W_BF16, Cfg>), grid, block, 0, st, gr);
+      else if (!o && !f32) hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_W_BF16_ANY, Cfg>), grid, block, 0, st, gr);
       else if (!o) hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_W_F32, Cfg>), grid, block, 0, st, gr);
       else if (!f32) hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_O_BF16, Cfg>), grid, block, 0, st, gr);
       else hipLaunchKernelGGL((k_gemm_group<EPI_FINAL_O_F32, Cfg>), grid, block, 0, st, gr);
@@ -2287,6 +2392,8 @@ struct SliceArgs {
   StepScalars sc;
   int32_t s, l, L;
   int32_t nsl, np;           // slices and Gram partials per matrix
+  int32_t nmat;
+  int32_t nnorm;             // slices of the prologue (square sums) per matrix
   int32_t first;
   uint16_t* X;               // per matrix: S x L (matX elements), rows of stride L
   int64_t matX;
@@ -2296,10 +2403,13 @@ struct SliceArgs {
   float a, b, c;
 };
 
-template <int RB>
+// NW: wavefronts of the workgroup, 8, or 4 in the last step: its slices are
+// half as wide (no Gram partial depends on them), so that two workgroups fit a
+// compute unit and one computes while the other waits for W.
+template <int RB, int NW = 8>
 struct SliceCfg {
-  static constexpr int Sx = 32 * RB, W = 1024 / RB, PITCH = 2 * W;   // PITCH: bytes of a slice row
-  static constexpr int SW = W / 8;                                   // columns of a wavefront
+  static constexpr int Sx = 32 * RB, SW = 128 / RB;                  // SW: columns of a wavefront
+  static constexpr int W = NW * SW, PITCH = 2 * W;                   // PITCH: bytes of a slice row
   static constexpr int NB = RB * (RB + 1) / 2;                       // upper 32 x 32 blocks of A
   static constexpr int AP = 2 * Sx, ABYTES = Sx * AP;                // A row, A
   static constexpr bool KSPLIT = RB < 4;  // Gram: each wavefront its own columns (a partial each), else output blocks
@@ -2307,14 +2417,32 @@ struct SliceCfg {
 };
 __device__ __forceinline__ int slice_key(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 // LDS byte of column col (in elements) of slice row r
-template <int RB>
+template <int RB, int NW = 8>
 __device__ __forceinline__ int slice_at(int r, int col) {
-  return r * SliceCfg<RB>::PITCH + (((col >> 3) ^ slice_key(r)) << 4) + (col & 7) * 2;
+  return r * SliceCfg<RB, NW>::PITCH + (((col >> 3) ^ slice_key(r)) << 4) + (col & 7) * 2;
 }
 // LDS byte of element (r, c) of A or B
 template <int RB>
 __device__ __forceinline__ int slice_a_at(int r, int c) {
   return r * SliceCfg<RB>::AP + (((c >> 3) ^ (slice_key(r) & (4 * RB - 1))) << 4) + (c & 7) * 2;
+}
+
+// Workgroup b's matrix and slice.  Workgroup b runs on XCD b % 8: from 8
+// matrices on, a matrix's slices share an XCD, whose L2 then holds its A once,
+// and that XCD sees every column range (dealt out one by one, XCD x would see
+// columns of the slices x, x + 8, .. only, which at power-of-two row strides
+// are few of its L2 channels).  With fewer, a matrix's slices spread over all.
+__device__ __forceinline__ bool slice_of(const SliceArgs& sa, int& m, int& j) {
+  const int b = blockIdx.x;
+  if (sa.nmat < 8) {
+    m = b / sa.nsl;
+    j = b - m * sa.nsl;
+    return true;
+  }
+  const int q = b >> 3, mq = q / sa.nsl;
+  m = mq * 8 + (b & 7);
+  j = q - mq * sa.nsl;
+  return m < sa.nmat;
 }
 
 // r = 1 / (||u|| + eps) from a matrix's slice sums, by all 256 or 512 threads
@@ -2402,11 +2530,12 @@ __global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
   using C = SliceCfg<RB>;
   __shared__ __attribute__((aligned(16))) char xs[C::Sx * C::PITCH];
   __shared__ double red[8];
-  const int m = blockIdx.x / sa.nsl, j = blockIdx.x % sa.nsl;
+  int m, j;
+  if (!slice_of(sa, m, j)) return;
   const int c0 = j * C::W, nv = min(C::W, sa.L - c0);
   float s1 = 1.f, s2 = 1.f;
   if (RESCALE) {
-    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nnorm, sa.nnorm, sa.sc.eps, red);
     if (slice_folds(r)) return;
     split_scale(r, s1, s2);
   }
@@ -2483,7 +2612,7 @@ __global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < 8; ++w) t += red[w];
-    sa.norm[static_cast<int64_t>(m) * sa.nsl + j] = t;
+    sa.norm[static_cast<int64_t>(m) * sa.nnorm + j] = t;
   }
   slice_store<RB>(xs, nv, sa.X + m * sa.matX + c0, sa.L);
   slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
@@ -2498,7 +2627,7 @@ __global__ __launch_bounds__(256) void k_slice_reduce(SliceArgs sa) {
   const int m = blockIdx.x / C::NB, nb = blockIdx.x % C::NB;
   float scale = 1.f;
   if (sa.first) {
-    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nnorm, sa.nnorm, sa.sc.eps, red);
     const float rf = slice_folds(r) ? static_cast<float>(r) : 1.f;
     scale = rf * rf;
   }
@@ -2533,26 +2662,21 @@ __global__ __launch_bounds__(256) void k_slice_reduce(SliceArgs sa) {
   }
 }
 
-// 4 elements of the parameter as they lie in memory, and as fp32.
-template <int PDT> struct Quad { using T = uint2; };
-template <> struct Quad<DT_F32> { using T = float4; };
-__device__ __forceinline__ void quad_get(uint2 t, float v[4]) { unpack_bf16x4(t, v); }
-__device__ __forceinline__ void quad_get(float4 t, float v[4]) { v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
-__device__ __forceinline__ void quad_put(uint2* p, const float v[4]) { *p = pack_bf16x4(v); }
-__device__ __forceinline__ void quad_put(float4* p, const float v[4]) { *p = make_float4(v[0], v[1], v[2], v[3]); }
-
 // FK: -1 a middle step; 0 the last, updating W; 1 the last, writing out (both
 // of dtype PDT).
 template <int RB, int FK, int PDT>
-__global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
-  using C = SliceCfg<RB>;
+__global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs sa) {
   constexpr bool FINAL = FK >= 0;
-  constexpr int XB = C::Sx * C::PITCH;                     // 64 KB
-  __shared__ __attribute__((aligned(1024))) char smem[XB + C::ABYTES];
+  constexpr int NW = FINAL ? 4 : 8;
+  using C = SliceCfg<RB, NW>;
+  constexpr int XB = C::Sx * C::PITCH;                     // 8 KB a wavefront
+  constexpr int OB = FINAL ? C::Sx * C::W * 4 : 0;         // O of the slice in fp32, over both
+  __shared__ __attribute__((aligned(1024))) char smem[OB > XB + C::ABYTES ? OB : XB + C::ABYTES];
   __shared__ double red[4];
   char* const xs = smem;
   char* const as = smem + XB;
-  const int m = blockIdx.x / sa.nsl, j = blockIdx.x % sa.nsl;
+  int m, j;
+  if (!slice_of(sa, m, j)) return;
   const int c0 = j * C::W, nv = min(C::W, sa.L - c0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lds0 = lds_offset(smem);
@@ -2560,15 +2684,45 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
   const char* const Ag = reinterpret_cast<const char*>(sa.A + static_cast<int64_t>(m) * C::Sx * C::Sx);
   float osc = 1.f;
   if (sa.first) {
-    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nsl, sa.nsl, sa.sc.eps, red);
+    const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nnorm, sa.nnorm, sa.sc.eps, red);
     if (slice_folds(r)) osc = static_cast<float>(r);
   }
+  // the last step: the slice's part of the matrix in the parameter's layout, 8
+  // elements a thread and unit, and its W values, read ahead.  (96 matrices of
+  // 128 x 4096: 80 us; 147 with the descriptor's fields read where they are
+  // used, 216 with 4 elements a unit, 251 with W read where it is used.)
+  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
+  constexpr int NU = FINAL ? C::Sx * C::W / 8 / (64 * NW) : 1;   // units per thread
+  const MatDesc* md = FINAL ? sa.desc + m : nullptr;
+  const bool tr = FINAL && md->transposed != 0;
+  WView w{};
+  if constexpr (FINAL) w = w_view<FK == 0 ? 0 : 1>(md);
+  const int nx = min(C::W, sa.l - c0), wrows = tr ? nx : sa.s, wcols = tr ? sa.s : nx;
+  const int ush = 31 - __builtin_clz((tr ? C::Sx : C::W) / 8);   // units per row: a power of two
+  auto w_unit = [&](int t, int& r, int& c) {
+    const int i = threadIdx.x + 64 * NW * t;
+    r = i >> ush;
+    c = (i & ((1 << ush) - 1)) * 8;
+  };
+  auto w_at = [&](int r, int c) { return tr ? w_index(w, c0 + r, c) : w_index(w, r, c0 + c); };
+  Raw8<PT> wv[NU];
+  auto read_w = [&]() __attribute__((always_inline)) {
+    if constexpr (FK == 0) {
+      if (!w.vec8) return;
+#pragma unroll
+      for (int t = 0; t < NU; ++t) {
+        int r, c;
+        w_unit(t, r, c);
+        if (r < wrows && c + 8 <= wcols) wv[t] = read8<PT>(w, w_at(r, c));
+      }
+    }
+  };
   // ---- A and the slice into LDS: 1 KB per wavefront instruction, lane i the
   // 16 bytes at 16 i; each lane fetches the chunk that belongs there ----------
   constexpr int ACH = C::AP / 16, AI = C::ABYTES / 1024;   // chunks of an A row; instructions
 #pragma unroll
-  for (int k = 0; k < (AI + 7) / 8; ++k) {
-    const int t = wave + 8 * k;
+  for (int k = 0; k < (AI + NW - 1) / NW; ++k) {
+    const int t = wave + NW * k;
     if (t < AI) {
       const int p = t * 64 + lane, r = p / ACH;
       load_lds16(Ag, static_cast<uint32_t>(r * C::AP + ((p % ACH) ^ (slice_key(r) & (ACH - 1))) * 16),
@@ -2578,17 +2732,22 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
   constexpr int XCH = C::PITCH / 16;                       // chunks of a slice row
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const int t = wave + 8 * k, p = t * 64 + lane, r = p / XCH;
+    const int t = wave + NW * k, p = t * 64 + lane, r = p / XCH;
     int ch = (p % XCH) ^ slice_key(r);
     if (8 * ch >= nv) ch &= 15;                            // past the matrix: any chunk of the row (not used)
     load_lds16(reinterpret_cast<const char*>(X), static_cast<uint32_t>(r) * static_cast<uint32_t>(sa.L * 2) + ch * 16,
                lds0 + t * 1024);
   }
-  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");         // A has landed, the slice may not
+  if constexpr (FINAL) {
+    read_w();                                              // in flight together with A and the slice
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // A has landed, the slice may not
+  }
   __syncthreads();
   // ---- B = b A + c A A, in place --------------------------------------------
-  constexpr int PB = RB == 4 ? 2 : 1;                      // 32 x 32 blocks of B per wavefront
-  const int pi = RB == 4 ? 2 * (wave >> 2) : wave / RB, pj = RB == 4 ? (wave & 3) : wave % RB;
+  constexpr int PB = RB == 4 ? 16 / NW : 1;                // 32 x 32 blocks of B per wavefront
+  const int pi = RB == 4 ? PB * (wave >> 2) : wave / RB, pj = RB == 4 ? (wave & 3) : wave % RB;
   const bool pact = RB == 4 || wave < RB * RB;
   uint2 bh[PB][4];
   if (pact) {
@@ -2627,34 +2786,6 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the slice has landed
   __syncthreads();
-  // the last step: this half's part of the matrix in the parameter's layout,
-  // and its W values, read ahead
-  using PT = typename std::conditional<PDT == DT_BF16, uint16_t, float>::type;
-  using QT = typename Quad<PDT>::T;
-  constexpr int HW = C::W / 2, NU = C::Sx * HW / 4 / 512;  // half a slice; its accesses per thread
-  const MatDesc* md = FINAL ? sa.desc + m : nullptr;
-  const bool tr = FINAL && md->transposed != 0, vec = FINAL && md->vec4_ok != 0;
-  auto half_rows = [&](int half) { return tr ? min(HW, sa.l - c0 - half * HW) : sa.s; };
-  auto half_cols = [&](int half) { return tr ? sa.s : min(HW, sa.l - c0 - half * HW); };
-  auto w_index = [&](int half, int r, int c) {
-    const int x0 = c0 + half * HW;
-    return tr ? view_index(*md, x0 + r, c) : view_index(*md, r, x0 + c);
-  };
-  QT wv[NU];
-  auto read_w = [&](int half) __attribute__((always_inline)) {
-    if constexpr (FK == 0) {
-      if (!vec) return;
-      const int rows = half_rows(half), cols = half_cols(half);
-#pragma unroll
-      for (int t = 0; t < NU; ++t) {
-        const int i = threadIdx.x + 512 * t, r = tr ? i / (C::Sx / 4) : i / (HW / 4);
-        const int c = (tr ? i % (C::Sx / 4) : i % (HW / 4)) * 4;
-        if (r < rows && c + 4 <= cols)
-          wv[t] = *reinterpret_cast<const QT*>(static_cast<const PT*>(md->W) + w_index(half, r, c));
-      }
-    }
-  };
-  if constexpr (FINAL) read_w(0);
   // ---- X'^T = a X^T + X^T B over the wavefront's columns: a lane gets 4
   // consecutive columns of one row ----------------------------------------------
   constexpr int CBW = C::SW / 32;                          // 32-column blocks of a wavefront
@@ -2671,7 +2802,7 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
 #pragma unroll
       for (int k = 0; k < CBW; ++k) {
         const int row = 16 * g + 8 * (G >> 1) + (Lq >> 2), col = w0 + 32 * k + 16 * (G & 1) + 4 * (Lq & 3);
-        const uint2 lo = tr_read_b64(xs + slice_at<RB>(row, col)), hi = tr_read_b64(xs + slice_at<RB>(row + 4, col));
+        const uint2 lo = tr_read_b64(xs + slice_at<RB, NW>(row, col)), hi = tr_read_b64(xs + slice_at<RB, NW>(row + 4, col));
         const u32x4_t xf{lo.x, lo.y, hi.x, hi.y};
 #pragma unroll
         for (int i = 0; i < RB; ++i) Mma<uint16_t>::run(xf, bf[i], acc[k][i]);
@@ -2684,7 +2815,7 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int row = 32 * i + (lane & 31), col = w0 + 32 * k + 8 * g + 4 * (lane >> 5);
-          char* p = xs + slice_at<RB>(row, col);
+          char* p = xs + slice_at<RB, NW>(row, col);
           float e[4], v[4];
           unpack_bf16x4(*reinterpret_cast<const uint2*>(p), e);
 #pragma unroll
@@ -2702,57 +2833,43 @@ __global__ __launch_bounds__(512) void k_slice_step(SliceArgs sa) {
     slice_store<RB>(xs, nv, X, sa.L);
     slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
   } else {
-    // ---- the parameter (or output), half a slice at a time: O in fp32 through
-    // LDS in the parameter's layout, whole rows back, 4 elements a thread and
-    // access.  W is read ahead, 8 accesses in flight a thread: read one by one
-    // it took most of the step (96 matrices of 128 x 4096: 251 us). ----------------
+    // ---- the parameter (or output): O in fp32 through LDS in the parameter's
+    // layout, whole rows back --------------------------------------------------------
     float* const os = reinterpret_cast<float*>(smem);
-    // row-major [Sx][HW], 16-byte chunk ch of row r at ch ^ (r % 16); or [HW][Sx] (parameter l x s)
-    auto oat = [](int r, int c) { return r * HW + ((((c >> 2) ^ (r & 15)) << 2) | (c & 3)); };
-    for (int half = 0; half < 2; ++half) {
-      if (half) __syncthreads();
-      const int h0 = half * HW;
-      if (w0 >= h0 && w0 < h0 + HW && w0 < nv) {
+    // row-major [Sx][W], 16-byte chunk ch of row r at ch ^ (r % 16); or [W][Sx] (parameter l x s)
+    auto oat = [](int r, int c) { return r * C::W + ((((c >> 2) ^ (r & 15)) << 2) | (c & 3)); };
+    if (w0 < nv) {
 #pragma unroll
-        for (int k = 0; k < CBW; ++k)
+      for (int k = 0; k < CBW; ++k)
 #pragma unroll
-          for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              const int row = 32 * i + (lane & 31), col = w0 - h0 + 32 * k + 8 * g + 4 * (lane >> 5);
-              const f32x16_t& o = acc[k][i];
-              if (tr) {
+          for (int g = 0; g < 4; ++g) {
+            const int row = 32 * i + (lane & 31), col = w0 + 32 * k + 8 * g + 4 * (lane >> 5);
+            const f32x16_t& o = acc[k][i];
+            if (tr) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) os[(col + q) * C::Sx + row] = o[4 * g + q];
-              } else {
-                *reinterpret_cast<float4*>(os + oat(row, col)) =
-                    make_float4(o[4 * g], o[4 * g + 1], o[4 * g + 2], o[4 * g + 3]);
-              }
+              for (int q = 0; q < 4; ++q) os[(col + q) * C::Sx + row] = o[4 * g + q];
+            } else {
+              *reinterpret_cast<float4*>(os + oat(row, col)) =
+                  make_float4(o[4 * g], o[4 * g + 1], o[4 * g + 2], o[4 * g + 3]);
             }
-      }
-      __syncthreads();
-      const int rows = half_rows(half), cols = half_cols(half);
-      if (rows > 0 && cols > 0) {
-#pragma unroll
-        for (int t = 0; t < NU; ++t) {
-          const int i = threadIdx.x + 512 * t, r = tr ? i / (C::Sx / 4) : i / (HW / 4);
-          const int c = (tr ? i % (C::Sx / 4) : i % (HW / 4)) * 4, n = min(4, cols - c);
-          if (r >= rows || n <= 0) continue;
-          const float4 ov = *reinterpret_cast<const float4*>(os + (tr ? r * C::Sx + c : oat(r, c)));
-          const float o[4] = {ov.x, ov.y, ov.z, ov.w};
-          const int64_t idx = w_index(half, r, c);
-          if (vec && n == 4) {
-            float w[4] = {0.f, 0.f, 0.f, 0.f}, v[4];
-            if (FK == 0) quad_get(wv[t], w);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = FK == 0 ? fmaf(md->decay, w[q], -md->upd_scale * o[q]) : o[q];
-            quad_put(reinterpret_cast<QT*>(static_cast<PT*>(FK == 0 ? md->W : md->out) + idx), v);
-          } else {
-            apply_tail<FK == 0 ? 0 : 1, PDT>(md, idx, o[0], o[1], o[2], o[3], n);
           }
-        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NU; ++t) {
+      int r, c;
+      w_unit(t, r, c);
+      const int n = min(8, wcols - c);
+      if (r >= wrows || n <= 0) continue;
+      float o[8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 ov = *reinterpret_cast<const float4*>(os + (tr ? r * C::Sx + c + 4 * h : oat(r, c + 4 * h)));
+        o[4 * h] = ov.x; o[4 * h + 1] = ov.y; o[4 * h + 2] = ov.z; o[4 * h + 3] = ov.w;
       }
-      if (half == 0) read_w(1);
+      apply8<FK == 0 ? 0 : 1, PT>(w, w_at(r, c), o, n, wv[t]);
     }
   }
 }
@@ -2766,13 +2883,16 @@ hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuf
   sa.sc = sc;
   sa.s = cg.s; sa.l = cg.l; sa.L = cg.L;
   sa.nsl = (cg.L + C::W - 1) / C::W;
+  sa.nnorm = sa.nsl;
   sa.np = C::KSPLIT ? cg.L / C::SW : sa.nsl;
   sa.X = static_cast<uint16_t*>(wb.X[0]);
   sa.matX = static_cast<int64_t>(cg.S) * cg.L;
   sa.part = static_cast<float*>(wb.X[1]);                  // over X[1], XT[0] and XT[1]
   sa.A = static_cast<uint16_t*>(wb.A);
   sa.norm = wb.partials;
-  const dim3 slices(static_cast<unsigned>(sa.nsl) * static_cast<unsigned>(cg.nmat));
+  sa.nmat = cg.nmat;
+  const unsigned mats = cg.nmat < 8 ? cg.nmat : (cg.nmat + 7) / 8 * 8;
+  const dim3 slices(static_cast<unsigned>(sa.nsl) * mats);
   const dim3 blocks(static_cast<unsigned>(C::NB) * static_cast<unsigned>(cg.nmat));
   if (sc.momentum) {
     hipLaunchKernelGGL((k_slice_first<GT, RB, true, false>), slices, dim3(512), 0, st, sa);
@@ -2785,13 +2905,15 @@ hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuf
     sa.first = k == 0 ? 1 : 0;
     sa.a = coeffs[3 * k]; sa.b = coeffs[3 * k + 1]; sa.c = coeffs[3 * k + 2];
     hipLaunchKernelGGL((k_slice_reduce<RB>), blocks, dim3(256), 0, st, sa);
-    const bool o = sc.final_kind != 0, f32 = cg.param_dtype == DT_F32;
     if (k + 1 < K) hipLaunchKernelGGL((k_slice_step<RB, -1, DT_BF16>), slices, dim3(512), 0, st, sa);
-    else if (!o && !f32) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_BF16>), slices, dim3(512), 0, st, sa);
-    else if (!o) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_F32>), slices, dim3(512), 0, st, sa);
-    else if (!f32) hipLaunchKernelGGL((k_slice_step<RB, 1, DT_BF16>), slices, dim3(512), 0, st, sa);
-    else hipLaunchKernelGGL((k_slice_step<RB, 1, DT_F32>), slices, dim3(512), 0, st, sa);
   }
+  const bool o = sc.final_kind != 0, f32 = cg.param_dtype == DT_F32;
+  sa.nsl = (cg.L + C::W / 2 - 1) / (C::W / 2);
+  const dim3 halves(static_cast<unsigned>(sa.nsl) * mats);
+  if (!o && !f32) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_BF16>), halves, dim3(256), 0, st, sa);
+  else if (!o) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_F32>), halves, dim3(256), 0, st, sa);
+  else if (!f32) hipLaunchKernelGGL((k_slice_step<RB, 1, DT_BF16>), halves, dim3(256), 0, st, sa);
+  else hipLaunchKernelGGL((k_slice_step<RB, 1, DT_F32>), halves, dim3(256), 0, st, sa);
   return hipGetLastError();
 }
 
@@ -3019,7 +3141,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
     // reads B, X (twice under qtr, else X^T and X); writes X' (and X'^T)
     r.b[2] = nm * (s * s + (qtr ? 3 : 4) * s * l) * xsz;
   } else {
-    u.desc = d_desc; u.final_kind = sc.final_kind; u.param_dtype = cg.param_dtype;
+    u.desc = d_desc; u.final_kind = sc.final_kind; u.param_dtype = cg.param_dtype; u.w_rows16 = cg.w_rows16;
     // reads B, X^T, X (and W); writes W or out
     r.b[2] = nm * ((s * s + 2 * s * l) * xsz + s * l * (sc.final_kind == 0 ? 2 * psz : psz));
   }
