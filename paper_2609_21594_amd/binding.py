@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -214,6 +215,41 @@ def _view(x):
     return t, E, rows, N, ld, rb, bs, ps
 
 
+# MuonParam as a packed record (a test compares it with the ctypes layout).
+_PARAM_PACK = struct.Struct("@PPPqqqqiiqqqifPii")
+
+
+def _plain_params(params, grads, moms):
+    """params_array for calls whose entries are all contiguous [M, N] or
+    [E, M, N] tensors without options, which is what an optimizer step over
+    many small matrices passes: the same structs, packed directly.  Through
+    `_view` and ctypes fields an entry takes three to four times as long,
+    more than a small matrix takes on the GPU.  None when some entry needs the
+    general path (or its error)."""
+    import torch
+    codes = {torch.float32: F32, torch.bfloat16: BF16}
+    f32, pack, size = torch.float32, _PARAM_PACK.pack_into, _PARAM_PACK.size
+    arr = (MuonParam * len(params))()
+    at = 0
+    for W, g, m in zip(params, grads, moms):
+        if W.__class__ is RowBlocks or g.__class__ is RowBlocks or m.__class__ is RowBlocks:
+            return None
+        shape = W.shape
+        nd = len(shape)
+        pd, gd = codes.get(W.dtype), codes.get(g.dtype)
+        if (nd != 2 and nd != 3) or g.shape != shape or m.shape != shape or pd is None or gd is None or \
+                m.dtype is not f32 or not (W.is_contiguous() and g.is_contiguous() and m.is_contiguous()):
+            return None
+        M, N = shape[-2:]
+        E = shape[0] if nd == 3 else 1
+        if E * M * N == 0:
+            return None
+        pack(arr, at, W.data_ptr(), g.data_ptr(), m.data_ptr(), M, N, E, N, pd, gd, 0, 0, M * N if E > 1 else 0,
+             0, 0.0, 0, 0, 0)
+        at += size
+    return arr, None
+
+
 def params_array(params, grads, moms, entry_coeffs=None, entry_scale_modes=None, entry_post_scales=None):
     """(MuonParam[], keepalive) for lists of logical matrices (see _view).
     grad takes the param's view; momentum takes it too, or is a dense
@@ -226,6 +262,10 @@ def params_array(params, grads, moms, entry_coeffs=None, entry_scale_modes=None,
     if not (len(params) == len(grads) == len(moms)):
         raise ValueError("params, grads and momenta must have equal length")
     n = len(params)
+    if n and entry_coeffs is None and entry_scale_modes is None and entry_post_scales is None:
+        plain = _plain_params(params, grads, moms)
+        if plain is not None:
+            return plain
     entry_coeffs = entry_coeffs or [None] * n
     entry_scale_modes = entry_scale_modes or [None] * n
     entry_post_scales = entry_post_scales or [None] * n
@@ -266,7 +306,7 @@ def _check_device(tensors, device: int):
     must never reach a kernel."""
     for t in tensors:
         t = t.t if isinstance(t, RowBlocks) else t
-        if t.device.type != "cuda" or t.device.index != device:
+        if not t.is_cuda or t.get_device() != device:
             raise ValueError(f"tensor on {t.device}, the handle runs on cuda:{device}")
 
 
@@ -398,15 +438,17 @@ class Muon:
         outs = (ctypes.c_void_p * n)()
         rows = (ctypes.c_int64 * n)()
         cols = (ctypes.c_int64 * n)()
+        tdt = inputs[0].dtype
         for i, (a, b) in enumerate(zip(inputs, outputs)):
-            if a.dim() != 2 or a.shape != b.shape:
+            shape = a.shape
+            if len(shape) != 2 or shape != b.shape:
                 raise ValueError(f"matrix {i}: need equal 2-D shapes")
-            if _dtype_code(a) != dt or _dtype_code(b) != dt:
+            if a.dtype is not tdt or b.dtype is not tdt:
                 raise TypeError("all inputs and outputs must share one dtype")
             if not (a.is_contiguous() and b.is_contiguous()):
                 raise ValueError(f"matrix {i}: tensors must be contiguous")
             ins[i], outs[i] = a.data_ptr(), b.data_ptr()
-            rows[i], cols[i] = a.shape[0], a.shape[1]
+            rows[i], cols[i] = shape
         coeff = None
         if ns_coeffs is not None:
             flat = _coeff_table(ns_coeffs, ns_steps)

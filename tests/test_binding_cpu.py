@@ -70,3 +70,33 @@ def test_optimizer_needs_gpu_parameters():
     from paper_2609_21594_amd.optim import MuonAdamW
     with pytest.raises(ValueError, match="one GPU"):
         MuonAdamW([torch.nn.Parameter(torch.zeros(4, 4))])
+
+
+def test_plain_entries_pack_the_same_structs_as_the_general_path():
+    """Calls whose entries are all contiguous take a packed path: it must give
+    the bytes that the general path gives, and hand over every other call."""
+    import ctypes
+    import torch
+    from paper_2609_21594_amd import binding as B
+    assert B._PARAM_PACK.size == ctypes.sizeof(B.MuonParam)
+    shapes = [(4, 6), (1, 5), (5, 1), (1, 1), (3, 4, 6), (1, 4, 6), (3, 1, 6), (2, 6, 1)]
+    for pd, gd in ((torch.float32, torch.float32), (torch.bfloat16, torch.float32), (torch.bfloat16, torch.bfloat16)):
+        W = [torch.zeros(s, dtype=pd) for s in shapes]
+        g = [torch.zeros(s, dtype=gd) for s in shapes]
+        m = [torch.zeros(s) for s in shapes]
+        assert B._plain_params(W, g, m) is not None
+        fast, _ = B.params_array(W, g, m)
+        slow, _ = B.params_array(W, g, m, entry_coeffs=[None] * len(shapes))
+        assert bytes(fast) == bytes(slow)
+    W, g, m = torch.zeros(4, 6), torch.zeros(4, 6), torch.zeros(4, 6)
+    wide = torch.zeros(4, 8)[:, :6]
+    others = [([wide], [torch.zeros(4, 8)[:, :6]], [m]), ([W], [g], [torch.zeros(1, 4, 6)]),
+              ([B.RowBlocks(torch.zeros(2, 2, 6))], [B.RowBlocks(torch.zeros(2, 2, 6))], [m]),
+              ([torch.zeros(0, 6)], [torch.zeros(0, 6)], [torch.zeros(0, 6)])]
+    for p, q, r in others:
+        assert B._plain_params(p, q, r) is None
+    for bad in (([W], [torch.zeros(6, 4)], [m]), ([W.double()], [g], [m]), ([W], [g], [m.bfloat16()]),
+                ([W.t()], [g.t()], [m.t()])):
+        assert B._plain_params(*bad) is None
+        with pytest.raises((ValueError, TypeError)):
+            B.params_array(*bad)
