@@ -874,6 +874,9 @@ using CfgSquare = TileCfg<256, 256, 2, 4, MUON_SQ_SLAB, MUON_SQ_STAGES, 2>;
 // element sees the same operations in the same order on both, so the choice
 // never changes a result.
 using CfgQuarter = TileCfg<128, 128, 2, 2, 128, 2, 2>;
+// The same tile with four stages, one workgroup per CU: launches of at most
+// one tile per CU, where each slab waits for its loads (deep_tiles).
+using CfgDeep = TileCfg<128, 128, 2, 2, 128, 4, 1>;
 
 // Tile `logical` of the launch: matrix-major; inside a matrix, banded
 // (GS / GM tile-rows per band, column by column inside a band).
@@ -951,7 +954,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  static_assert(SLAB == 128 && NS == 2 && GPS == 4 && (BM == 256 || BM == 128) && BN == BM && RPI == 8,
+  static_assert(SLAB == 128 && (NS == 2 || (NS == 4 && !SPLIT)) && GPS == 4 && (BM == 256 || BM == 128) && BN == BM && RPI == 8,
                 "slab geometry: 64 k of BM rows, or 64 k-rows of BM columns");
   constexpr int TRB = BM * 2;                 // bytes of a transposed slab row, of a staged tile row
   constexpr int TRC = TRB / 16;               // its 16-byte chunks
@@ -1037,8 +1040,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     }
   };
   auto issue = [&](int ks) __attribute__((always_inline)) {
-    issue_op(std::false_type{}, ks, (ks & 1) * STAGE);
-    issue_op(std::true_type{}, ks, (ks & 1) * STAGE);
+    issue_op(std::false_type{}, ks, (ks & (NS - 1)) * STAGE);
+    issue_op(std::true_type{}, ks, (ks & (NS - 1)) * STAGE);
   };
 
   f32x16_t acc[BI][BJ];
@@ -1223,7 +1226,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // Splitting the burst by operand measured 2-3% faster on the step than
   // issuing a slab at once; splitting each operand in halves, or P later,
   // measured slower.
-  constexpr bool EARLY = EPI == EPI_GRAM && !SPLIT;
+  //  - with four stages (DEEP), whole slabs three ahead: a launch of one
+  //    128 x 128 tile per CU waits on latency, not on contention.
+  constexpr bool DEEP = NS > 2;
+  constexpr bool EARLY = EPI == EPI_GRAM && !SPLIT && !DEEP;
   // The a*X (or A) term of slab ks, if it holds some of this wave's.
   auto take_e = [&](const char* sp, int ks) __attribute__((always_inline)) {
     if (ks == e_ks0 || ks == e_ks1) {  // wave-uniform; at most twice a tile
@@ -1249,8 +1255,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     }
   };
   auto slab = [&](auto ptc, auto qtc, auto nextc, auto ec, int ks) __attribute__((always_inline)) {
-    const char* sp = smem + (ks & 1) * STAGE;
-    if (ks + 1 < nk) {
+    const char* sp = smem + (ks & (NS - 1)) * STAGE;
+    if constexpr (DEEP) {
+      if (ks + 3 < nk) issue(ks + 3);                       // over slab ks - 1, which every wave has left
+    } else if (ks + 1 < nk) {
       if (!EARLY) issue_op(std::true_type{}, ks + 1, ((ks + 1) & 1) * STAGE);
       else if (ks >= 1) issue_op(std::false_type{}, ks + 1, ((ks + 1) & 1) * STAGE);  // slab 1 went out whole with slab 0
     }
@@ -1258,19 +1266,22 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     __builtin_amdgcn_sched_barrier(0);
     rd(ptc, qtc, sp, sp, I_<1>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
-    if (!EARLY && ks + 1 < nk) issue_op(std::false_type{}, ks + 1, ((ks + 1) & 1) * STAGE);
+    if (!EARLY && !DEEP && ks + 1 < nk) issue_op(std::false_type{}, ks + 1, ((ks + 1) & 1) * STAGE);
     __builtin_amdgcn_sched_barrier(0);
     rd(ptc, qtc, sp, sp, I_<2>{}, I_<0>{}); mm(I_<1>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
     rd(ptc, qtc, sp, sp, I_<3>{}, I_<1>{}); mm(I_<0>{}); interleave(ptc, qtc);
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // slab ks + 1 has landed
+    // slab ks + 1 has landed (DEEP: the two after it may not have)
+    if (DEEP && ks + 3 < nk) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (NLP + NLQ)) : "memory");
+    else if (DEEP && ks + 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLP + NLQ) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     // every wave is done with slab ks: its stage can take slab ks + 2
     if (EARLY && ks + 2 < nk) issue_op(std::true_type{}, ks + 2, (ks & 1) * STAGE);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (decltype(nextc)::value) {
-      const char* sn = smem + ((ks + 1) & 1) * STAGE;
+      const char* sn = smem + ((ks + 1) & (NS - 1)) * STAGE;
       rd(ptc, qtc, sn, sn, I_<0>{}, I_<0>{});
       mm(I_<1>{}); interleave(ptc, qtc);
     } else {
@@ -1333,7 +1344,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       for (int t = (pass == 0 ? 5 : 1) * (b - a) - 1; t > 0; --t) step(ptc, qtc, std::true_type{});
       step(ptc, qtc, std::false_type{});
     } else {
-      rd(ptc, qtc, smem + (a & 1) * STAGE, smem + (a & 1) * STAGE, I_<0>{}, I_<0>{});
+      const char* sa = smem + (a & (NS - 1)) * STAGE;
+      rd(ptc, qtc, sa, sa, I_<0>{}, I_<0>{});
       for (int ks = a; ks < b - 1; ++ks) slab(ptc, qtc, std::true_type{}, ec, ks);
       slab(ptc, qtc, std::false_type{}, ec, b - 1);
     }
@@ -1344,7 +1356,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     issue_op(F_{}, 0, 0, 0);
     issue_op(T_{}, 0, 0, 2 * ga.q_plane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  } else if (issue(0); EARLY && nk > 1) {
+  } else if (issue(0); DEEP) {
+    if (nk > 1) issue(1);
+    if (nk > 2) issue(2);
+    if (nk > 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (NLP + NLQ)) : "memory");
+    else if (nk > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLP + NLQ) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else if (EARLY && nk > 1) {
     issue(1);
     // slab 0 has landed, slab 1 (NLP + NLQ loads) may not
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLP + NLQ) : "memory");
@@ -1890,6 +1908,18 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
   return hipGetLastError();
 }
 
+int64_t quarter_tiles(const GemmArgs& ga) {  // 128 x 128 tiles of a matrix
+  const int64_t m = ga.tiles_m, n = ga.tiles_n;
+  return ga.syrk ? m * (m + 1) / 2 : m * n;
+}
+// At most one 128 x 128 tile per CU and at least 16 slabs: four stages.  Two
+// and four stages, us per launch: Gram of 1024 x 4096 54 / 38, of 2048 x 5632
+// 72 / 52, update of 2048 x 2048 36 / 31 (one matrix each); with 8 slabs or
+// fewer the three slabs issued first cost what they gain: 512 x 512 12.5 / 12.8,
+// eight 256 x 1024 9.1 / 10.3.
+bool deep_tiles(const GemmArgs& ga, int nmat) {
+  return ga.k_slabs >= 16 && quarter_tiles(ga) * nmat <= device_cu_count();
+}
 // Whether a launch runs on 128 x 128 tiles (CfgQuarter): where 256 x 256
 // tiles would leave many CUs idle, in a last round or in the only one.
 // The model is fitted to single launches on an MI355X (us, nk slabs of 64 k):
@@ -1902,14 +1932,15 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
 // one 114 / 73; update of 512 x 512, one matrix 21 / 12, 256 matrices 104 /
 // 122; update of 4096 x 11008 319 / 387; Gram of 768 x 768, 48 matrices 54 / 39.
 bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
-  const int64_t m1 = ga.tiles_m, n1 = ga.tiles_n, m2 = (m1 + 1) / 2, n2 = (n1 + 1) / 2;
-  const double t1 = double(nmat) * double(ga.syrk ? m1 * (m1 + 1) / 2 : m1 * n1);
+  const int64_t m2 = (ga.tiles_m + 1) / 2, n2 = (ga.tiles_n + 1) / 2;
+  const double t1 = double(nmat) * double(quarter_tiles(ga));
   const double t2 = double(nmat) * double(ga.syrk ? m2 * (m2 + 1) / 2 : m2 * n2);
   const double cus = device_cu_count(), nk = ga.k_slabs * (split ? 6 : 1);
   const double rounds2 = std::ceil(t2 / cus), f = t2 / (rounds2 * cus);
   const double r1 = t1 / (2.0 * cus), rounds1 = std::ceil(r1);
   const double cost2 = rounds2 * ((1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f);
-  const double cost1 = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
+  double cost1 = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
+  if (!split && deep_tiles(ga, nmat)) cost1 = 0.6 * nk + 4.0;
   return cost1 < cost2;
 }
 
@@ -3164,9 +3195,12 @@ hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBu
       if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st);
     if constexpr (std::is_same<XT, float>::value)
       return hipErrorInvalidValue;
-    else
-      return small_tiles(ga, nmat, split) ? launch_tile<CfgQuarter, split>(epi, ga, nmat, st)
-                                          : launch_tile<CfgSquare, split>(epi, ga, nmat, st);
+    else {
+      if (!small_tiles(ga, nmat, split)) return launch_tile<CfgSquare, split>(epi, ga, nmat, st);
+      if constexpr (!split)
+        if (deep_tiles(ga, nmat)) return launch_tile<CfgDeep, false>(epi, ga, nmat, st);
+      return launch_tile<CfgQuarter, split>(epi, ga, nmat, st);
+    }
   };
   int cur = 0;
   for (int k = 0; k < K; ++k) {
