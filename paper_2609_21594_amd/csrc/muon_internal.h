@@ -130,16 +130,19 @@ inline bool chunk_keeps_xt(int64_t S, int64_t L, bool ns_f32, int K) {
   return ns_f32 || !chunk_on_tiles(S, L, K) || S % 256 != 0 || L % 256 != 0;
 }
 // A chunk whose short side is at most 128 runs in one of two ways, by its
-// shape alone, so that a matrix gets the same bits in any batch:
+// shape and precision alone, so that a matrix gets the same bits in any batch:
 //  - as one fused launch (k_ns_small: momentum, norm, every Newton-Schulz step
-//    and the update, the workgroups of a matrix meeting at barriers): fp32
-//    Newton-Schulz, K = 0, and bf16 matrices of at most 64 x 384 or 128 x 256;
+//    and the update, the workgroups of a matrix meeting at barriers): K = 0,
+//    bf16 matrices of at most 64 x 384 or 128 x 256, fp32 ones of at most 64 x
+//    512 or 128 x 1024;
 //  - as column slices (k_slice_*: two launches a step over all matrices): the
-//    other bf16 ones, with at least one step.
-// Measured on an MI355X (us per call, bf16 orthogonalisation, fused / slices):
-// one 16 x 128 38 / 40, 16 x 1024 97 / 51, 64 x 300 56 / 62, 64 x 512 63 / 64,
-// 128 x 256 51 / 76, 128 x 512 71 / 77; 64 matrices of 64 x 300 121 / 130, of
-// 64 x 512 150 / 132, of 128 x 512 288 / 130, of 64 x 4096 1029 / 184.
+//    others, with at least one step.
+// Measured on an MI355X (us per orthogonalisation, fused / slices), bf16: one
+// 16 x 128 38 / 40, 16 x 1024 97 / 48, 64 x 300 56 / 62, 64 x 512 63 / 63,
+// 128 x 256 51 / 76, 128 x 512 71 / 74; 64 matrices of 64 x 300 121 / 130, of
+// 64 x 512 150 / 135, of 128 x 512 288 / 142, of 64 x 4096 1029 / 181.  fp32:
+// one 16 x 1024 123 / 83, 128 x 1024 161 / 202, 64 x 2048 247 / 119, 128 x 4096
+// 701 / 227; 64 of 64 x 4096 1426 / 454, of 128 x 2048 1622 / 868.
 // The fused launch needs group counters (kSmallSyncBytes) and kSmallMaxGroup
 // norm partials per matrix.  chunk_reserves_small says which chunks reserve
 // them: also some that now run as slices, since what a call needs of a
@@ -151,10 +154,11 @@ inline bool chunk_reserves_small(int64_t s, int64_t l, bool ns_f32) {
   return ns_f32 || s <= 64 || l <= 512;
 }
 inline bool chunk_is_small(int64_t s, int64_t l, bool ns_f32, int K) {
-  return chunk_reserves_small(s, l, ns_f32) && (ns_f32 || K == 0 || l <= (s <= 32 || s > 64 ? 256 : 384));
+  if (!chunk_reserves_small(s, l, ns_f32)) return false;
+  return K == 0 || l <= (ns_f32 ? (s > 64 ? 1024 : 512) : s <= 32 || s > 64 ? 256 : 384);
 }
 inline bool chunk_is_sliced(int64_t s, int64_t l, bool ns_f32, int K) {
-  return !ns_f32 && s <= 128 && chunk_on_tiles(128, round_up(l, kPad), K) && !chunk_is_small(s, l, ns_f32, K);
+  return s <= 128 && K > 0 && tile_rows_fit(128, round_up(l, kPad), ns_f32 ? 4 : 2) && !chunk_is_small(s, l, ns_f32, K);
 }
 
 // A group: chunks whose products of each Newton-Schulz step run as one

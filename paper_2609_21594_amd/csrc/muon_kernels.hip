@@ -2395,7 +2395,7 @@ __global__ __launch_bounds__(256) void k_ns_small(SmallArgs sa) {
 }
 
 // ---------------------------------------------------------------------------
-// bf16 Newton-Schulz for short sides up to 128 (k_slice_*).  The tile kernel
+// Newton-Schulz for short sides up to 128 (k_slice_*).  The tile kernel
 // has one Gram tile per such matrix (64 slabs of k on one compute unit for
 // 128 x 4096) and half-empty update tiles; here X is cut into column slices
 // of 64 KB, one per workgroup, and a step is two launches over all matrices:
@@ -2426,37 +2426,47 @@ struct SliceArgs {
   int32_t nmat;
   int32_t nnorm;             // slices of the prologue (square sums) per matrix
   int32_t first;
-  uint16_t* X;               // per matrix: S x L (matX elements), rows of stride L
+  void* X;                   // per matrix: S x L (matX elements), rows of stride L
   int64_t matX;
   float* part;               // per matrix: np x NB x 1024, MFMA output order
-  uint16_t* A;               // per matrix: Sx x Sx
+  void* A;                   // per matrix: Sx x Sx
   double* norm;              // per matrix: nsl
   float a, b, c;
 };
 
-// NW: wavefronts of the workgroup, 8, or 4 in the last step: its slices are
-// half as wide (no Gram partial depends on them), so that two workgroups fit a
-// compute unit and one computes while the other waits for W.
-template <int RB, int NW = 8>
+// XT: the iterate's type, bfloat16 or fp32 (whose products are fp32 MFMA).
+// NW: wavefronts of the workgroup: 8 for bf16, or 4 in its last step, whose
+// slices are half as wide (no Gram partial depends on them), so that two
+// workgroups fit a compute unit and one computes while the other waits for W;
+// 4 for fp32, whose A takes the other 64 KB of the LDS.
+template <typename XT, int RB, int NW>
 struct SliceCfg {
+  static constexpr int ES = sizeof(XT), EPC = 16 / ES;               // bytes an element, elements a 16-byte chunk
   static constexpr int Sx = 32 * RB, SW = 128 / RB;                  // SW: columns of a wavefront
-  static constexpr int W = NW * SW, PITCH = 2 * W;                   // PITCH: bytes of a slice row
+  static constexpr int W = NW * SW, PITCH = ES * W;                  // PITCH: bytes of a slice row
   static constexpr int NB = RB * (RB + 1) / 2;                       // upper 32 x 32 blocks of A
-  static constexpr int AP = 2 * Sx, ABYTES = Sx * AP;                // A row, A
+  static constexpr int AP = ES * Sx, ABYTES = Sx * AP;               // A row, A
   static constexpr bool KSPLIT = RB < 4;  // Gram: each wavefront its own columns (a partial each), else output blocks
-  static constexpr int PPS = KSPLIT ? 8 : 1;                         // partials of a full slice
+  static constexpr int PPS = KSPLIT ? NW : 1;                        // partials of a full slice
 };
+template <typename XT> constexpr int kSliceWaves = sizeof(XT) == 2 ? 8 : 4;
 __device__ __forceinline__ int slice_key(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 // LDS byte of column col (in elements) of slice row r
-template <int RB, int NW = 8>
+template <class C>
 __device__ __forceinline__ int slice_at(int r, int col) {
-  return r * SliceCfg<RB, NW>::PITCH + (((col >> 3) ^ slice_key(r)) << 4) + (col & 7) * 2;
+  return r * C::PITCH + (((col / C::EPC) ^ slice_key(r)) << 4) + (col % C::EPC) * C::ES;
 }
 // LDS byte of element (r, c) of A or B
-template <int RB>
+template <class C>
 __device__ __forceinline__ int slice_a_at(int r, int c) {
-  return r * SliceCfg<RB>::AP + (((c >> 3) ^ (slice_key(r) & (4 * RB - 1))) << 4) + (c & 7) * 2;
+  return r * C::AP + (((c / C::EPC) ^ (slice_key(r) & (C::AP / 16 - 1))) << 4) + (c % C::EPC) * C::ES;
 }
+template <typename XT> struct Four { using T = uint2; };
+template <> struct Four<float> { using T = float4; };
+__device__ __forceinline__ void get4(const uint2& t, float v[4]) { unpack_bf16x4(t, v); }
+__device__ __forceinline__ void get4(const float4& t, float v[4]) { v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
+__device__ __forceinline__ void set4(uint2& t, const float v[4]) { t = pack_bf16x4(v); }
+__device__ __forceinline__ void set4(float4& t, const float v[4]) { t = make_float4(v[0], v[1], v[2], v[3]); }
 
 // Workgroup b's matrix and slice.  Workgroup b runs on XCD b % 8: from 8
 // matrices on, a matrix's slices share an XCD, whose L2 then holds its A once,
@@ -2493,13 +2503,36 @@ __device__ __forceinline__ double slice_r(const double* norm, int n, float eps, 
 // range, else 1 (X then holds r u, see k_slice_first<RESCALE>).
 __device__ __forceinline__ bool slice_folds(double r) { return r >= 0x1p-40 && r <= 0x1p40; }
 
+// fp32 products of k in kSums interleaved sums, added at the end: one chain of
+// 64 additions (k = 128) left up to 1.7 times the error of the fused launch,
+// which keeps two of 16 each.
+constexpr int kSums = 4;
+__device__ __forceinline__ f32x16_t add_sums(const f32x16_t p[kSums]) { return (p[0] + p[1]) + (p[2] + p[3]); }
+// Mma<XT>::run into one sum (bf16) or its four interleaved ones (fp32).
+template <typename XT>
+__device__ __forceinline__ void mma_sums(const u32x4_t& a, const u32x4_t& b, f32x16_t* p) {
+  if constexpr (sizeof(XT) == 2) {
+    Mma<XT>::run(a, b, p[0]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      p[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[j]), __uint_as_float(b[j]), p[j], 0, 0, 0);
+  }
+}
+template <typename XT>
+__device__ __forceinline__ f32x16_t all_sums(const f32x16_t* p) {
+  if constexpr (sizeof(XT) == 2) return p[0];
+  else return add_sums(p);
+}
+
 // The Gram partial(s) of the slice in LDS (nv columns, a multiple of 128).
-template <int RB>
+// One fragment pair is 16 (bf16) or 8 (fp32) columns.
+template <typename XT, class C, int NW>
 __device__ __forceinline__ void slice_gram(const char* xs, int nv, float* part) {
-  using C = SliceCfg<RB>;
+  constexpr int RB = C::Sx / 32, KC = 32 / C::ES, NS = sizeof(XT) == 2 ? 1 : kSums;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   auto frag = [&](int rb, int col) {
-    return *reinterpret_cast<const u32x4_t*>(xs + slice_at<RB>(32 * rb + (lane & 31), col + 8 * (lane >> 5)));
+    return *reinterpret_cast<const u32x4_t*>(xs + slice_at<C>(32 * rb + (lane & 31), col + C::EPC * (lane >> 5)));
   };
   auto put = [&](float* p, const f32x16_t& v) {
 #pragma unroll
@@ -2509,56 +2542,77 @@ __device__ __forceinline__ void slice_gram(const char* xs, int nv, float* part) 
   if constexpr (C::KSPLIT) {
     const int c0 = wave * C::SW;
     if (c0 >= nv) return;
-    f32x16_t acc[C::NB] = {};
+    f32x16_t acc[C::NB][NS] = {};
 #pragma unroll
-    for (int g = 0; g < C::SW / 16; ++g) {
+    for (int g = 0; g < C::SW / KC; ++g) {
       u32x4_t f[RB];
 #pragma unroll
-      for (int i = 0; i < RB; ++i) f[i] = frag(i, c0 + 16 * g);
+      for (int i = 0; i < RB; ++i) f[i] = frag(i, c0 + KC * g);
 #pragma unroll
       for (int j = 0; j < RB; ++j)
 #pragma unroll
-        for (int i = 0; i <= j; ++i) Mma<uint16_t>::run(f[i], f[j], acc[j * (j + 1) / 2 + i]);
+        for (int i = 0; i <= j; ++i) mma_sums<XT>(f[i], f[j], acc[j * (j + 1) / 2 + i]);
     }
     float* p = part + static_cast<int64_t>(wave) * C::NB * 1024;
 #pragma unroll
-    for (int n = 0; n < C::NB; ++n) put(p + n * 1024, acc[n]);
-  } else {
+    for (int n = 0; n < C::NB; ++n) put(p + n * 1024, all_sums<XT>(acc[n]));
+  } else if constexpr (NW == 8) {
     // wavefront (wm, wn): row blocks 2 wm and 2 wm + 1 of column block wn, those on or above the diagonal
     const int wm = wave >> 2, wn = wave & 3;
     if (2 * wm > wn) return;
     const bool two = 2 * wm + 1 <= wn;
-    f32x16_t acc[2] = {};
-    for (int g = 0; g < nv / 16; ++g) {
-      const u32x4_t q = frag(wn, 16 * g);
-      Mma<uint16_t>::run(frag(2 * wm, 16 * g), q, acc[0]);
-      if (two) Mma<uint16_t>::run(frag(2 * wm + 1, 16 * g), q, acc[1]);
+    f32x16_t acc[2][NS] = {};
+    for (int g = 0; g < nv / KC; ++g) {
+      const u32x4_t q = frag(wn, KC * g);
+      mma_sums<XT>(frag(2 * wm, KC * g), q, acc[0]);
+      if (two) mma_sums<XT>(frag(2 * wm + 1, KC * g), q, acc[1]);
     }
     float* p = part + (wn * (wn + 1) / 2 + 2 * wm) * 1024;
-    put(p, acc[0]);
-    if (two) put(p + 1024, acc[1]);
+    put(p, all_sums<XT>(acc[0]));
+    if (two) put(p + 1024, all_sums<XT>(acc[1]));
+  } else {
+    // the 10 upper blocks dealt to 4 wavefronts: blocks wave, wave + 4, wave + 8
+    static_assert(RB == 4 && NW == 4, "block split");
+    f32x16_t acc[3][NS] = {};
+    int bi[3], bj[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int n = min(wave + 4 * t, C::NB - 1);
+      bj[t] = n >= 6 ? 3 : n >= 3 ? 2 : n >= 1 ? 1 : 0;
+      bi[t] = n - bj[t] * (bj[t] + 1) / 2;
+    }
+    const bool third = wave + 8 < C::NB;
+    for (int g = 0; g < nv / KC; ++g) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        if (t < 2 || third) mma_sums<XT>(frag(bi[t], KC * g), frag(bj[t], KC * g), acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < 2 || third) put(part + (wave + 4 * t) * 1024, all_sums<XT>(acc[t]));
   }
 }
 
 // The slice in LDS -> memory, 16 bytes a thread.
-template <int RB>
-__device__ __forceinline__ void slice_store(const char* xs, int nv, uint16_t* X, int L) {
-  using C = SliceCfg<RB>;
-  for (int i = threadIdx.x; i < C::Sx * (C::W / 8); i += 512) {
-    const int r = i / (C::W / 8), ch = i % (C::W / 8);
-    if (8 * ch >= nv) continue;
-    *reinterpret_cast<u32x4_t*>(X + static_cast<int64_t>(r) * L + 8 * ch) =
-        *reinterpret_cast<const u32x4_t*>(xs + slice_at<RB>(r, 8 * ch));
+template <typename XT, class C, int NW>
+__device__ __forceinline__ void slice_store(const char* xs, int nv, XT* X, int L) {
+  constexpr int CPR = C::W / C::EPC;
+  for (int i = threadIdx.x; i < C::Sx * CPR; i += 64 * NW) {
+    const int r = i / CPR, col = i % CPR * C::EPC;
+    if (col >= nv) continue;
+    *reinterpret_cast<u32x4_t*>(X + static_cast<int64_t>(r) * L + col) =
+        *reinterpret_cast<const u32x4_t*>(xs + slice_at<C>(r, col));
   }
 }
 
-// Prologue: momentum in place, u (zero outside the matrix) as bf16 into LDS
+// Prologue: momentum in place, u (zero outside the matrix) into LDS
 // and X, its square sum, the first Gram partial.  RESCALE: the matrices whose
 // r cannot be applied to the products get X0 = r u and its Gram partial
 // instead (the momentum is already advanced); all others return at once.
-template <typename GT, int RB, bool MOM, bool RESCALE>
-__global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
-  using C = SliceCfg<RB>;
+template <typename GT, typename XT, int RB, bool MOM, bool RESCALE>
+__global__ __launch_bounds__(64 * kSliceWaves<XT>) void k_slice_first(SliceArgs sa) {
+  constexpr int NW = kSliceWaves<XT>;
+  using C = SliceCfg<XT, RB, NW>;
   __shared__ __attribute__((aligned(16))) char xs[C::Sx * C::PITCH];
   __shared__ double red[8];
   int m, j;
@@ -2579,7 +2633,7 @@ __global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
   // 8 rows of X (u l x s)
   const int upr = tr ? C::Sx / 8 : nv / 8;                 // units per row of u
   const int nu = tr ? nv * upr : C::Sx * upr;
-  for (int i = threadIdx.x; i < nu; i += 512) {
+  for (int i = threadIdx.x; i < nu; i += 64 * NW) {
     const int a = i / upr, e = (i - a * upr) * 8;
     const int ur = tr ? c0 + a : a, uc = tr ? e : c0 + e;
     float v[8];
@@ -2628,9 +2682,14 @@ __global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
     }
     if (tr) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) *reinterpret_cast<uint16_t*>(xs + slice_at<RB>(e + q, a)) = f32_to_bf16(v[q]);
+      for (int q = 0; q < 8; ++q) *reinterpret_cast<XT*>(xs + slice_at<C>(e + q, a)) = from_f32<XT>(v[q]);
     } else {
-      store8(reinterpret_cast<uint16_t*>(xs + slice_at<RB>(a, e)), 0, v);
+#pragma unroll
+      for (int h = 0; h < 8; h += C::EPC) {
+        XT* p = reinterpret_cast<XT*>(xs + slice_at<C>(a, e + h));
+        if constexpr (C::EPC == 8) store8(p, 0, v);
+        else *reinterpret_cast<float4*>(p) = make_float4(v[h], v[h + 1], v[h + 2], v[h + 3]);
+      }
     }
   }
   if (!RESCALE) {
@@ -2642,18 +2701,18 @@ __global__ __launch_bounds__(512) void k_slice_first(SliceArgs sa) {
   if (!RESCALE && threadIdx.x == 0) {
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) t += red[w];
+    for (int w = 0; w < NW; ++w) t += red[w];
     sa.norm[static_cast<int64_t>(m) * sa.nnorm + j] = t;
   }
-  slice_store<RB>(xs, nv, sa.X + m * sa.matX + c0, sa.L);
-  slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
+  slice_store<XT, C, NW>(xs, nv, static_cast<XT*>(sa.X) + m * sa.matX + c0, sa.L);
+  slice_gram<XT, C, NW>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
 }
 
 // A = sum of the partials (times r^2 on the first step), one 32 x 32 block
 // per workgroup, written on both sides of the diagonal.
-template <int RB>
+template <typename XT, int RB>
 __global__ __launch_bounds__(256) void k_slice_reduce(SliceArgs sa) {
-  using C = SliceCfg<RB>;
+  using C = SliceCfg<XT, RB, kSliceWaves<XT>>;
   __shared__ double red[4];
   const int m = blockIdx.x / C::NB, nb = blockIdx.x % C::NB;
   float scale = 1.f;
@@ -2682,25 +2741,27 @@ __global__ __launch_bounds__(256) void k_slice_reduce(SliceArgs sa) {
   while ((bj + 1) * (bj + 2) / 2 <= nb) ++bj;
   const int bi = nb - bj * (bj + 1) / 2, lane = threadIdx.x & 63;
   const int row = 32 * bi + 8 * (threadIdx.x >> 6) + 4 * (lane >> 5), col = 32 * bj + (lane & 31);
-  uint16_t* A = sa.A + static_cast<int64_t>(m) * C::Sx * C::Sx;
-  const uint2 h = pack_bf16x4(v);
-  *reinterpret_cast<uint2*>(A + col * C::Sx + row) = h;
+  XT* A = static_cast<XT*>(sa.A) + static_cast<int64_t>(m) * C::Sx * C::Sx;
+  using F4 = typename Four<XT>::T;
+  F4 h;
+  set4(h, v);
+  *reinterpret_cast<F4*>(A + col * C::Sx + row) = h;
   if (bi != bj) {
-    A[row * C::Sx + col] = static_cast<uint16_t>(h.x);
-    A[(row + 1) * C::Sx + col] = static_cast<uint16_t>(h.x >> 16);
-    A[(row + 2) * C::Sx + col] = static_cast<uint16_t>(h.y);
-    A[(row + 3) * C::Sx + col] = static_cast<uint16_t>(h.y >> 16);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) A[(row + q) * C::Sx + col] = from_f32<XT>(v[q]);
   }
 }
 
 // FK: -1 a middle step; 0 the last, updating W; 1 the last, writing out (both
 // of dtype PDT).
-template <int RB, int FK, int PDT>
-__global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs sa) {
-  constexpr bool FINAL = FK >= 0;
-  constexpr int NW = FINAL ? 4 : 8;
-  using C = SliceCfg<RB, NW>;
-  constexpr int XB = C::Sx * C::PITCH;                     // 8 KB a wavefront
+template <typename XT, int RB, int FK, int PDT>
+__global__ __launch_bounds__(FK >= 0 ? 256 : 64 * kSliceWaves<XT>, sizeof(XT) == 2 ? 2 : 1)
+void k_slice_step(SliceArgs sa) {
+  constexpr bool FINAL = FK >= 0, BF = sizeof(XT) == 2;
+  constexpr int NW = FINAL ? 4 : kSliceWaves<XT>;
+  using C = SliceCfg<XT, RB, NW>;
+  using F4 = typename Four<XT>::T;
+  constexpr int XB = C::Sx * C::PITCH;                     // 8 KB a wavefront (fp32: 16)
   constexpr int OB = FINAL ? C::Sx * C::W * 4 : 0;         // O of the slice in fp32, over both
   __shared__ __attribute__((aligned(1024))) char smem[OB > XB + C::ABYTES ? OB : XB + C::ABYTES];
   __shared__ double red[4];
@@ -2711,8 +2772,8 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
   const int c0 = j * C::W, nv = min(C::W, sa.L - c0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t lds0 = lds_offset(smem);
-  uint16_t* const X = sa.X + m * sa.matX + c0;
-  const char* const Ag = reinterpret_cast<const char*>(sa.A + static_cast<int64_t>(m) * C::Sx * C::Sx);
+  XT* const X = static_cast<XT*>(sa.X) + m * sa.matX + c0;
+  const char* const Ag = static_cast<const char*>(sa.A) + static_cast<int64_t>(m) * C::ABYTES;
   float osc = 1.f;
   if (sa.first) {
     const double r = slice_r(sa.norm + static_cast<int64_t>(m) * sa.nnorm, sa.nnorm, sa.sc.eps, red);
@@ -2761,36 +2822,54 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
     }
   }
   constexpr int XCH = C::PITCH / 16;                       // chunks of a slice row
+  constexpr int XI = XB / 1024 / NW;                       // instructions of a wavefront
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < XI; ++k) {
     const int t = wave + NW * k, p = t * 64 + lane, r = p / XCH;
     int ch = (p % XCH) ^ slice_key(r);
-    if (8 * ch >= nv) ch &= 15;                            // past the matrix: any chunk of the row (not used)
-    load_lds16(reinterpret_cast<const char*>(X), static_cast<uint32_t>(r) * static_cast<uint32_t>(sa.L * 2) + ch * 16,
+    if (C::EPC * ch >= nv) ch &= 8 * C::ES - 1;            // past the matrix: any chunk of the row (not used)
+    load_lds16(reinterpret_cast<const char*>(X), static_cast<uint32_t>(r) * static_cast<uint32_t>(sa.L * C::ES) + ch * 16,
                lds0 + t * 1024);
   }
   if constexpr (FINAL) {
     read_w();                                              // in flight together with A and the slice
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // A has landed, the slice may not
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(XI) : "memory");  // A has landed, the slice may not
   }
   __syncthreads();
   // ---- B = b A + c A A, in place --------------------------------------------
   constexpr int PB = RB == 4 ? 16 / NW : 1;                // 32 x 32 blocks of B per wavefront
   const int pi = RB == 4 ? PB * (wave >> 2) : wave / RB, pj = RB == 4 ? (wave & 3) : wave % RB;
   const bool pact = RB == 4 || wave < RB * RB;
-  uint2 bh[PB][4];
+  F4 bh[PB][4];
   if (pact) {
-    auto afrag = [&](int rb, int g) {
-      return *reinterpret_cast<const u32x4_t*>(as + slice_a_at<RB>(32 * rb + (lane & 31), 16 * g + 8 * (lane >> 5)));
-    };
     f32x16_t acc[PB] = {};
+    if constexpr (BF) {
+      auto afrag = [&](int rb, int g) {
+        return *reinterpret_cast<const u32x4_t*>(as + slice_a_at<C>(32 * rb + (lane & 31), 16 * g + 8 * (lane >> 5)));
+      };
 #pragma unroll
-    for (int g = 0; g < C::Sx / 16; ++g) {
-      const u32x4_t q = afrag(pj, g);
+      for (int g = 0; g < C::Sx / 16; ++g) {
+        const u32x4_t q = afrag(pj, g);
 #pragma unroll
-      for (int i = 0; i < PB; ++i) Mma<uint16_t>::run(afrag(pi + i, g), q, acc[i]);
+        for (int i = 0; i < PB; ++i) Mma<uint16_t>::run(afrag(pi + i, g), q, acc[i]);
+      }
+    } else {
+      // A is symmetric: the operands' rows at k are row k of A
+      f32x16_t part[PB][kSums] = {};
+      for (int k0 = 0; k0 < C::Sx; k0 += 2 * kSums)
+#pragma unroll
+        for (int t = 0; t < kSums; ++t) {
+          const int k = k0 + 2 * t + (lane >> 5);
+          const float q = *reinterpret_cast<const float*>(as + slice_a_at<C>(k, 32 * pj + (lane & 31)));
+#pragma unroll
+          for (int i = 0; i < PB; ++i)
+            part[i][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                *reinterpret_cast<const float*>(as + slice_a_at<C>(k, 32 * (pi + i) + (lane & 31))), q, part[i][t], 0, 0, 0);
+        }
+#pragma unroll
+      for (int i = 0; i < PB; ++i) acc[i] = add_sums(part[i]);
     }
 #pragma unroll
     for (int i = 0; i < PB; ++i)
@@ -2799,10 +2878,10 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
         // rows row .. row + 3 of column col; A is symmetric, so they lie in row col
         const int row = 32 * (pi + i) + 8 * g + 4 * (lane >> 5), col = 32 * pj + (lane & 31);
         float e[4], v[4];
-        unpack_bf16x4(*reinterpret_cast<const uint2*>(as + slice_a_at<RB>(col, row)), e);
+        get4(*reinterpret_cast<const F4*>(as + slice_a_at<C>(col, row)), e);
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = fmaf(sa.b, e[q], sa.c * acc[i][4 * g + q]);
-        bh[i][g] = pack_bf16x4(v);
+        set4(bh[i][g], v);
       }
   }
   __syncthreads();                                         // every read of A is done
@@ -2812,7 +2891,7 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int row = 32 * (pi + i) + 8 * g + 4 * (lane >> 5), col = 32 * pj + (lane & 31);
-        *reinterpret_cast<uint2*>(as + slice_a_at<RB>(col, row)) = bh[i][g];  // B is symmetric too
+        *reinterpret_cast<F4*>(as + slice_a_at<C>(col, row)) = bh[i][g];  // B is symmetric too
       }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the slice has landed
@@ -2823,21 +2902,46 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
   const int w0 = wave * C::SW;
   f32x16_t acc[CBW][RB] = {};
   if (w0 < nv) {
-    const int G = lane >> 4, Lq = lane & 15;
+    if constexpr (BF) {
+      const int G = lane >> 4, Lq = lane & 15;
 #pragma unroll
-    for (int g = 0; g < C::Sx / 16; ++g) {
-      u32x4_t bf[RB];
+      for (int g = 0; g < C::Sx / 16; ++g) {
+        u32x4_t bf[RB];
 #pragma unroll
-      for (int i = 0; i < RB; ++i)
-        bf[i] = *reinterpret_cast<const u32x4_t*>(as + slice_a_at<RB>(32 * i + (lane & 31), 16 * g + 8 * (lane >> 5)));
+        for (int i = 0; i < RB; ++i)
+          bf[i] = *reinterpret_cast<const u32x4_t*>(as + slice_a_at<C>(32 * i + (lane & 31), 16 * g + 8 * (lane >> 5)));
 #pragma unroll
-      for (int k = 0; k < CBW; ++k) {
-        const int row = 16 * g + 8 * (G >> 1) + (Lq >> 2), col = w0 + 32 * k + 16 * (G & 1) + 4 * (Lq & 3);
-        const uint2 lo = tr_read_b64(xs + slice_at<RB, NW>(row, col)), hi = tr_read_b64(xs + slice_at<RB, NW>(row + 4, col));
-        const u32x4_t xf{lo.x, lo.y, hi.x, hi.y};
+        for (int k = 0; k < CBW; ++k) {
+          const int row = 16 * g + 8 * (G >> 1) + (Lq >> 2), col = w0 + 32 * k + 16 * (G & 1) + 4 * (Lq & 3);
+          const uint2 lo = tr_read_b64(xs + slice_at<C>(row, col)), hi = tr_read_b64(xs + slice_at<C>(row + 4, col));
+          const u32x4_t xf{lo.x, lo.y, hi.x, hi.y};
 #pragma unroll
-        for (int i = 0; i < RB; ++i) Mma<uint16_t>::run(xf, bf[i], acc[k][i]);
+          for (int i = 0; i < RB; ++i) Mma<uint16_t>::run(xf, bf[i], acc[k][i]);
+        }
       }
+    } else {
+      // both operands take row k as it lies (B is symmetric): 32 consecutive floats
+      f32x16_t part[CBW][RB][kSums] = {};
+      for (int k0 = 0; k0 < C::Sx; k0 += 2 * kSums)
+#pragma unroll
+        for (int t = 0; t < kSums; ++t) {
+          const int row = k0 + 2 * t + (lane >> 5);
+          float bf[RB];
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+            bf[i] = *reinterpret_cast<const float*>(as + slice_a_at<C>(row, 32 * i + (lane & 31)));
+#pragma unroll
+          for (int k = 0; k < CBW; ++k) {
+            const float xf = *reinterpret_cast<const float*>(xs + slice_at<C>(row, w0 + 32 * k + (lane & 31)));
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+              part[k][i][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf, bf[i], part[k][i][t], 0, 0, 0);
+          }
+        }
+#pragma unroll
+      for (int k = 0; k < CBW; ++k)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) acc[k][i] = add_sums(part[k][i]);
     }
 #pragma unroll
     for (int k = 0; k < CBW; ++k)
@@ -2846,23 +2950,23 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int row = 32 * i + (lane & 31), col = w0 + 32 * k + 8 * g + 4 * (lane >> 5);
-          char* p = xs + slice_at<RB, NW>(row, col);
+          F4* p = reinterpret_cast<F4*>(xs + slice_at<C>(row, col));
           float e[4], v[4];
-          unpack_bf16x4(*reinterpret_cast<const uint2*>(p), e);
+          get4(*p, e);
 #pragma unroll
           for (int q = 0; q < 4; ++q) v[q] = osc * fmaf(sa.a, e[q], acc[k][i][4 * g + q]);
           if constexpr (FINAL) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[k][i][4 * g + q] = v[q];
           } else {
-            *reinterpret_cast<uint2*>(p) = pack_bf16x4(v);
+            set4(*p, v);
           }
         }
   }
   __syncthreads();
   if constexpr (!FINAL) {
-    slice_store<RB>(xs, nv, X, sa.L);
-    slice_gram<RB>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
+    slice_store<XT, C, NW>(xs, nv, X, sa.L);
+    slice_gram<XT, C, NW>(xs, nv, sa.part + (static_cast<int64_t>(m) * sa.np + j * C::PPS) * (C::NB * 1024));
   } else {
     // ---- the parameter (or output): O in fp32 through LDS in the parameter's
     // layout, whole rows back --------------------------------------------------------
@@ -2905,10 +3009,12 @@ __global__ __launch_bounds__(FK >= 0 ? 256 : 512, 2) void k_slice_step(SliceArgs
   }
 }
 
-template <typename GT, int RB>
+template <typename GT, typename XT, int RB>
 hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb, const StepScalars& sc,
                       const float* coeffs, int K, hipStream_t st) {
-  using C = SliceCfg<RB>;
+  constexpr int NW = kSliceWaves<XT>;
+  using C = SliceCfg<XT, RB, NW>;
+  using CF = SliceCfg<XT, RB, 4>;                          // the last step's slices
   SliceArgs sa{};
   sa.desc = d_desc;
   sa.sc = sc;
@@ -2916,46 +3022,46 @@ hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuf
   sa.nsl = (cg.L + C::W - 1) / C::W;
   sa.nnorm = sa.nsl;
   sa.np = C::KSPLIT ? cg.L / C::SW : sa.nsl;
-  sa.X = static_cast<uint16_t*>(wb.X[0]);
+  sa.X = wb.X[0];
   sa.matX = static_cast<int64_t>(cg.S) * cg.L;
   sa.part = static_cast<float*>(wb.X[1]);                  // over X[1], XT[0] and XT[1]
-  sa.A = static_cast<uint16_t*>(wb.A);
+  sa.A = wb.A;
   sa.norm = wb.partials;
   sa.nmat = cg.nmat;
   const unsigned mats = cg.nmat < 8 ? cg.nmat : (cg.nmat + 7) / 8 * 8;
   const dim3 slices(static_cast<unsigned>(sa.nsl) * mats);
   const dim3 blocks(static_cast<unsigned>(C::NB) * static_cast<unsigned>(cg.nmat));
   if (sc.momentum) {
-    hipLaunchKernelGGL((k_slice_first<GT, RB, true, false>), slices, dim3(512), 0, st, sa);
-    hipLaunchKernelGGL((k_slice_first<GT, RB, true, true>), slices, dim3(512), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, XT, RB, true, false>), slices, dim3(64 * NW), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, XT, RB, true, true>), slices, dim3(64 * NW), 0, st, sa);
   } else {
-    hipLaunchKernelGGL((k_slice_first<GT, RB, false, false>), slices, dim3(512), 0, st, sa);
-    hipLaunchKernelGGL((k_slice_first<GT, RB, false, true>), slices, dim3(512), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, XT, RB, false, false>), slices, dim3(64 * NW), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_first<GT, XT, RB, false, true>), slices, dim3(64 * NW), 0, st, sa);
   }
   for (int k = 0; k < K; ++k) {
     sa.first = k == 0 ? 1 : 0;
     sa.a = coeffs[3 * k]; sa.b = coeffs[3 * k + 1]; sa.c = coeffs[3 * k + 2];
-    hipLaunchKernelGGL((k_slice_reduce<RB>), blocks, dim3(256), 0, st, sa);
-    if (k + 1 < K) hipLaunchKernelGGL((k_slice_step<RB, -1, DT_BF16>), slices, dim3(512), 0, st, sa);
+    hipLaunchKernelGGL((k_slice_reduce<XT, RB>), blocks, dim3(256), 0, st, sa);
+    if (k + 1 < K) hipLaunchKernelGGL((k_slice_step<XT, RB, -1, DT_BF16>), slices, dim3(64 * NW), 0, st, sa);
   }
   const bool o = sc.final_kind != 0, f32 = cg.param_dtype == DT_F32;
-  sa.nsl = (cg.L + C::W / 2 - 1) / (C::W / 2);
+  sa.nsl = (cg.L + CF::W - 1) / CF::W;
   const dim3 halves(static_cast<unsigned>(sa.nsl) * mats);
-  if (!o && !f32) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_BF16>), halves, dim3(256), 0, st, sa);
-  else if (!o) hipLaunchKernelGGL((k_slice_step<RB, 0, DT_F32>), halves, dim3(256), 0, st, sa);
-  else if (!f32) hipLaunchKernelGGL((k_slice_step<RB, 1, DT_BF16>), halves, dim3(256), 0, st, sa);
-  else hipLaunchKernelGGL((k_slice_step<RB, 1, DT_F32>), halves, dim3(256), 0, st, sa);
+  if (!o && !f32) hipLaunchKernelGGL((k_slice_step<XT, RB, 0, DT_BF16>), halves, dim3(256), 0, st, sa);
+  else if (!o) hipLaunchKernelGGL((k_slice_step<XT, RB, 0, DT_F32>), halves, dim3(256), 0, st, sa);
+  else if (!f32) hipLaunchKernelGGL((k_slice_step<XT, RB, 1, DT_BF16>), halves, dim3(256), 0, st, sa);
+  else hipLaunchKernelGGL((k_slice_step<XT, RB, 1, DT_F32>), halves, dim3(256), 0, st, sa);
   return hipGetLastError();
 }
 
-template <typename GT>
+template <typename GT, typename XT>
 hipError_t run_sliced_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb, const StepScalars& sc,
                             const float* coeffs, int K, hipStream_t st, LaunchTimer* timer) {
   Timed tm(timer, KK_SMALL, st);
   const int Sx = cg.s <= 32 ? 32 : cg.s <= 64 ? 64 : 128;
-  const hipError_t e = Sx == 32   ? run_slices<GT, 1>(cg, d_desc, wb, sc, coeffs, K, st)
-                       : Sx == 64 ? run_slices<GT, 2>(cg, d_desc, wb, sc, coeffs, K, st)
-                                  : run_slices<GT, 4>(cg, d_desc, wb, sc, coeffs, K, st);
+  const hipError_t e = Sx == 32   ? run_slices<GT, XT, 1>(cg, d_desc, wb, sc, coeffs, K, st)
+                       : Sx == 64 ? run_slices<GT, XT, 2>(cg, d_desc, wb, sc, coeffs, K, st)
+                                  : run_slices<GT, XT, 4>(cg, d_desc, wb, sc, coeffs, K, st);
   if (e != hipSuccess) return e;
   const double nm = cg.nmat, s = cg.s, l = cg.l, L = cg.L;
   const double gsz = sizeof(GT), psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
@@ -3233,8 +3339,11 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
                      LaunchTimer* timer) {
   const bool gbf = cg.grad_dtype == DT_BF16;
   if (chunk_is_sliced(cg.s, cg.l, cg.ns_f32 != 0, K)) {
-    return gbf ? run_sliced_chunk<uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer)
-               : run_sliced_chunk<float>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+    if (cg.ns_f32)
+      return gbf ? run_sliced_chunk<uint16_t, float>(cg, d_desc, wb, sc, coeffs, K, st, timer)
+                 : run_sliced_chunk<float, float>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+    return gbf ? run_sliced_chunk<uint16_t, uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer)
+               : run_sliced_chunk<float, uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer);
   }
   if (cg.ns_f32 && !wb.sync && chunk_on_tiles(cg.S, cg.L, K)) {
     return gbf ? run_chunk_t<uint16_t, Split3>(cg, d_desc, wb, sc, coeffs, K, st, timer)

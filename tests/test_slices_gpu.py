@@ -1,8 +1,8 @@
-"""bf16 Newton-Schulz of short sides up to 128 in column slices: the edges of
+"""Newton-Schulz of short sides up to 128 in column slices, bf16 and fp32: the edges of
 the row blocks (32, 64, 128) and of the slices (256, 512, 1024 columns, and a
 last one of 128), both orientations, K = 1 and 5, norms that the first step's
 products cannot take (out of [2^-40, 2^40]), strided views, W rows with and
-without vector accesses, against the oracle with the gates of the bf16 path;
+without vector accesses, against the oracle with the gates of the path;
 and each result in a batch bit for bit the one it has alone.
 
 A wide matrix of few rows has nearly equal singular values, which take the
@@ -21,7 +21,7 @@ from tests.gpu_util import MOMENTUM_TOL, decode, o_gate, rel, require_gpu, to_bi
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(16, 257), (17, 1030), (32, 2100), (33, 400), (64, 385), (64, 1100), (65, 260), (100, 700), (128, 257),
-          (128, 1152), (1300, 24), (600, 50), (520, 128), (300, 127)]
+          (128, 1152), (1300, 24), (128, 640), (40, 513), (1029, 32), (600, 50), (520, 128), (300, 127)]
 
 
 @pytest.fixture(scope="module")
@@ -37,30 +37,33 @@ def rng(*key):
     return np.random.Generator(np.random.PCG64(np.random.SeedSequence([synth.ROOT_SEED, 8600, *key])))
 
 
+@pytest.mark.parametrize("prec", ["bf16", "f32"])
 @pytest.mark.parametrize("steps", [5, 1])
 @pytest.mark.parametrize("scale", [1.0, 1e14, 1e-14])
-def test_slices_match_oracle_and_do_not_depend_on_the_batch(muon, steps, scale):
+def test_slices_match_oracle_and_do_not_depend_on_the_batch(muon, steps, scale, prec):
     import torch
     G = [synth.draw(s, 1.0, "f32", rng(steps, i)) * np.float32(scale) for i, s in enumerate(SHAPES)]
     ins = [to_dev(g, "f32") for g in G for _ in range(3)]
     outs = [torch.full_like(t, float("nan")) for t in ins]
-    muon.orthogonalize(ins, outs, ns_steps=steps)
+    muon.orthogonalize(ins, outs, ns_steps=steps, ns_precision=prec)
     torch.cuda.synchronize()
     for i, (s, g) in enumerate(zip(SHAPES, G)):
         one = torch.full_like(ins[3 * i], float("nan"))
-        muon.orthogonalize([ins[3 * i]], [one], ns_steps=steps)
+        muon.orthogonalize([ins[3 * i]], [one], ns_steps=steps, ns_precision=prec)
         torch.cuda.synchronize()
         for k in range(3):
             assert np.array_equal(to_bits(outs[3 * i + k]), to_bits(one)), (s, k)
         x = decode(g, "f32")
-        err, gate = o_gate(to_host(one), ref.orthogonalize(x, steps), "f32", "bf16", steps, G=x)
-        gate = max(gate, FEW_SV_MARGIN * storage_error(x, steps))
-        print(f"slices K={steps} x{scale:g} {s}: O err {err:.2e}", flush=True)
+        err, gate = o_gate(to_host(one), ref.orthogonalize(x, steps), "f32", prec, steps, G=x)
+        if prec == "bf16":
+            gate = max(gate, FEW_SV_MARGIN * storage_error(x, steps))
+        print(f"slices {prec} K={steps} x{scale:g} {s}: O err {err:.2e}", flush=True)
         assert err <= gate, (s, err, gate)
 
 
+@pytest.mark.parametrize("prec", ["bf16", "f32"])
 @pytest.mark.parametrize("pdt,gdt", [("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")])
-def test_slices_step_matches_oracle(muon, pdt, gdt):
+def test_slices_step_matches_oracle(muon, pdt, gdt, prec):
     import torch
     hp = ref.MuonHParams(lr=0.02, beta=0.95, weight_decay=0.1, nesterov=True)
     Ws = [synth.draw(s, 0.02, pdt, rng(30, i, 0)) for i, s in enumerate(SHAPES)]
@@ -74,7 +77,7 @@ def test_slices_step_matches_oracle(muon, pdt, gdt):
         return big, big[:, :t.shape[1]]
 
     vW, vg, vb = [[wide(t) for t in ts] for ts in (dW, dg, db)]
-    kw = dict(lr=hp.lr, beta=hp.beta, weight_decay=hp.weight_decay)
+    kw = dict(lr=hp.lr, beta=hp.beta, weight_decay=hp.weight_decay, ns_precision=prec)
     muon.step(dW, dg, db, **kw)
     muon.step([v for _, v in vW], [v for _, v in vg], [v for _, v in vb], **kw)
     torch.cuda.synchronize()
@@ -82,9 +85,10 @@ def test_slices_step_matches_oracle(muon, pdt, gdt):
         W0 = decode(W, pdt)
         r = ref.muon_step_matrix(W0, decode(g, gdt), np.asarray(b, np.float64), hp)
         err, rho = w_gate(to_host(w_dev), r.W_new, W0, pdt)
-        print(f"slices step {pdt}/{gdt} {s}: W err {err:.2e} (rho {rho:.1e})", flush=True)
+        print(f"slices step {pdt}/{gdt} {prec} {s}: W err {err:.2e} (rho {rho:.1e})", flush=True)
         u = 0.05 * decode(g, gdt) + 0.95 * r.buf_new
-        assert err <= max(tol_for("bf16", s), FEW_SV_MARGIN * storage_error(u)) + rho, (s, err, rho)
+        gate = tol_for(prec, s) if prec == "f32" else max(tol_for(prec, s), FEW_SV_MARGIN * storage_error(u))
+        assert err <= gate + rho, (s, err, gate, rho)
         assert rel(to_host(b_dev), r.buf_new) <= MOMENTUM_TOL, s
         assert np.array_equal(to_bits(w_view.contiguous()), to_bits(w_dev)), s
         assert np.array_equal(to_bits(b_view.contiguous()), to_bits(b_dev)), s
