@@ -323,7 +323,8 @@ muon_status_t muon_plan_step(const muon_param_t* params, int64_t n, const muon_h
  * whose r is too large or small to be applied in the first products),
  * gram_syrk, poly_syrk, update_gemm, update_apply_gemm,
  * apply_x0, adamw, ns_small (the whole step of a chunk whose short side is
- * at most 128 with fp32 Newton-Schulz, in one fused launch).  `reset` != 0
+ * at most 128, counted as one launch).  exec_flops of fp32 Newton-Schulz on
+ * the tile kernel counts its six bf16 products.  `reset` != 0
  * clears the counters after reading. */
 typedef struct {
   const char* name;

@@ -6,14 +6,16 @@
 //   k_finalize   r = 1 / (||u||_F + eps) per matrix (fixed-order sum)
 //   k_rescale    X0 = r*u for the rare matrices whose r the first products
 //                cannot apply (see k_finalize); others exit at once
-//   k_gemm_tile  the three contractions of Eq. (1) on MFMA, 256 x 256 tiles
-//                (bf16; S and L multiples of 256):
+//   k_gemm_tile  the three contractions of Eq. (1) on MFMA, 256 x 256 or
+//                128 x 128 tiles (bf16, or fp32 as three bf16 planes):
 //                  A  = X X^T          (Gram, upper-triangle tiles only)
 //                  B  = b A + c A A    (A is symmetric, so A A = A A^T)
 //                  X' = a X + B X      (X read K-major by transposing LDS reads)
 //                the last step's epilogue applies the update to W directly;
-//   k_gemm_nt    the same on 128 x 128 tiles (fp32 NS and other extents;
-//                writes mirrored A and B and reads X^T);
+//   k_gemm_nt    the same on 128 x 128 tiles for rows past the tile kernel's
+//                offsets (writes mirrored A and B and reads X^T);
+//   k_slice_*    short sides up to 128 in column slices; k_ns_small the
+//                smallest of them in one launch;
 //   k_apply_x0   the update from X0 when K = 0;
 //   k_adamw      AdamW for the parameters Muon does not take.
 //
@@ -647,7 +649,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_nt(GemmArgs ga) {
 
 // ---------------------------------------------------------------------------
 // bf16 C = P Q^T with a 256 x 256 output tile per workgroup (M and N
-// multiples of 256).  512 threads = 8 wavefronts in a 2 x 4 grid, each owning
+// multiples of 128).  512 threads = 8 wavefronts in a 2 x 4 grid, each owning
 // a 128 x 64 sub-tile = 4 x 2 blocks of v_mfma_f32_32x32x16_bf16, so every
 // operand fragment read from LDS feeds two or four MFMAs.
 //
@@ -1944,8 +1946,8 @@ bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
   return cost1 < cost2;
 }
 
-// The products on the 128 x 128 kernel: fp32 Newton-Schulz, and bf16 rows
-// past the 256 x 256 kernel's 32-bit offsets (chunk_on_tiles).
+// The products on k_gemm_nt: rows past the tile kernel's 32-bit offsets
+// (chunk_on_tiles).
 template <typename T>
 hipError_t launch_gemm(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(ga.tiles_per_mat) * nmat), block(256);
