@@ -133,8 +133,8 @@ inline bool chunk_keeps_xt(int64_t S, int64_t L, bool ns_f32, int K) {
 // shape and precision alone, so that a matrix gets the same bits in any batch:
 //  - as one fused launch (k_ns_small: momentum, norm, every Newton-Schulz step
 //    and the update, the workgroups of a matrix meeting at barriers): K = 0,
-//    bf16 matrices of at most 64 x 384 or 128 x 256, fp32 ones of at most 64 x
-//    512 or 128 x 1024;
+//    bf16 matrices of at most 32 x 256 or 128 x 384, fp32 ones of at most 32 x
+//    512, 64 x 768 or 128 x 1024;
 //  - as column slices (k_slice_*: two launches a step over all matrices): the
 //    others, with at least one step.
 // Measured on an MI355X (us per orthogonalisation, fused / slices), bf16: one
@@ -155,7 +155,8 @@ inline bool chunk_reserves_small(int64_t s, int64_t l, bool ns_f32) {
 }
 inline bool chunk_is_small(int64_t s, int64_t l, bool ns_f32, int K) {
   if (!chunk_reserves_small(s, l, ns_f32)) return false;
-  return K == 0 || l <= (ns_f32 ? (s > 64 ? 1024 : 512) : s <= 32 || s > 64 ? 256 : 384);
+  if (K == 0) return true;
+  return l <= (ns_f32 ? (s <= 32 ? 512 : s <= 64 ? 768 : 1024) : s <= 32 ? 256 : 384);
 }
 inline bool chunk_is_sliced(int64_t s, int64_t l, bool ns_f32, int K) {
   return s <= 128 && K > 0 && tile_rows_fit(128, round_up(l, kPad), ns_f32 ? 4 : 2) && !chunk_is_small(s, l, ns_f32, K);
