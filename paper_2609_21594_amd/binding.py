@@ -232,7 +232,7 @@ def _plain_params(params, grads, moms):
     arr = (MuonParam * len(params))()
     at = 0
     for W, g, m in zip(params, grads, moms):
-        if W.__class__ is RowBlocks or g.__class__ is RowBlocks or m.__class__ is RowBlocks:
+        if isinstance(W, RowBlocks) or isinstance(g, RowBlocks) or isinstance(m, RowBlocks):
             return None
         shape = W.shape
         nd = len(shape)

@@ -100,3 +100,17 @@ def test_plain_entries_pack_the_same_structs_as_the_general_path():
         assert B._plain_params(*bad) is None
         with pytest.raises((ValueError, TypeError)):
             B.params_array(*bad)
+
+
+def test_subclass_of_row_blocks_takes_the_general_path():
+    import torch
+    from paper_2609_21594_amd import binding as B
+
+    class Heads(B.RowBlocks):
+        pass
+
+    for wrap in (B.RowBlocks, Heads):
+        W, g, m = torch.zeros(2, 3, 2, 6)[:, 0], torch.zeros(2, 3, 2, 6)[:, 0], torch.zeros(4, 6)
+        for momentum in (m, wrap(torch.zeros(2, 3, 2, 6)[:, 0])):
+            arr, _ = B.params_array([wrap(W)], [wrap(g)], [momentum])
+            assert (arr[0].rows, arr[0].cols) == (4, 6)
