@@ -74,9 +74,9 @@ struct ChunkBuffers {
   void* B;              // S x S
   double* partials;     // nmat x norm_tiles(S, L) (at least kSmallMaxGroup), sums of u^2 in fp64
   unsigned* sync;       // group counters of the fused small-matrix launch (chunk_is_small), or null
-  double* rscale;       // nmat: r = 1 / (||u||_F + eps), fp64
+  double* rscale;       // nmat: what k_rescale multiplies u by (1: not at all), fp64
   float* xscale;        // nmat: the scale the first Newton-Schulz step applies
-                        // to X: r, or 1 where X already holds r*u
+                        // to X: r = 1 / (||u||_F + eps), or 1 where X already holds r*u
 };
 
 struct StepScalars {

@@ -346,14 +346,23 @@ __global__ __launch_bounds__(256) void k_prologue(const MatDesc* __restrict__ de
   write_transposed<XT>(tile, t);
 }
 
-// r = 1 / (sqrt(sum of partials) + eps), one workgroup per matrix, in fp64,
-// and the scale the first products apply: r itself while X~ X~^T stays well
-// inside the fp32 range (||u|| between 2^-40 and 2^40), else 1 (k_rescale
-// then writes r*u into X instead).  1024 threads each sum every 1024th
+// r = 1 / (sqrt(sum of partials) + eps), one workgroup per matrix, in fp64;
+// xscale, the scale the first products apply, and rscale, what k_rescale
+// multiplies u by (1: nothing to do).  While r is between 2^-40 and 2^40, X~
+// X~^T stays well inside the fp32 range: xscale = r, rscale = 1.  Else X0 =
+// r*u is written out: xscale = 1, rscale = r.
+// Three planes (split) hold 24 bits of a value down to 2^-110 only, where
+// plain fp32 holds them down to 2^-126.  When X0's norm is below 2^-60, X is
+// therefore kept times 2^40 through all steps (k_rescale writes 2^40 r u; the
+// Gram products and the last step take 2^-40, see gemm_tile_body): at that
+// size the products add nothing to a*X, and X X^T stays finite while X grows.
+// rscale = -2^40 r marks such a matrix.  1024 threads each sum every 1024th
 // partial into four accumulators (independent loads in flight; an 8192 x
 // 28672 matrix has 57344 partials), combined in a fixed order.
+constexpr float kTinyScale = 0x1p-40f;
 __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ partials, int nparts, float eps,
-                                                   double* __restrict__ rscale, float* __restrict__ xscale) {
+                                                   int split, double* __restrict__ rscale,
+                                                   float* __restrict__ xscale) {
   __shared__ double red16[16];
   const int m = blockIdx.x;
   const double* p = partials + static_cast<int64_t>(m) * nparts;
@@ -375,25 +384,28 @@ __global__ __launch_bounds__(1024) void k_finalize(const double* __restrict__ pa
 #pragma unroll
   for (int w = 0; w < 16; ++w) s += red16[w];
   if (threadIdx.x == 0) {
-    const double r = 1.0 / (sqrt(s) + static_cast<double>(eps));
-    rscale[m] = r;
-    xscale[m] = (r >= 0x1p-40 && r <= 0x1p40) ? static_cast<float>(r) : 1.0f;  // NaN fails both tests
+    const double n = sqrt(s), r = 1.0 / (n + static_cast<double>(eps));
+    const bool folds = r >= 0x1p-40 && r <= 0x1p40;        // NaN fails both tests
+    const bool tiny = split && n > 0.0 && n * r < 0x1p-60;
+    rscale[m] = tiny ? -(r * 0x1p40) : folds ? 1.0 : r;
+    xscale[m] = tiny ? kTinyScale : folds ? static_cast<float>(r) : 1.0f;
   }
 }
 
-// X0 = r*u, written over X~, for the matrices whose scale k_finalize left at
-// 1 (a norm outside the range above, zero with eps = 0, or NaN); every other
-// matrix's workgroups return at once.  The momentum is already advanced.
+// |rscale| u, written over X~, for the matrices that k_finalize says need it (a
+// norm outside the range above, zero with eps = 0, NaN, or tiny in three
+// planes); every other matrix's workgroups return at once.  The momentum is
+// already advanced.
 // grid = (workgroups per matrix, matrices); each loops over its tiles.
 template <typename GT, typename XT, bool MOM>
 __global__ __launch_bounds__(256) void k_rescale(const MatDesc* __restrict__ desc, const double* __restrict__ rscale,
-                                                 const float* __restrict__ xscale, StepScalars sc, ChunkGeom cg,
+                                                 StepScalars sc, ChunkGeom cg,
                                                  typename Store<XT>::E* __restrict__ X,
                                                  typename Store<XT>::E* __restrict__ XTb) {
   __shared__ typename Store<XT>::L tile[64 * TileStage<typename Store<XT>::L>::LDT];
   const int m = blockIdx.y;
-  const double r = rscale[m];
-  if (xscale[m] != 1.0f || r == 1.0) return;  // uniform over the block
+  const double r = fabs(rscale[m]);
+  if (r == 1.0) return;  // uniform over the block
   float s1, s2;
   split_scale(r, s1, s2);
   const MatDesc md = desc[m];
@@ -456,6 +468,7 @@ struct GemmArgs {
   // First Newton-Schulz step: X holds X~ = u unscaled, and the product is
   // scaled per matrix by xscale (the Gram product by its square); null after.
   const float* xscale;
+  const double* rscale;                          // SPLIT kernels, every step: negative marks a tiny matrix (k_finalize)
 };
 
 constexpr int kRowBytes = 144;                   // 128 data + 16 pad per LDS row
@@ -1129,12 +1142,15 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
       }
   }
   // The factor the accumulators leave with: c for a polynomial; on the first step, whose X holds u unscaled,
-  // r^2 for the Gram product and r for the update products.
+  // r^2 for the Gram product and r for the update products.  A tiny matrix's X is 2^40 times the iterate in
+  // every step but the last's output.
   float osc = 1.f;
   if (EPI == EPI_POLY) {
     osc = ga.beta;
-  } else if (ga.xscale) {
-    const float r = ga.xscale[mat];
+  } else {
+    float r = ga.xscale ? ga.xscale[mat] : 1.f;
+    if constexpr (SPLIT)
+      if (ga.rscale[mat] < 0.0) r = EPI == EPI_UPDATE ? 1.f : kTinyScale;
     osc = EPI == EPI_GRAM ? r * r : r;
   }
   const float alpha = SPLIT && EUPD ? ga.alpha * osc : ga.alpha;
@@ -3163,8 +3179,8 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
   }
   {
     Timed tm(timer, KK_FINALIZE, st);
-    hipLaunchKernelGGL(k_finalize, dim3(nmat), dim3(1024), 0, st, wb.partials, nparts, sc.eps, wb.rscale,
-                       wb.xscale);
+    hipLaunchKernelGGL(k_finalize, dim3(nmat), dim3(1024), 0, st, wb.partials, nparts, sc.eps,
+                       std::is_same<XT, Split3>::value ? 1 : 0, wb.rscale, wb.xscale);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     tm.done(0, 0, nm * nparts * 8.0 + nm * 12.0);
   }
@@ -3172,11 +3188,10 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
     Timed tm(timer, KK_NORMALIZE, st);
     const dim3 grid(64, nmat);
     if (sc.momentum)
-      hipLaunchKernelGGL((k_rescale<GT, XT, true>), grid, dim3(256), 0, st, d_desc, wb.rscale, wb.xscale, sc, cg,
-                         x0, xt0);
+      hipLaunchKernelGGL((k_rescale<GT, XT, true>), grid, dim3(256), 0, st, d_desc, wb.rscale, sc, cg, x0, xt0);
     else
-      hipLaunchKernelGGL((k_rescale<GT, XT, false>), grid, dim3(256), 0, st, d_desc, wb.rscale, wb.xscale, sc,
-                         cg, x0, xt0);
+      hipLaunchKernelGGL((k_rescale<GT, XT, false>), grid, dim3(256), 0, st, d_desc, wb.rscale, sc, cg, x0,
+                         xt0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     tm.done(0, 0, nm * 12.0);  // nothing else unless a norm is out of range
   }
@@ -3229,6 +3244,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   const char* XTc = static_cast<const char*>(wb.XT[cur]);
   // A = X X^T: M = N = S, K = L.
   GemmArgs& g = r.gram;
+  GemmArgs& u = r.upd;
   g.P = X; g.p_mat = matX; g.ldp = cg.L * es;
   g.Q = X; g.q_mat = matX; g.ldq = cg.L * es;
   g.k_slabs = cg.L * es / 128;
@@ -3236,6 +3252,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   g.C = static_cast<char*>(wb.A); g.c_mat = matA; g.ldc = cg.S * es;
   g.p_plane = g.q_plane = planeX; g.c_plane = planeA;
   g.xscale = k == 0 ? wb.xscale : nullptr;  // A0 = r^2 X~ X~^T
+  g.rscale = u.rscale = planes == 3 ? wb.rscale : nullptr;
   // Under qtr every consumer of A and B runs on the 256 x 256 kernel and
   // reads them as upper-triangle tiles (mode 1): no mirrored tile is
   // written.  Otherwise the lower triangle is written as the mirror.
@@ -3256,7 +3273,6 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * pairs * upper * Sp; r.b[1] = nm * 2 * s * s * xsz;
   // X' = a X + B X: M = S, N = L, K = S.  The second operand is X^T (N x K,
   // K contiguous) on the 128 x 128 kernel, X itself (K x N) under qtr.
-  GemmArgs& u = r.upd;
   u.P = static_cast<const char*>(wb.B); u.p_mat = matA; u.ldp = cg.S * es;
   if (qtr) {
     u.Q = X; u.q_mat = matX; u.ldq = cg.L * es;
