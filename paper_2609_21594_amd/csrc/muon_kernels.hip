@@ -1949,6 +1949,13 @@ bool deep_tiles(const GemmArgs& ga, int nmat) {
 // Measured per launch, 256 / 128: Gram of 2048 x 5632, three matrices 119 / 89,
 // one 114 / 73; update of 512 x 512, one matrix 21 / 12, 256 matrices 104 /
 // 122; update of 4096 x 11008 319 / 387; Gram of 768 x 768, 48 matrices 54 / 39.
+// The smaller tiles are taken where the model says they save a tenth: nearer
+// ties are within its error, and in a call on two streams the other stream's
+// work would have used the CUs that 256 x 256 tiles leave idle, while 128 x 128
+// tiles load twice as much (two streams, 2 x 4096^2 and 4096 x 11008, whose
+// Gram and polynomial are at 0.96: 5.40 ms on the small tiles, 5.23 on the
+// large; 3 and 2 of them 9.36 and 8.95; no other of 34 calls moved by more
+// than the runs differ, and at 0.65 several lost 5 to 60%).
 bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
   const int64_t m2 = (ga.tiles_m + 1) / 2, n2 = (ga.tiles_n + 1) / 2;
   const double t1 = double(nmat) * double(quarter_tiles(ga));
@@ -1959,7 +1966,7 @@ bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
   const double cost2 = rounds2 * ((1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f);
   double cost1 = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
   if (!split && deep_tiles(ga, nmat)) cost1 = 0.6 * nk + 4.0;
-  return cost1 < cost2;
+  return cost1 < 0.9 * cost2;
 }
 
 // The products on k_gemm_nt: rows past the tile kernel's 32-bit offsets
