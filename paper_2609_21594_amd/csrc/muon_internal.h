@@ -134,15 +134,27 @@ inline bool chunk_keeps_xt(int64_t S, int64_t L, bool ns_f32, int K) {
 //  - as one fused launch (k_ns_small: momentum, norm, every Newton-Schulz step
 //    and the update, the workgroups of a matrix meeting at barriers): K = 0,
 //    bf16 matrices of at most 32 x 256 or 128 x 384, fp32 ones of at most 32 x
-//    512, 64 x 768 or 128 x 1024;
+//    576, 64 x 768, 96 x 1536 or 128 x 1408;
 //  - as column slices (k_slice_*: two launches a step over all matrices): the
 //    others, with at least one step.
-// Measured on an MI355X (us per orthogonalisation, fused / slices), bf16: one
-// 16 x 128 38 / 40, 16 x 1024 97 / 48, 64 x 300 56 / 62, 64 x 512 63 / 63,
-// 128 x 256 51 / 76, 128 x 512 71 / 74; 64 matrices of 64 x 300 121 / 130, of
-// 64 x 512 150 / 135, of 128 x 512 288 / 142, of 64 x 4096 1029 / 181.  fp32:
-// one 16 x 1024 123 / 83, 128 x 1024 161 / 202, 64 x 2048 247 / 119, 128 x 4096
-// 701 / 227; 64 of 64 x 4096 1426 / 454, of 128 x 2048 1622 / 868.
+// The lines lie where one matrix takes as long either way (within 5%), since a
+// loop over single matrices has nothing else to gain from; many matrices gain
+// from slices before that.  Measured on an MI355X at the lines (us per
+// orthogonalisation, fused / slices):
+//   bf16, one matrix:   32 x 256 44 / 49, 257 53 / 47; 64 x 384 59 / 56, 385 65 /
+//                       65; 128 x 384 65 / 69, 392 72 / 71
+//   fp32, one matrix:   32 x 576 87 / 82, 577 89 / 94; 64 x 768 112 / 110, 769
+//                       122 / 122; 96 x 1536 210 / 216, 1537 217 / 226; 128 x
+//                       1408 212 / 217, 1416 217 / 219
+//   16 matrices, bf16:  32 x 257 54 / 59, 64 x 385 71 / 70, 128 x 392 83 / 76
+//                fp32:  32 x 577 90 / 96, 64 x 769 128 / 130, 96 x 1152 194 / 235,
+//                       1536 270 / 243, 128 x 1152 239 / 238, 1408 289 / 242
+//   64 matrices, bf16:  64 x 385 141 / 93, 128 x 392 279 / 95
+//                fp32:  64 x 768 272 / 140, 96 x 1025 713 / 655, 1536 1095 / 657,
+//                       128 x 1408 1123 / 658
+// bf16 65 to 128 rows change at 384 although one matrix whose rows are no whole
+// 16 bytes loses up to 9% from there to 512 (96 x 417 71 / 75): 64 of them take
+// a third of the time (285 / 97).
 // The fused launch needs group counters (kSmallSyncBytes) and kSmallMaxGroup
 // norm partials per matrix.  chunk_reserves_small says which chunks reserve
 // them: also some that now run as slices, since what a call needs of a
@@ -156,7 +168,8 @@ inline bool chunk_reserves_small(int64_t s, int64_t l, bool ns_f32) {
 inline bool chunk_is_small(int64_t s, int64_t l, bool ns_f32, int K) {
   if (!chunk_reserves_small(s, l, ns_f32)) return false;
   if (K == 0) return true;
-  return l <= (ns_f32 ? (s <= 32 ? 512 : s <= 64 ? 768 : 1024) : s <= 32 ? 256 : 384);
+  if (!ns_f32) return l <= (s <= 32 ? 256 : 384);
+  return l <= (s <= 32 ? 576 : s <= 64 ? 768 : s <= 96 ? 1536 : 1408);
 }
 inline bool chunk_is_sliced(int64_t s, int64_t l, bool ns_f32, int K) {
   return s <= 128 && K > 0 && tile_rows_fit(128, round_up(l, kPad), ns_f32 ? 4 : 2) && !chunk_is_small(s, l, ns_f32, K);

@@ -21,7 +21,8 @@ from tests.gpu_util import MOMENTUM_TOL, decode, o_gate, rel, require_gpu, to_bi
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(16, 257), (17, 1030), (32, 2100), (33, 400), (64, 385), (64, 1100), (65, 390), (100, 700), (128, 385),
-          (128, 1152), (1300, 24), (128, 640), (40, 513), (1029, 32), (600, 50), (520, 128), (400, 127), (100, 1100), (60, 800)]
+          (128, 1152), (1300, 24), (128, 640), (40, 513), (1029, 32), (600, 50), (520, 128), (400, 127), (100, 1100), (60, 800),
+          (30, 577), (70, 1537), (1540, 96), (100, 1409), (128, 1411)]
 
 
 @pytest.fixture(scope="module")
