@@ -887,14 +887,15 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
   // products run as one launch per product and step (muon::run_group):
   // chunks whose Gram launch leaves CUs idle in its last round (occupancy
   // below 0.9), that can share the 256 x 256 kernel, with the same step
-  // count and parameter dtype, at most kGroupMax to a group.  A group's
+  // count and parameter dtype, at most kGroupMax to a group, where that takes
+  // less time than one by one (muon::group_pays).  A group's
   // members each keep their own workspace region.  Groups are formed when
   // the call runs on one stream: with two, such chunks overlap on the two
-  // streams instead, which measured faster (one block, hidden 2048: 2.17
-  // against 2.36 ms per step; its two chunks' Gram products differ in K, and
+  // streams instead, which measured faster (one block, hidden 2048: 2.05
+  // against 2.28 ms per step grouped on one stream, 2.39 one by one; its two
+  // chunks' Gram products differ in K, and
   // a grouped round waits for the longest tile, where a chunk on its own
-  // stream moves on to its next product).  On one stream, groups measured
-  // 2.51 against 2.95 ms.
+  // stream moves on to its next product).
   const bool concurrent = h->nstreams > 1 && h->side != nullptr;
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device);
@@ -914,6 +915,11 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
     return g;
   };
   auto steps_of = [&](const Chunk& c) { return int(tables[size_t(c.cset)].size() / 3); };
+  // Whether a chunk leaves CUs idle: by the rounds of its Gram launch on the
+  // larger tiles.  Short sides up to 128 have no such launch; for them this asks
+  // for less than 0.9 of a round of matrices, which measured as well as pricing
+  // their slices or calling them always idle (30 mixed calls: within 1%, or up
+  // to 14% faster than the latter, 250 of 32 x 128 beside 250 of 64 x 256).
   auto idle_of = [&](const Chunk& c) {
     const bool tile = muon::chunk_on_tiles(c.S, c.L, steps_of(c));
     const int64_t t = tile ? (c.S + 255) / 256 : c.S / 128;
@@ -952,11 +958,18 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
       units[it->second].members.push_back(ci);
       grouped[ci] = 1;
     }
-    // a group of one is a plain chunk
-    for (Unit& u : units)
-      if (u.members.size() == 1) grouped[u.members[0]] = 0;
-    units.erase(std::remove_if(units.begin(), units.end(), [](const Unit& u) { return u.members.size() < 2; }),
-                units.end());
+    // a group of one is a plain chunk; so are the members of one that does not pay
+    const auto plain = [&](const Unit& u) {
+      if (u.members.size() < 2) return true;
+      ChunkGeom geoms[muon::kGroupMax];
+      for (size_t mi = 0; mi < u.members.size(); ++mi) geoms[mi] = geom_of(plan.chunks[u.members[mi]]);
+      return !muon::group_pays(geoms, int(u.members.size()));
+    };
+    units.erase(std::remove_if(units.begin(), units.end(), [&](const Unit& u) {
+      if (!plain(u)) return false;
+      for (size_t ci : u.members) grouped[ci] = 0;
+      return true;
+    }), units.end());
   }
   for (size_t ci = 0; ci < nch; ++ci)
     if (!grouped[ci]) {

@@ -190,6 +190,9 @@ constexpr int kGroupMax = 8;
 // extents multiples of 256, rows within its offsets), at least one step,
 // not a fused small-matrix chunk.
 bool group_eligible(const ChunkGeom& g, int K);
+// Whether n such chunks (n <= kGroupMax) take less time as a group than one
+// by one.
+bool group_pays(const ChunkGeom* geoms, int n);
 hipError_t run_group(const GroupMember* members, int n, const StepScalars& sc, int K, hipStream_t stream,
                      LaunchTimer* timer);
 

@@ -24,6 +24,7 @@
 // every step (padded rows/columns of X, A and B stay exactly zero).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 #include <utility>
@@ -1956,17 +1957,26 @@ bool deep_tiles(const GemmArgs& ga, int nmat) {
 // Gram and polynomial are at 0.96: 5.40 ms on the small tiles, 5.23 on the
 // large; 3 and 2 of them 9.36 and 8.95; no other of 34 calls moved by more
 // than the runs differ, and at 0.65 several lost 5 to 60%).
-bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
-  const int64_t m2 = (ga.tiles_m + 1) / 2, n2 = (ga.tiles_n + 1) / 2;
-  const double t1 = double(nmat) * double(quarter_tiles(ga));
-  const double t2 = double(nmat) * double(ga.syrk ? m2 * (m2 + 1) / 2 : m2 * n2);
+struct TileCosts { double small, large; };         // us on 128 x 128 and on 256 x 256 tiles
+double large_tile_us(double f, double nk) { return (1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f; }
+int64_t large_tiles(const GemmArgs& ga) {
+  const int64_t m = (ga.tiles_m + 1) / 2, n = (ga.tiles_n + 1) / 2;
+  return ga.syrk ? m * (m + 1) / 2 : m * n;
+}
+TileCosts tile_costs(const GemmArgs& ga, int nmat, bool split) {
+  const double t1 = double(nmat) * double(quarter_tiles(ga)), t2 = double(nmat) * double(large_tiles(ga));
   const double cus = device_cu_count(), nk = ga.k_slabs * (split ? 6 : 1);
   const double rounds2 = std::ceil(t2 / cus), f = t2 / (rounds2 * cus);
   const double r1 = t1 / (2.0 * cus), rounds1 = std::ceil(r1);
-  const double cost2 = rounds2 * ((1.15 + 0.4 * f) * nk + 4.0 + 8.0 * f);
-  double cost1 = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
-  if (!split && deep_tiles(ga, nmat)) cost1 = 0.6 * nk + 4.0;
-  return cost1 < 0.9 * cost2;
+  TileCosts c;
+  c.large = rounds2 * large_tile_us(f, nk);
+  c.small = r1 <= 1.0 ? 0.95 * nk + 2.0 : (1.03 * r1 + 0.5) * nk + 5.0 * rounds1;
+  if (!split && deep_tiles(ga, nmat)) c.small = 0.6 * nk + 4.0;
+  return c;
+}
+bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
+  const TileCosts c = tile_costs(ga, nmat, split);
+  return c.small < 0.9 * c.large;
 }
 
 // The products on k_gemm_nt: rows past the tile kernel's 32-bit offsets
@@ -3385,6 +3395,38 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
 bool group_eligible(const ChunkGeom& cg, int K) {
   return !cg.ns_f32 && K > 0 && cg.S % 256 == 0 && cg.L % 256 == 0 && tile_rows_fit(cg.S, cg.L, 2) &&
          !chunk_is_small(cg.s, cg.l, false, K) && !chunk_is_sliced(cg.s, cg.l, false, K);
+}
+
+// A group's launches run all members' tiles on 256 x 256 tiles: as one round
+// while they fit (then as long as the longest takes), else as rounds of their
+// mean.  Alone, a member's launches take the faster tile size.  On one stream,
+// us per step call, grouped / alone / the model's ratio: 3 x 512^2 + 3 x 512 x
+// 1536 + 2 x 768 x 1024 489 / 630 / 0.70; 4 x 2048^2 + 3 x 2048 x 5632 2284 /
+// 2391 / 0.97; 4096^2 + 2 x 1024 x 4096 1690 / 1874 / 0.95; 4 x 1024^2 + 3 x 1024
+// x 2816 691 / 668 / 1.06; 4 x 768^2 + 2 x 768 x 3072 643 / 575 / 1.06; 1024^2 +
+// 1024 x 4096 725 / 609 / 1.18.
+bool group_pays(const ChunkGeom* geoms, int n) {
+  double grouped = 0.0, alone = 0.0;
+  for (int q = 0; q < 3; ++q) {
+    double tiles = 0.0, slabs_us = 0.0, longest = 0.0;
+    GemmArgs ga[kMaxGroup];
+    for (int c = 0; c < n; ++c) {
+      const float coeffs[3] = {1.f, 1.f, 1.f};
+      const StepProducts sp = step_products<uint16_t>(geoms[c], nullptr, ChunkBuffers{}, StepScalars{}, coeffs, 1, 0, 0);
+      ga[c] = q == 0 ? sp.gram : q == 1 ? sp.poly : sp.upd;
+      const TileCosts own = tile_costs(ga[c], geoms[c].nmat, false);
+      alone += own.small < 0.9 * own.large ? own.small : own.large;
+      tiles += double(geoms[c].nmat) * double(large_tiles(ga[c]));
+    }
+    const double cus = device_cu_count(), rounds = std::ceil(tiles / cus), f = tiles / (rounds * cus);
+    for (int c = 0; c < n; ++c) {
+      const double us = large_tile_us(f, ga[c].k_slabs);
+      longest = std::max(longest, us);
+      slabs_us += us * double(geoms[c].nmat) * double(large_tiles(ga[c]));
+    }
+    grouped += std::max(longest, rounds * slabs_us / tiles);
+  }
+  return grouped < alone;
 }
 
 hipError_t run_group(const GroupMember* m, int n, const StepScalars& sc, int K, hipStream_t st,

@@ -110,6 +110,21 @@ def test_one_launch_per_product_and_step(muon):
         assert g["_flops"][k] == pytest.approx(s["_flops"][k], rel=1e-12)
 
 
+def test_chunks_that_are_faster_alone_stay_alone(muon):
+    # one 1024^2 and one 1024 x 4096 matrix: on 256 x 256 tiles they would wait
+    # for ten tiles of 64 slabs, alone they take the 128 x 128 tiles
+    W, G, B, pdts = inputs([(1024, 1024), (1024, 4096)], key=6)
+    muon.profile(True)
+    muon.profile_read(reset=True)
+    gw, gb = run_step(muon, W, G, B, pdts, True)
+    st = muon.profile_read(reset=True)
+    muon.profile(False)
+    assert st["gram_syrk"]["launches"] == 10 and st["update_apply_gemm"]["launches"] == 2
+    sw, sb = run_step(muon, W, G, B, pdts, False)
+    for a, b in zip(gw + gb, sw + sb):
+        assert np.array_equal(to_bits(a), to_bits(b))
+
+
 def test_groups_split_by_parameter_dtype_and_step_count(muon):
     # fp32 parameters form their own group; entries with a 3-step table form
     # theirs; results equal the chunk-by-chunk run
