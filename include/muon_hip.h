@@ -314,8 +314,9 @@ muon_status_t muon_plan_step(const muon_param_t* params, int64_t n, const muon_h
  *   flops       dense flop count of the product the kernel computes
  *               (2 s^2 l for X X^T and B X, 2 s^3 for A A; 0 for
  *               elementwise kernels),
- *   exec_flops  flops the kernel issues on the real extents (upper tiles
- *               only for the symmetric products),
+ *   exec_flops  flops the launched kernels' matrix instructions execute
+ *               (whole tiles of padded extents, upper tiles only of the
+ *               symmetric products; 0 for a polynomial with c = 0, a scaling),
  *   bytes       minimal HBM traffic: each operand read once, each output
  *               written once.
  * Families (in this order): momentum_norm (momentum, norm partials and the
@@ -323,9 +324,9 @@ muon_status_t muon_plan_step(const muon_param_t* params, int64_t n, const muon_h
  * whose r is too large or small to be applied in the first products),
  * gram_syrk, poly_syrk, update_gemm, update_apply_gemm,
  * apply_x0, adamw, ns_small (the whole step of a chunk whose short side is
- * at most 128, counted as one launch).  exec_flops of fp32 Newton-Schulz on
- * the tile kernel counts its six bf16 products.  `reset` != 0
- * clears the counters after reading. */
+ * at most 128, one launch in the count although column slices are 2 K + 2
+ * kernels).  exec_flops of fp32 Newton-Schulz on the tile kernel counts its
+ * six bf16 products.  `reset` != 0 clears the counters after reading. */
 typedef struct {
   const char* name;
   int64_t launches;

@@ -1024,10 +1024,11 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
         const Chunk& c = plan.chunks[ci];
         std::fprintf(stderr,
                      "muon:   chunk %zu: %lld matrices of %lld x %lld (padded %lld x %lld), K = %zu, "
-                     "coefficient set %d, X^T %s, %s stream, %zu workspace bytes%s\n",
+                     "coefficient set %d, X^T %s, %s stream, %zu workspace bytes, %s%s\n",
                      ci, (long long)c.count, (long long)c.s, (long long)c.l, (long long)c.S, (long long)c.L,
                      tables[size_t(c.cset)].size() / 3, int(c.cset), c.keeps_xt ? "kept" : "not kept",
                      on_side[ui] ? "second" : "caller's", c.bytes,
+                     muon::route_of(geom_of(c), steps_of(c)).c_str(),
                      units[ui].members.size() > 1 ? (mi == 0 ? ", grouped launches (first of the group)"
                                                             : ", grouped launches") : "");
       }

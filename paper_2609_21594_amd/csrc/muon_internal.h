@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <string>
+
 namespace muon {
 
 // Workspace extents of every matrix are rounded up to this multiple, and the
@@ -244,6 +246,11 @@ hipError_t put_descriptors(const MatDesc* host, int n, MatDesc* dev, hipStream_t
 
 // The HBM reference copy (dst and src 16-byte aligned, not overlapping).
 hipError_t stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
+
+// The kernels a chunk runs on alone: "fused", "slices", "long rows", "no products" (K = 0), or
+// "tiles" and the tiles of its Gram, polynomial and update launches (256, 128,
+// or 128x4: 128 with four LDS stages).
+std::string route_of(const ChunkGeom& g, int K);
 
 // Enqueues the whole step for one chunk on `stream`: momentum + partial
 // norms, norm finalisation, normalise + transpose-first + cast, K

@@ -26,6 +26,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <string>
 #include <type_traits>
 #include <utility>
 
@@ -886,7 +887,7 @@ struct TileCfg {
 #endif
 using CfgSquare = TileCfg<256, 256, 2, 4, MUON_SQ_SLAB, MUON_SQ_STAGES, 2>;
 // 128 x 128, 4 wavefronts of 64 x 64, two workgroups per CU: for launches
-// whose 256 x 256 tiles would leave CUs without work (small_tiles).  Every
+// whose 256 x 256 tiles would leave CUs without work (tiles_of).  Every
 // element sees the same operations in the same order on both, so the choice
 // never changes a result.
 using CfgQuarter = TileCfg<128, 128, 2, 2, 128, 2, 2>;
@@ -1834,8 +1835,16 @@ hipError_t launch_scale_upper(const GemmArgs& ga, int nmat, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The launchers set `exec` to the flops the launch's MFMAs execute: whole
+// tiles of the kernel that runs the product, of the symmetric ones the upper
+// tiles, six products of planes for one of SPLIT values; none for a scaling.
+template <class Cfg>
+double executed(const GemmArgs& ga, int pairs) {  // ga in tiles of Cfg
+  return 2.0 * pairs * double(ga.total_tiles) * Cfg::BM * Cfg::BN * double(ga.k_slabs) * (Cfg::SLAB / 2);
+}
+
 template <class Cfg, bool SPLIT>
-hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
+hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st, double& exec) {
   // ga arrives in 128 x 128 tiles and 128-byte slabs
   ga.m_ext = ga.tiles_m * kTile;
   ga.n_ext = ga.tiles_n * kTile;
@@ -1844,6 +1853,7 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
   ga.tiles_per_mat = ga.syrk ? ga.tiles_m * (ga.tiles_m + 1) / 2 : ga.tiles_m * ga.tiles_n;
   ga.k_slabs = ga.k_slabs * 128 / Cfg::SLAB;
   ga.total_tiles = ga.tiles_per_mat * nmat;
+  exec = epi == EPI_POLY && ga.beta == 0.f ? 0.0 : executed<Cfg>(ga, SPLIT ? 6 : 1);
   // B = b A + c A^2 = c (A^2 + (b/c) A): the A term joins the accumulators
   // in the main loop
   if (epi == EPI_POLY) {
@@ -1876,8 +1886,9 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st) {
 // persistent launch over all their tiles.  The chunks share the product, the
 // final kind and the parameter dtype.
 template <class Cfg>
-hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, hipStream_t st) {
+hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, hipStream_t st, double& exec) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  exec = 0.0;
   GroupArgs gr{};
   gr.start[0] = 0;
   bool rows16 = true;
@@ -1901,6 +1912,7 @@ hipError_t launch_group(int epi, const GemmArgs* gas, const int* nmats, int n, h
     }
     if (c > 0 && (ga.final_kind != gr.ga[0].final_kind || ga.param_dtype != gr.ga[0].param_dtype))
       return hipErrorInvalidValue;
+    exec += executed<Cfg>(ga, 1);
     rows16 = rows16 && ga.w_rows16;
     gr.ga[c] = ga;
     gr.start[c + 1] = gr.start[c] + ga.total_tiles;
@@ -1974,15 +1986,18 @@ TileCosts tile_costs(const GemmArgs& ga, int nmat, bool split) {
   if (!split && deep_tiles(ga, nmat)) c.small = 0.6 * nk + 4.0;
   return c;
 }
-bool small_tiles(const GemmArgs& ga, int nmat, bool split) {
+enum class Tiles { square, quarter, deep };
+Tiles tiles_of(const GemmArgs& ga, int nmat, bool split) {
   const TileCosts c = tile_costs(ga, nmat, split);
-  return c.small < 0.9 * c.large;
+  if (c.small >= 0.9 * c.large) return Tiles::square;
+  return !split && deep_tiles(ga, nmat) ? Tiles::deep : Tiles::quarter;
 }
 
 // The products on k_gemm_nt: rows past the tile kernel's 32-bit offsets
 // (chunk_on_tiles).
 template <typename T>
-hipError_t launch_gemm(int epi, GemmArgs ga, int nmat, hipStream_t st) {
+hipError_t launch_gemm(int epi, GemmArgs ga, int nmat, hipStream_t st, double& exec) {
+  exec = 2.0 * double(nmat) * ga.tiles_per_mat * kTile * kTile * double(ga.k_slabs) * (128 / sizeof(T));
   const dim3 grid(static_cast<unsigned>(ga.tiles_per_mat) * nmat), block(256);
   switch (epi) {
     case EPI_GRAM: hipLaunchKernelGGL((k_gemm_nt<T, EPI_GRAM>), grid, block, 0, st, ga); break;
@@ -3046,7 +3061,7 @@ void k_slice_step(SliceArgs sa) {
 
 template <typename GT, typename XT, int RB>
 hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuffers& wb, const StepScalars& sc,
-                      const float* coeffs, int K, hipStream_t st) {
+                      const float* coeffs, int K, hipStream_t st, double& exec) {
   constexpr int NW = kSliceWaves<XT>;
   using C = SliceCfg<XT, RB, NW>;
   using CF = SliceCfg<XT, RB, 4>;                          // the last step's slices
@@ -3079,8 +3094,13 @@ hipError_t run_slices(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuf
     hipLaunchKernelGGL((k_slice_reduce<XT, RB>), blocks, dim3(256), 0, st, sa);
     if (k + 1 < K) hipLaunchKernelGGL((k_slice_step<XT, RB, -1, DT_BF16>), slices, dim3(64 * NW), 0, st, sa);
   }
+  // what the MFMAs execute: per step the upper blocks of A and X' over all
+  // columns, and B in every slice
+  const int nlast = (cg.L + CF::W - 1) / CF::W;
+  const double Sx = C::Sx, Lp = cg.L;
+  exec = double(cg.nmat) * (K * 2.0 * Lp * (C::NB * 1024.0 + Sx * Sx) + 2.0 * Sx * Sx * Sx * ((K - 1.0) * sa.nsl + nlast));
   const bool o = sc.final_kind != 0, f32 = cg.param_dtype == DT_F32;
-  sa.nsl = (cg.L + CF::W - 1) / CF::W;
+  sa.nsl = nlast;
   const dim3 halves(static_cast<unsigned>(sa.nsl) * mats);
   if (!o && !f32) hipLaunchKernelGGL((k_slice_step<XT, RB, 0, DT_BF16>), halves, dim3(256), 0, st, sa);
   else if (!o) hipLaunchKernelGGL((k_slice_step<XT, RB, 0, DT_F32>), halves, dim3(256), 0, st, sa);
@@ -3094,13 +3114,14 @@ hipError_t run_sliced_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const Ch
                             const float* coeffs, int K, hipStream_t st, LaunchTimer* timer) {
   Timed tm(timer, KK_SMALL, st);
   const int Sx = cg.s <= 32 ? 32 : cg.s <= 64 ? 64 : 128;
-  const hipError_t e = Sx == 32   ? run_slices<GT, XT, 1>(cg, d_desc, wb, sc, coeffs, K, st)
-                       : Sx == 64 ? run_slices<GT, XT, 2>(cg, d_desc, wb, sc, coeffs, K, st)
-                                  : run_slices<GT, XT, 4>(cg, d_desc, wb, sc, coeffs, K, st);
+  double exec = 0.0;
+  const hipError_t e = Sx == 32   ? run_slices<GT, XT, 1>(cg, d_desc, wb, sc, coeffs, K, st, exec)
+                       : Sx == 64 ? run_slices<GT, XT, 2>(cg, d_desc, wb, sc, coeffs, K, st, exec)
+                                  : run_slices<GT, XT, 4>(cg, d_desc, wb, sc, coeffs, K, st, exec);
   if (e != hipSuccess) return e;
-  const double nm = cg.nmat, s = cg.s, l = cg.l, L = cg.L;
+  const double nm = cg.nmat, s = cg.s, l = cg.l;
   const double gsz = sizeof(GT), psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
-  tm.done(nm * K * (4.0 * s * s * l + 2.0 * s * s * s), nm * K * (4.0 * Sx * Sx * L + 2.0 * Sx * Sx * Sx),
+  tm.done(nm * K * (4.0 * s * s * l + 2.0 * s * s * s), exec,
           nm * s * l * (gsz + (sc.momentum ? 8.0 : 0.0) + (sc.final_kind == 0 ? 2.0 * psz : psz)));
   return hipSuccess;
 }
@@ -3232,7 +3253,7 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
 struct StepProducts {
   GemmArgs gram, poly, upd;
   bool last;              // upd is the last step's product (parameter update or O)
-  double f[3], x[3], b[3];  // dense flops, executed flops, bytes of gram, poly, upd
+  double f[3], b[3];      // dense flops (Eq. 1, on the real extents) and bytes of gram, poly, upd
 };
 
 template <typename XT>
@@ -3242,19 +3263,12 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   const double nm = cg.nmat;
   const double s = cg.s, l = cg.l;
   constexpr int planes = Store<XT>::planes;
-  constexpr int pairs = planes == 3 ? 6 : 1;  // products of planes per product of values
   const int es = static_cast<int>(sizeof(typename Store<XT>::E));
   const double xsz = es * planes;
   const double psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
   const int64_t planeX = static_cast<int64_t>(cg.S) * cg.L * es, matX = planeX * planes;
   const int64_t planeA = static_cast<int64_t>(cg.S) * cg.S * es, matA = planeA * planes;
   const int ts = cg.S / kTile, tl = cg.L / kTile;
-  // Work accounting: `flops` is the dense count of each product on the real
-  // extents (Eq. 1); `exec` is what the MFMAs execute: whole tiles of the
-  // kernel that runs the products, and of the symmetric ones the upper tiles.
-  const int te = qtr ? 256 : kTile;
-  const double TS = (cg.S + te - 1) / te, TL = (cg.L + te - 1) / te;
-  const double upper = TS * (TS + 1) / 2 * te * te, Sp = cg.S, Lp = cg.L;
   StepProducts r{};
   const float a = coeffs[3 * k], b = coeffs[3 * k + 1], c = coeffs[3 * k + 2];
   const char* X = static_cast<const char*>(wb.X[cur]);
@@ -3274,7 +3288,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   // reads them as upper-triangle tiles (mode 1): no mirrored tile is
   // written.  Otherwise the lower triangle is written as the mirror.
   if (!qtr) { g.CT = g.C; g.ct_mat = matA; g.ldct = g.ldc; }
-  r.f[0] = nm * 2 * s * s * l; r.x[0] = nm * 2 * pairs * upper * Lp; r.b[0] = nm * (s * l + s * s) * xsz;
+  r.f[0] = nm * 2 * s * s * l; r.b[0] = nm * (s * l + s * s) * xsz;
   // B = b A + c A A^T: M = N = K = S.
   GemmArgs& pp = r.poly;
   pp = g;
@@ -3287,7 +3301,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   pp.p_mode = pp.q_mode = qtr ? 1 : 0;
   pp.p_plane = pp.q_plane = planeA;
   pp.alpha = b; pp.beta = c;
-  r.f[1] = nm * 2 * s * s * s; r.x[1] = nm * 2 * pairs * upper * Sp; r.b[1] = nm * 2 * s * s * xsz;
+  r.f[1] = nm * 2 * s * s * s; r.b[1] = nm * 2 * s * s * xsz;
   // X' = a X + B X: M = S, N = L, K = S.  The second operand is X^T (N x K,
   // K contiguous) on the 128 x 128 kernel, X itself (K x N) under qtr.
   u.P = static_cast<const char*>(wb.B); u.p_mat = matA; u.ldp = cg.S * es;
@@ -3305,7 +3319,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   u.alpha = a;
   u.s = cg.s; u.l = cg.l;
   u.xscale = k == 0 ? wb.xscale : nullptr;  // X1 = r (a X~ + B0 X~)
-  r.f[2] = nm * 2 * s * s * l; r.x[2] = nm * 2 * pairs * (TS * te) * (TL * te) * Sp;
+  r.f[2] = nm * 2 * s * s * l;
   r.last = k + 1 == K;
   if (!r.last) {
     u.C = static_cast<char*>(wb.X[cur ^ 1]); u.c_mat = matX; u.ldc = cg.L * es;
@@ -3331,16 +3345,18 @@ hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBu
   if (e != hipSuccess || K == 0) return e;
   const bool qtr = runs_on_tiles<XT>(cg, K);
   const int nmat = cg.nmat;
+  double exec = 0.0;
   auto launch = [&](int epi, const GemmArgs& ga) {
     if constexpr (!split)
-      if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st);
+      if (!qtr) return launch_gemm<XT>(epi, ga, nmat, st, exec);
     if constexpr (std::is_same<XT, float>::value)
       return hipErrorInvalidValue;
     else {
-      if (!small_tiles(ga, nmat, split)) return launch_tile<CfgSquare, split>(epi, ga, nmat, st);
+      const Tiles kind = tiles_of(ga, nmat, split);
+      if (kind == Tiles::square) return launch_tile<CfgSquare, split>(epi, ga, nmat, st, exec);
       if constexpr (!split)
-        if (deep_tiles(ga, nmat)) return launch_tile<CfgDeep, false>(epi, ga, nmat, st);
-      return launch_tile<CfgQuarter, split>(epi, ga, nmat, st);
+        if (kind == Tiles::deep) return launch_tile<CfgDeep, false>(epi, ga, nmat, st, exec);
+      return launch_tile<CfgQuarter, split>(epi, ga, nmat, st, exec);
     }
   };
   int cur = 0;
@@ -3349,18 +3365,18 @@ hipError_t run_chunk_t(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBu
     {
       Timed tm(timer, KK_GRAM, st);
       if ((e = launch(EPI_GRAM, sp.gram)) != hipSuccess) return e;
-      tm.done(sp.f[0], sp.x[0], sp.b[0]);
+      tm.done(sp.f[0], exec, sp.b[0]);
     }
     {
       Timed tm(timer, KK_POLY, st);
       if ((e = launch(EPI_POLY, sp.poly)) != hipSuccess) return e;
-      tm.done(sp.f[1], sp.x[1], sp.b[1]);
+      tm.done(sp.f[1], exec, sp.b[1]);
     }
     {
       const int epi = sp.last ? EPI_FINAL : EPI_UPDATE;
       Timed tm(timer, sp.last ? KK_FINAL : KK_UPDATE, st);
       if ((e = launch(epi, sp.upd)) != hipSuccess) return e;
-      tm.done(sp.f[2], sp.x[2], sp.b[2]);
+      tm.done(sp.f[2], exec, sp.b[2]);
     }
     cur ^= 1;
   }
@@ -3390,6 +3406,24 @@ hipError_t run_chunk(const ChunkGeom& cg, const MatDesc* d_desc, const ChunkBuff
   }
   return gbf ? run_chunk_t<uint16_t, uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer)
              : run_chunk_t<float, uint16_t>(cg, d_desc, wb, sc, coeffs, K, st, timer);
+}
+
+// The kernels a chunk runs on alone, for the plan printed to stderr.
+std::string route_of(const ChunkGeom& cg, int K) {
+  const bool f32 = cg.ns_f32 != 0;
+  if (chunk_is_small(cg.s, cg.l, f32, K)) return "fused";
+  if (chunk_is_sliced(cg.s, cg.l, f32, K)) return "slices";
+  if (!chunk_on_tiles(cg.S, cg.L, K)) return K == 0 ? "no products" : "long rows";
+  const float coeffs[3] = {1.f, 1.f, 1.f};
+  const StepProducts sp =
+      f32 ? step_products<Split3>(cg, nullptr, ChunkBuffers{}, StepScalars{}, coeffs, 1, 0, 0)
+          : step_products<uint16_t>(cg, nullptr, ChunkBuffers{}, StepScalars{}, coeffs, 1, 0, 0);
+  std::string r = "tiles";
+  for (const GemmArgs* ga : {&sp.gram, &sp.poly, &sp.upd}) {
+    const Tiles kind = tiles_of(*ga, cg.nmat, f32);
+    r += kind == Tiles::square ? " 256" : kind == Tiles::quarter ? " 128" : " 128x4";
+  }
+  return r;
 }
 
 bool group_eligible(const ChunkGeom& cg, int K) {
@@ -3445,21 +3479,22 @@ hipError_t run_group(const GroupMember* m, int n, const StepScalars& sc, int K, 
   for (int k = 0; k < K; ++k) {
     GemmArgs ga[3][kMaxGroup];
     int nm[kMaxGroup];
-    double f[3] = {0, 0, 0}, x[3] = {0, 0, 0}, b[3] = {0, 0, 0};
+    double f[3] = {0, 0, 0}, b[3] = {0, 0, 0};
     bool last = false;
     for (int c = 0; c < n; ++c) {
       const StepProducts sp = step_products<uint16_t>(m[c].geom, m[c].desc, m[c].wb, sc, m[c].coeffs, K, k, cur);
       ga[0][c] = sp.gram; ga[1][c] = sp.poly; ga[2][c] = sp.upd;
       nm[c] = m[c].geom.nmat;
-      for (int q = 0; q < 3; ++q) { f[q] += sp.f[q]; x[q] += sp.x[q]; b[q] += sp.b[q]; }
+      for (int q = 0; q < 3; ++q) { f[q] += sp.f[q]; b[q] += sp.b[q]; }
       last = sp.last;
     }
     const int kinds[3] = {KK_GRAM, KK_POLY, last ? KK_FINAL : KK_UPDATE};
     const int epis[3] = {EPI_GRAM, EPI_POLY, last ? EPI_FINAL : EPI_UPDATE};
     for (int q = 0; q < 3; ++q) {
       Timed tm(timer, kinds[q], st);
-      if ((e = launch_group<CfgSquare>(epis[q], ga[q], nm, n, st)) != hipSuccess) return e;
-      tm.done(f[q], x[q], b[q]);
+      double exec = 0.0;
+      if ((e = launch_group<CfgSquare>(epis[q], ga[q], nm, n, st, exec)) != hipSuccess) return e;
+      tm.done(f[q], exec, b[q]);
     }
     cur ^= 1;
   }

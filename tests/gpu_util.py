@@ -104,3 +104,28 @@ def o_gate(O_gpu, O_ref, dtype, prec, ns_steps: int = 5, coeffs=None, G=None):
     if dtype == "bf16" and prec == "f32":
         gate += rel(ref.round_to(O_ref, dtype), O_ref)
     return err, gate
+
+
+def logged_routes(text):
+    """{(matrices, s, l): route} of the plan that MUON_HIP_LOG=1 prints: "fused",
+    "slices", "long rows", "no products", or the tiles of the Gram, polynomial and update
+    launches, e.g. ("256", "128", "128x4")."""
+    import re
+    out = {}
+    for n, s, l, rest in re.findall(r"chunk \d+: (\d+) matrices of (\d+) x (\d+) .*workspace bytes, ([^\n]*)", text):
+        route = rest.split(", grouped")[0]
+        out[int(n), int(s), int(l)] = tuple(route.split()[1:]) if route.startswith("tiles") else route
+    return out
+
+
+def route_recorder(monkeypatch, capfd):
+    """Call it before creating the handle; the function it returns gives the
+    routes of the calls since the last one."""
+    monkeypatch.setenv("MUON_HIP_LOG", "1")
+    capfd.readouterr()
+
+    def routes():
+        out, err = capfd.readouterr()
+        print(out, end="", flush=True)
+        return logged_routes(err)
+    return routes
