@@ -1,14 +1,15 @@
-"""The 256 x 256 and the 128 x 128 configuration of the tile kernel give the
-same bits: which of them a launch takes depends on how many matrices share
-it, and a matrix's result may not.  Each shape runs alone and among enough
-copies to fill the chip, so that its products move from one to the other
-(also one product at a time: A written by one, read by the other)."""
+"""The configurations of the tile kernel (256 x 256, 128 x 128, 128 x 128 with four
+stages) give the same bits: which of them a launch takes depends on how many
+matrices share it, and a matrix's result may not.  Each shape runs alone and
+among more copies.  In the second test every product of a call meets every
+configuration, also with A and B written by one and read by another, which the
+calls' printed plans must show."""
 import numpy as np
 import pytest
 
 from oracle import muon_ref as ref
 from paper_2609_21594_amd import synth
-from tests.gpu_util import decode, o_gate, require_gpu, to_bits, to_dev, to_host
+from tests.gpu_util import decode, o_gate, require_gpu, route_recorder, to_bits, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,42 @@ def test_result_does_not_depend_on_the_batch(shape, prec):
             assert err <= gate, (shape, err, gate)
     finally:
         m.close()
+
+
+# padded extents: 1408 x 1408, 1024 x 1408, 1408 x 2048
+@pytest.mark.parametrize("prec", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", [(1300, 1300), (1000, 1400), (2000, 1390)])
+def test_every_configuration_gives_the_same_bits(shape, prec, monkeypatch, capfd):
+    require_gpu()
+    import torch
+    from paper_2609_21594_amd.binding import Muon
+    routes = route_recorder(monkeypatch, capfd)
+    s, l = sorted(shape)
+    W, g, b = (synth.draw(shape, sd, dt, rng(70 + k, *shape)) for k, (sd, dt) in
+               enumerate(((0.02, "bf16"), (1e-3, "bf16"), (1e-3, "f32"))))
+    first, seen = {}, set()
+    m = Muon(0)
+    try:
+        for n in (1, 2, 3, 4, 6, 8, 9, 16, 30):
+            # a step on bf16 and one on fp32 parameters, and the orthogonalisation
+            for kind in ("bf16", "f32", "orth"):
+                if kind == "orth":
+                    ins = [to_dev(g, "bf16") for _ in range(n)]
+                    outs = [torch.full_like(t, float("nan")) for t in ins]
+                    m.orthogonalize(ins, outs, ns_steps=3, ns_precision=prec)
+                else:
+                    outs = [to_dev(W, "bf16").to(torch.float32 if kind == "f32" else torch.bfloat16) for _ in range(n)]
+                    m.step(outs, [to_dev(g, "bf16") for _ in range(n)], [to_dev(b, "f32") for _ in range(n)], lr=0.02,
+                           beta=0.95, ns_steps=3, ns_precision=prec)
+                torch.cuda.synchronize()
+                seen.add(routes()[n, s, l])
+                want = first.setdefault(kind, outs[0].clone())
+                for i in range(n):
+                    assert torch.equal(outs[i], want), (shape, kind, n, i)
+    finally:
+        m.close()
+    print(f"{shape} {prec}: {sorted(seen)}", flush=True)
+    for product in range(3):
+        kinds = {r[product] for r in seen}
+        assert kinds >= ({"256", "128", "128x4"} if prec == "bf16" else {"256", "128"}), (product, seen)
+    assert any(r[0] == r[1] != r[2] for r in seen)  # A and B written by one, read by another
