@@ -10,7 +10,7 @@ import pytest
 
 from oracle import muon_ref as ref
 from paper_2609_21594_amd import synth
-from tests.gpu_util import (MOMENTUM_TOL, TOL, decode, o_gate, rel, require_gpu, to_bits,
+from tests.gpu_util import (MOMENTUM_TOL, TOL, decode, o_gate, rel, require_gpu, route_recorder, to_bits,
                             to_dev, to_host, tol_for, w_gate)
 
 pytestmark = pytest.mark.gpu
@@ -171,6 +171,65 @@ def test_rows_past_the_tile_kernel_offsets(muon):
     err = rel(got, want)
     print(f"long rows ({s} x {l}): err {err:.3e} (rho {rho:.1e})", flush=True)
     assert err <= TOL["bf16"] + rho
+
+
+# Rows of 2^22 columns and more on k_gemm_nt ("long rows"): fp32 products, fp32
+# parameters, outputs, l x s matrices; and an fp32 short side of 128 whose rows
+# are past the slices' offsets (2^21 columns) but not the tile kernel's.
+@pytest.mark.parametrize("s,blk,prec,pdt,kind,tall", [
+    (256, 16385, "f32", "f32", "step", False), (256, 16385, "f32", "f32", "step", True),
+    (256, 16385, "f32", "bf16", "orth", False), (256, 16385, "bf16", "f32", "step", True),
+    (256, 16385, "bf16", "bf16", "orth", True), (256, 16385, "bf16", "f32", "orth", False),
+    (128, 16400, "f32", "f32", "step", False), (128, 16400, "f32", "f32", "orth", True)])
+def test_long_rows_of_every_kind(s, blk, prec, pdt, kind, tall, monkeypatch, capfd):
+    # Row i of the gradient holds random values on column block i and zeros
+    # elsewhere: X X^T stays diagonal, so row i of O is its own direction times
+    # the oracle's value for the diagonal matrix of the rows' norms.
+    import torch
+    from paper_2609_21594_amd.binding import Muon
+    require_gpu()
+    l, lr = s * blk, 0.02
+    dt = torch.float32 if pdt == "f32" else torch.bfloat16
+    gen_ = torch.Generator(device="cuda").manual_seed(s + blk)
+    vals = torch.randn(s, blk, device="cuda", generator=gen_).to(dt)
+    ar = torch.arange(s, device="cuda")
+
+    def spread(v, dtype):
+        m = torch.zeros((s, s, blk), dtype=dtype, device="cuda")
+        m[ar, ar, :] = v.to(dtype)
+        m = m.view(s, l)
+        return m.t().contiguous() if tall else m
+
+    G = spread(vals, dt)
+    out = torch.zeros_like(G)
+    routes = route_recorder(monkeypatch, capfd)
+    m = Muon(0)
+    try:
+        if kind == "step":
+            M = torch.zeros(G.shape, dtype=torch.float32, device="cuda")
+            m.step([out], [G], [M], lr=lr, beta=0.95, weight_decay=0.0, ns_precision=prec)
+            del M
+        else:
+            m.orthogonalize([G], [out], ns_precision=prec)
+        torch.cuda.synchronize()
+    finally:
+        m.close()
+    route = routes()[1, s, l]
+    assert route == "long rows" if s == 256 else route[0] in ("128", "256"), route
+    del G
+    O = (out.t() if tall else out).reshape(s, s, blk)
+    rows = O[ar, ar, :].double()
+    assert int(torch.count_nonzero(out)) <= s * blk
+    norms = vals.double().norm(dim=1)
+    o = torch.from_numpy(np.diag(ref.orthogonalize(np.diag(norms.cpu().numpy()), 5)).copy()).cuda()
+    want = vals.double() * (o / norms)[:, None]
+    if kind == "step":
+        want *= -lr * 0.2 * np.sqrt(l)
+    rounded = want.to(dt).double()
+    rho = float((rounded - want).norm() / want.norm())
+    err = float((rows - want).norm() / want.norm())
+    print(f"long rows {s} x {l} {prec} NS, {pdt} {kind}{' tall' if tall else ''}: {route} err {err:.2e} (rho {rho:.1e})", flush=True)
+    assert err <= TOL[prec] + rho
 
 
 def test_fp32_step_recovers_orthogonalised_update(muon):
