@@ -729,14 +729,6 @@ __device__ __forceinline__ void quad_transpose(float x[4]) {
 #endif
 // Epilogue outputs are written once and read by a later launch: streaming
 // (non-temporal) stores keep them from displacing operand data in L2.
-__device__ __forceinline__ void store_out(uint2* p, uint2 v) {
-  if (MUON_NT) {
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-  } else {
-    *p = v;
-  }
-}
 __device__ __forceinline__ void store_out(u32x4_t* p, u32x4_t v) {
   if (MUON_NT) __builtin_nontemporal_store(v, p);
   else *p = v;
@@ -1112,9 +1104,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   // every later product to that term's last bit (measured: up to 8 times the
   // error where a*X dominates), and b/c would be a rounded coefficient.
   constexpr bool EUPD = QTR;
-  constexpr int EPS = (BN / WN) / 64;           // P slabs holding a wave's columns of A
-  static_assert(EPS == 1 || EPS == 2, "A term: one or two slabs per wave");
-  constexpr int EJ = BJ / EPS;                  // 32-column blocks per such slab
+  static_assert(BN / WN == 64, "A term: a wave's columns of A are one P slab");
   constexpr int ERS = (BM / WM) / 64;           // Q slabs holding a wave's rows of X
   static_assert(ERS * 2 == BI, "X term: whole slabs per wave");
   constexpr bool epoly = EPI == EPI_POLY;
@@ -1123,9 +1113,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     e_ks0 = bm * (BM / 64) + ERS * wm;
     if (ERS > 1) e_ks1 = e_ks0 + 1;
   } else if (epoly) {
-    // the wave's BN / WN columns are EPS slabs of 64 k
-    e_ks0 = bn * (BN / 64) + wn * EPS;
-    if (EPS > 1) e_ks1 = e_ks0 + 1;
+    e_ks0 = bn * (BN / 64) + wn;
   }
   int eo[BJ][2];
   {
@@ -1139,7 +1127,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
                       ((2 * (wn * (BN / WN) + 32 * j) + 32 * (G & 1) + 8 * (L & 3)) ^ ((L >> 2) << 6));
         else       // P slab: row r holds chunk c at c ^ ((r >> 1) % 8)
           eo[j][gp] = (wm * (BM / WM) + 4 * (G >> 1) + (L >> 2)) * SLAB +
-                      (((4 * (j % EJ) + 2 * (G & 1) + ((L >> 1) & 1)) ^ (4 * gp + 2 * (G >> 1) + (L >> 3))) << 4) +
+                      (((4 * j + 2 * (G & 1) + ((L >> 1) & 1)) ^ (4 * gp + 2 * (G >> 1) + (L >> 3))) << 4) +
                       8 * (L & 1);
       }
   }
@@ -1156,26 +1144,25 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
     osc = EPI == EPI_GRAM ? r * r : r;
   }
   const float alpha = SPLIT && EUPD ? ga.alpha * osc : ga.alpha;
-  // Rows [i0, i0 + ni) and 32-column blocks [j0, j0 + nj) of the wave's
-  // accumulators take the term from the slab at sp.
-  auto add_e = [&](const char* sp, auto i0c, auto nic, auto j0c, auto njc) __attribute__((always_inline)) {
+  // Row blocks [i0, i0 + ni) of the wave's accumulators take the term from the
+  // slab at sp.
+  auto add_e = [&](const char* sp, auto i0c, auto nic) __attribute__((always_inline)) {
     constexpr int i0 = decltype(i0c)::value, ni = decltype(nic)::value;
-    constexpr int j0 = decltype(j0c)::value, nj = decltype(njc)::value;
     static_for<ni>([&](auto II) {
       constexpr int i = i0 + decltype(II)::value;
-      uint2 ev[nj][4];
-      static_for<nj>([&](auto J) {
+      uint2 ev[BJ][4];
+      static_for<BJ>([&](auto J) {
         static_for<4>([&](auto Gc) {
-          constexpr int jj = decltype(J)::value, j = j0 + jj, g = decltype(Gc)::value;
-          ev[jj][g] = EUPD ? tr_read_b64(sp + eo[j][0] + (32 * (i & 1) + 8 * g) * TRB)
+          constexpr int j = decltype(J)::value, g = decltype(Gc)::value;
+          ev[j][g] = EUPD ? tr_read_b64(sp + eo[j][0] + (32 * (i & 1) + 8 * g) * TRB)
                            : tr_read_b64(sp + eo[j][g & 1] + (32 * i + 8 * g) * SLAB);
         });
       });
-      static_for<nj>([&](auto J) {
+      static_for<BJ>([&](auto J) {
         static_for<4>([&](auto Gc) {
-          constexpr int jj = decltype(J)::value, j = j0 + jj, g = decltype(Gc)::value;
+          constexpr int j = decltype(J)::value, g = decltype(Gc)::value;
           float e[4];
-          unpack_bf16x4(ev[jj][g], e);
+          unpack_bf16x4(ev[j][g], e);
           f32x16_t& c = acc[i][j];
           c[4 * g + 0] = fmaf(alpha, e[0], c[4 * g + 0]);
           c[4 * g + 1] = fmaf(alpha, e[1], c[4 * g + 1]);
@@ -1254,23 +1241,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   auto take_e = [&](const char* sp, int ks) __attribute__((always_inline)) {
     if (ks == e_ks0 || ks == e_ks1) {  // wave-uniform; at most twice a tile
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (EUPD && ERS == 1) {
-        add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
-      } else if constexpr (EUPD) {
+      if constexpr (!EUPD || ERS == 1) {
+        add_e(sp, I_<0>{}, I_<BI>{});
+      } else {
         // (the comments keep the compiler from merging the two calls into one
         // with a run-time row block, which would put the accumulators in memory)
         if (ks == e_ks0) {
-          add_e(sp, I_<0>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
+          add_e(sp, I_<0>{}, I_<2>{});
           asm volatile("; row blocks 0, 1");
         } else {
-          add_e(sp, I_<2>{}, I_<2>{}, I_<0>{}, I_<BJ>{});
+          add_e(sp, I_<2>{}, I_<2>{});
           asm volatile("; row blocks 2, 3");
         }
-      } else if constexpr (EPS == 1) {
-        add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<BJ>{});
-      } else {
-        if (ks == e_ks0) add_e(sp, I_<0>{}, I_<BI>{}, I_<0>{}, I_<EJ>{});
-        else add_e(sp, I_<0>{}, I_<BI>{}, I_<EJ>{}, I_<EJ>{});
       }
     }
   };
@@ -1430,7 +1412,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
         take_e(smem + ERS * wm * OPSZ - OPQ, e_ks0);
         if (ERS > 1) take_e(smem + (ERS * wm + 1) * OPSZ - OPQ, e_ks1);
       } else {
-        static_assert(EPS == 1, "A term: one slab per wave");
         take_e(smem + wn * OPSZ, e_ks0);
       }
       __syncthreads();
