@@ -886,7 +886,7 @@ muon_status_t execute(muon_handle_t h, const std::vector<Item>& items, const Pla
   // Units of work, in plan order: one chunk, or a group of chunks whose
   // products run as one launch per product and step (muon::run_group):
   // chunks whose Gram launch leaves CUs idle in its last round (occupancy
-  // below 0.9), that can share the 256 x 256 kernel, with the same step
+  // below 0.9), that can share 256 x 256 tiles, with the same step
   // count and parameter dtype, at most kGroupMax to a group, where that takes
   // less time than one by one (muon::group_pays).  A group's
   // members each keep their own workspace region.  Groups are formed when

@@ -106,7 +106,7 @@ inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 // Norm partial sums per matrix: one per 64x64 tile of the padded extent.
 inline int64_t norm_tiles(int64_t S, int64_t L) { return (S / 64) * (L / 64); }
 
-// The 256 x 256 kernel addresses a tile's 256 rows (operands, the a*X
+// The tile kernel addresses a tile's (up to) 256 rows (operands, the a*X
 // term, the parameter block) by 32-bit offsets from one base, so every row
 // it reads or writes must be shorter than 2^31 / 256 bytes.
 constexpr int64_t kTileMaxRowBytes = (int64_t(1) << 31) / 256;
@@ -178,7 +178,7 @@ inline bool chunk_is_sliced(int64_t s, int64_t l, bool ns_f32, int K) {
 }
 
 // A group: chunks whose products of each Newton-Schulz step run as one
-// launch per product (the 256 x 256 kernel over all their tiles).  Each
+// launch per product (256 x 256 tiles of all of them).  Each
 // member has its own workspace; they share the step count, the NS precision
 // (bf16) and the parameter dtype.
 struct GroupMember {
@@ -188,7 +188,7 @@ struct GroupMember {
   const float* coeffs;  // host, K x 3
 };
 constexpr int kGroupMax = 8;
-// A chunk can join a group: bf16 NS on the 256 x 256 kernels (padded
+// A chunk can join a group: bf16 NS on the tile kernel (padded
 // extents multiples of 256, rows within its offsets), at least one step,
 // not a fused small-matrix chunk.
 bool group_eligible(const ChunkGeom& g, int K);

@@ -462,7 +462,7 @@ struct GemmArgs {
   int32_t final_kind, param_dtype, w_rows16;
   int32_t s, l;
   int32_t total_tiles;                           // tiles_per_mat * matrices
-  // operand storage, 256 x 256 kernel only: 0 row-major over K; 1 symmetric,
+  // operand storage, tile kernel only: 0 row-major over K; 1 symmetric,
   // upper-triangle 256 x 256 tiles only; 2 (Q) stored K x N
   int32_t p_mode, q_mode;
   // SPLIT kernels: bytes from one plane of the operand or output to the next
@@ -663,28 +663,34 @@ __global__ __launch_bounds__(256, 2) void k_gemm_nt(GemmArgs ga) {
 }
 
 // ---------------------------------------------------------------------------
-// bf16 C = P Q^T with a 256 x 256 output tile per workgroup (M and N
-// multiples of 128).  512 threads = 8 wavefronts in a 2 x 4 grid, each owning
-// a 128 x 64 sub-tile = 4 x 2 blocks of v_mfma_f32_32x32x16_bf16, so every
-// operand fragment read from LDS feeds two or four MFMAs.
+// The tile kernel: C = P Q^T on v_mfma_f32_32x32x16_bf16, extents multiples of
+// 128, operands bf16 or (SPLIT) fp32 in three bfloat16 planes.  The tiles of a
+// workgroup, one of three configurations (TileCfg; the choice is tiles_of):
+//   256 x 256   512 threads = 8 wavefronts in a 2 x 4 grid, each owning a 128 x
+//               64 sub-tile = 4 x 2 blocks of 32 x 32, so every operand fragment
+//               read from LDS feeds two or four MFMAs; one workgroup per CU;
+//   128 x 128   256 threads = 4 wavefronts of 64 x 64, two workgroups per CU, or
+//               one with four LDS stages.
+// An element sees the same operations in the same order on all of them.
 //
 // K is staged 64 elements (128 bytes per row) at a time with direct
 // global-to-LDS loads (global_load_lds_dwordx4: lane i of a wavefront writes
-// bytes [16 i, 16 i + 16) after the wave-uniform LDS base), double-buffered.
-// A wavefront instruction fills 8 consecutive tile rows; lane i fetches the
-// 16-byte k-chunk (i % 8) ^ ((row >> 1) % 8) of its row, so LDS row r holds
-// chunk c at position c ^ ((r >> 1) % 8).  A fragment read (32 rows, one
-// chunk) then spreads over all 64 banks.
+// bytes [16 i, 16 i + 16) after the wave-uniform LDS base), double-buffered (or
+// in four stages).  A wavefront instruction fills 8 consecutive tile rows; lane
+// i fetches the 16-byte k-chunk (i % 8) ^ ((row >> 1) % 8) of its row, so LDS
+// row r holds chunk c at position c ^ ((r >> 1) % 8).  A fragment read (32 rows,
+// one chunk) then spreads over all 64 banks.
 //
-// The launch is persistent (one workgroup per CU).  Workgroup b runs on XCD
+// The launch is persistent (one workgroup per CU slot).  Workgroup b runs on XCD
 // b % 8; every round, the workgroups of one XCD take one compact block of the
 // tile order (bands 8 tile-rows high), so they share operand panels in that
 // XCD's L2.
 //
-// The epilogue works on the accumulator registers directly: lane l holds
-// rows 8*(r/4) + 4*(l/32) + (r%4) of column l%32 in register r of a block, so
-// 4 consecutive registers are 4 consecutive elements of a row of the
-// transposed tile; a 4-lane transpose (DPP) gives the direct orientation.
+// The epilogue starts from the accumulator registers: lane l holds rows 8*(r/4)
+// + 4*(l/32) + (r%4) of column l%32 in register r of a block, so 4 consecutive
+// registers are 4 consecutive rows of one column.  Outputs go to LDS as they are
+// and leave as whole rows through transposing LDS reads; the last step's go
+// through LDS in the parameter's own layout.
 // ---------------------------------------------------------------------------
 // Compile-time loop: f(std::integral_constant<int, 0>) ... f(<N-1>), so array
 // indices inside f are constants whatever the unroller decides.
@@ -929,7 +935,9 @@ __device__ __forceinline__ void tile_from_logical(const GemmArgs& ga, int logica
 
 // SPLIT: the operands and outputs are fp32 values in three bfloat16 planes
 // (Split3), and each product of values is the six bfloat16 products whose
-// weight is above 2^-24.  A first pass over k adds the five small ones, per
+// weight is above 2^-24 (the method of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
+// ARITH 2019).  A first pass over k adds the five small ones, per
 // slab of 64 k in the order
 //   (P, Q) = (h, l) (h, m) (m, m) (m, h) (l, h),
 // in which one operand changes at a time (six operand slabs loaded for five
@@ -1433,8 +1441,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& ga, char* smem, i
   //  - The last step's parameter update runs in the parameter's layout:
   //    direct when it is s x l, natural when it is l x s.
   const bool diag = ga.syrk && bm == bn;
-  // The 256 x 256 kernel reads the diagonal 256 x 256 blocks of A and B
-  // whole: of such a block, the 128 x 128 kernel also writes the quarter below
+  // 256 x 256 tiles read the diagonal 256 x 256 blocks of A and B
+  // whole: of such a block, a launch on 128 x 128 tiles also writes the quarter below
   // the diagonal, the mirror of its (even, odd) tile.
   const bool pair_mirror = BM == 128 && ga.syrk && (bm & 1) == 0 && bn == bm + 1;
   const MatDesc* md = FINAL ? ga.desc + mat : nullptr;
@@ -1862,7 +1870,7 @@ hipError_t launch_tile(int epi, GemmArgs ga, int nmat, hipStream_t st, double& e
   return hipGetLastError();
 }
 
-// The products of one step for a group of chunks on the 256 x 256 kernel:
+// The products of one step for a group of chunks on 256 x 256 tiles:
 // each chunk's arguments prepared as launch_tile prepares them, one
 // persistent launch over all their tiles.  The chunks share the product, the
 // final kind and the parameter dtype.
@@ -2003,7 +2011,8 @@ struct Timed {
 };
 
 // ---------------------------------------------------------------------------
-// Fused Newton-Schulz for short sides up to 128 (k_ns_small): the whole step
+// Fused Newton-Schulz for the smaller matrices of short side up to 128
+// (k_ns_small; which, chunk_is_small): the whole step
 // of a chunk -- momentum, norm, X0, every Newton-Schulz step and the update --
 // in one launch.  Such matrices are far too small for the tile kernels: a
 // 128 x 256 fp32 product fills one or two workgroups, so separate launches
@@ -2431,20 +2440,24 @@ __global__ __launch_bounds__(256) void k_ns_small(SmallArgs sa) {
 // 128 x 4096) and half-empty update tiles; here X is cut into column slices
 // of 64 KB, one per workgroup, and a step is two launches over all matrices:
 //   k_slice_reduce  A = sum of the slices' Gram partials (fp32, in slice
-//                   order; r^2 on the first step), stored as bf16, whole;
-//   k_slice_step    per slice: B = b A + c A A (32 KB of A: cheaper to form
+//                   order; r^2 on the first step), stored whole in the
+//                   iterate's type;
+//   k_slice_step    per slice: B = b A + c A A (up to 32 KB of A in bf16, 64 in
+//                   fp32: cheaper to form
 //                   in each workgroup than to launch for), X' = a X + B X in
 //                   LDS, X' to memory, and the Gram partial of X'; the last
 //                   step writes the parameter (or output) instead.
 // k_slice_first does the prologue (momentum, u, its square sum) and the first
 // Gram partial while the slice is in LDS.  The slice width is a function of
-// the short side alone, so results do not depend on the batch.
+// the short side, the precision and the step alone, so results do not depend on
+// the batch.
 // What bounds it: the launches (about 4 us each, 2 K + 2 of them) for a few
 // matrices, HBM and L2 traffic of the slices for many.
 //
-// RB: 32-row blocks of the padded short side (1, 2 or 4).  A slice has
-// w = 1024 / RB columns; wavefront v of 8 owns columns [v w/8, (v + 1) w/8)
-// in the update.  LDS row r of a slice holds 16-byte chunk c at position
+// RB: 32-row blocks of the padded short side (1, 2 or 4).  A wavefront owns 128 /
+// RB columns of its slice in the update.  bf16 slices have 8 wavefronts (1024 /
+// RB columns, 64 KB), in the last step 4 (32 KB); fp32 ones always 4 (512 / RB
+// columns, 64 KB): SliceCfg.  LDS row r of a slice holds 16-byte chunk c at position
 // c ^ key(r), key(r) = 4 (r % 4) + (r / 4) % 4: the transposing reads of
 // 32 columns x 4 rows, the fragment reads of 32 rows x 16 bytes and the 8-byte
 // accesses of 32 rows all spread over the banks.
@@ -3178,7 +3191,7 @@ hipError_t run_prologue_t(const ChunkGeom& cg, const MatDesc* d_desc, const Chun
   using E = typename Store<XT>::E;
   const double gsz = sizeof(GT), xsz = sizeof(E) * Store<XT>::planes;
   const double psz = cg.param_dtype == DT_BF16 ? 2.0 : 4.0;
-  // On the 256 x 256 kernel the update products read X through transposing
+  // On the tile kernel the update products read X through transposing
   // LDS reads, so no X^T is kept (K = 0 applies X0 from whichever layout
   // matches the parameter).
   const bool qtr = runs_on_tiles<XT>(cg, K);
@@ -3265,7 +3278,7 @@ StepProducts step_products(const ChunkGeom& cg, const MatDesc* d_desc, const Chu
   g.p_plane = g.q_plane = planeX; g.c_plane = planeA;
   g.xscale = k == 0 ? wb.xscale : nullptr;  // A0 = r^2 X~ X~^T
   g.rscale = u.rscale = planes == 3 ? wb.rscale : nullptr;
-  // Under qtr every consumer of A and B runs on the 256 x 256 kernel and
+  // Under qtr every consumer of A and B runs on the tile kernel and
   // reads them as upper-triangle tiles (mode 1): no mirrored tile is
   // written.  Otherwise the lower triangle is written as the mirror.
   if (!qtr) { g.CT = g.C; g.ct_mat = matA; g.ldct = g.ldc; }

@@ -123,9 +123,9 @@ def test_upper_tile_path_orthogonalize_matches_oracle(muon):
 
 
 def test_upper_tile_path_zero_c_steps_match_oracle(muon):
-    # Steps with c = 0 (the cubic iteration) read the polynomial's A term in
-    # the epilogue; steps with c != 0 add it to the accumulators in the main
-    # loop.  Both kinds in one schedule.
+    # Steps with c = 0 (the cubic iteration) have no polynomial product, only
+    # a scaling of A; steps with c != 0 add the A term to the accumulators in
+    # the main loop.  Both kinds in one schedule.
     coeffs = [(3.4445, -4.7750, 2.0315)] * 3 + [(1.5, -0.5, 0.0)] * 3
     G, outs = run_orth(muon, UPPER_SHAPES, "bf16", "bf16", ns_steps=len(coeffs), coeffs=coeffs, key=22)
     for s, g, o in zip(UPPER_SHAPES, G, outs):
@@ -261,7 +261,7 @@ def test_custom_per_step_coefficients(muon):
 @pytest.mark.parametrize("steps", [1, 2])
 def test_one_and_two_steps_match_oracle(muon, steps, prec):
     # K = 1: the first step is also the last, so the last-step kernel applies
-    # the norm scale r itself (on the 256 x 256 kernel for the bf16 upper
+    # the norm scale r itself (on the tile kernel for the bf16 upper
     # shapes, on the 128 x 128 kernel otherwise); K = 2: one exchange of the
     # ping-pong iterates.  Both the parameter update and the standalone
     # orthogonalisation, whose last kernel writes O.

@@ -1,10 +1,9 @@
-"""The fused small-matrix launch (short side <= 128; always for fp32
-Newton-Schulz, for bf16 when the short side is <= 64 or the long side <= 512):
-element-wise parity with the oracle over short sides 1..128 and long sides
-128..2048, both orientations, K = 0, 1 and 5; many matrices sharing groups of
-workgroups; batching and repeat determinism.  The bf16 shapes cover both the
-fused launch and, for 128 x 2048 and 2048 x 128, the 128 x 128 tile kernel,
-against the bf16 gate."""
+"""Short sides up to 128: element-wise parity with the oracle over short sides
+1..128 and long sides 128..2048, both orientations, K = 0, 1 and 5; many matrices
+sharing groups of workgroups; batching and repeat determinism.  The shapes
+lie on both sides of the line between the fused launch (K = 0, and the smaller
+ones, 64 x 300 say) and the column slices (64 x 2048), in both precisions, each
+against its gate."""
 import numpy as np
 import pytest
 
