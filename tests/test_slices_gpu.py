@@ -7,9 +7,10 @@ and each result in a batch bit for bit the one it has alone.
 
 A wide matrix of few rows has nearly equal singular values, which take the
 roundings of X, A and B coherently: bf16 storage alone, emulated on the CPU,
-leaves 2.7e-2 on the 32 x 2100 input here.  The gate is therefore the flat
-2e-2 or 1.25 times the emulated storage error of the very input, whichever is
-more (the factor of tests/bf16_pipeline.py, for sums in another order)."""
+leaves 2.7e-2 on the 32 x 2100 input here.  The gate of short sides up to 64 is
+therefore the flat 2e-2 or 1.25 times the emulated storage error of the very
+input, whichever is more (the factor of tests/bf16_pipeline.py, for sums in
+another order; it is more for short sides up to 50 here); beyond, 2e-2."""
 import numpy as np
 import pytest
 
@@ -56,7 +57,7 @@ def test_slices_match_oracle_and_do_not_depend_on_the_batch(muon, steps, scale, 
             assert np.array_equal(to_bits(outs[3 * i + k]), to_bits(one)), (s, k)
         x = decode(g, "f32")
         err, gate = o_gate(to_host(one), ref.orthogonalize(x, steps), "f32", prec, steps, G=x)
-        if prec == "bf16":
+        if prec == "bf16" and min(s) <= 64:
             gate = max(gate, FEW_SV_MARGIN * storage_error(x, steps))
         print(f"slices {prec} K={steps} x{scale:g} {s}: O err {err:.2e}", flush=True)
         assert err <= gate, (s, err, gate)
@@ -88,7 +89,9 @@ def test_slices_step_matches_oracle(muon, pdt, gdt, prec):
         err, rho = w_gate(to_host(w_dev), r.W_new, W0, pdt)
         print(f"slices step {pdt}/{gdt} {prec} {s}: W err {err:.2e} (rho {rho:.1e})", flush=True)
         u = 0.05 * decode(g, gdt) + 0.95 * r.buf_new
-        gate = tol_for(prec, s) if prec == "f32" else max(tol_for(prec, s), FEW_SV_MARGIN * storage_error(u))
+        gate = tol_for(prec, s)
+        if prec == "bf16" and min(s) <= 64:
+            gate = max(gate, FEW_SV_MARGIN * storage_error(u))
         assert err <= gate + rho, (s, err, gate, rho)
         assert rel(to_host(b_dev), r.buf_new) <= MOMENTUM_TOL, s
         assert np.array_equal(to_bits(w_view.contiguous()), to_bits(w_dev)), s
