@@ -192,8 +192,8 @@ muon_status_t muon_set_streams(muon_handle_t h, int streams);
  * call that leave compute units idle (as above), run their Newton-Schulz
  * products on the 256 x 256 tile kernels (bf16 NS, padded extents multiples
  * of 256) and share the step count and parameter dtype are run together,
- * up to 8 at a time: per step, one launch per product over the tiles of all
- * of them.  With two streams such chunks overlap on the streams instead.
+ * up to 8 at a time, where a cost model says that this takes less time: per
+ * step, one launch per product over the tiles of all of them.  With two streams such chunks overlap on the streams instead.
  * Each member keeps its own workspace region, so the call's workspace can
  * exceed what muon_plan_step reports by the sum of those chunks' sizes
  * (never beyond the workspace limit: then the chunks run one by one).
