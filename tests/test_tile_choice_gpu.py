@@ -88,3 +88,27 @@ def test_every_configuration_gives_the_same_bits(shape, prec, monkeypatch, capfd
         kinds = {r[product] for r in seen}
         assert kinds >= ({"256", "128", "128x4"} if prec == "bf16" else {"256", "128"}), (product, seen)
     assert any(r[0] == r[1] != r[2] for r in seen)  # A and B written by one, read by another
+
+
+# The lines between the routes, where both sides were measured: one fp32 matrix
+# took up to 40% longer in slices below these, and two 4096^2 beside a 4096 x 11008
+# 3% longer on 128 x 128 tiles at a near tie (0.96) of the model.
+@pytest.mark.parametrize("n,s,l,prec,want", [
+    (1, 32, 576, "f32", "fused"), (1, 32, 577, "f32", "slices"), (1, 64, 768, "f32", "fused"), (1, 64, 769, "f32", "slices"),
+    (1, 65, 1025, "f32", "fused"), (1, 96, 1536, "f32", "fused"), (1, 96, 1537, "f32", "slices"),
+    (1, 97, 1408, "f32", "fused"), (1, 128, 1409, "f32", "slices"), (1, 32, 256, "bf16", "fused"),
+    (1, 32, 257, "bf16", "slices"), (1, 33, 384, "bf16", "fused"), (1, 128, 385, "bf16", "slices"),
+    (2, 4096, 4096, "bf16", ("256", "256", "256")), (1, 1024, 4096, "bf16", ("128x4", "128x4", "128x4"))])
+def test_routes_at_the_lines(n, s, l, prec, want, monkeypatch, capfd):
+    require_gpu()
+    import torch
+    from paper_2609_21594_amd.binding import Muon
+    routes = route_recorder(monkeypatch, capfd)
+    m = Muon(0)
+    try:
+        ins = [torch.randn(s, l, device="cuda") for _ in range(n)]
+        m.orthogonalize(ins, [torch.empty_like(t) for t in ins], ns_steps=1, ns_precision=prec)
+        torch.cuda.synchronize()
+    finally:
+        m.close()
+    assert routes()[n, s, l] == want
